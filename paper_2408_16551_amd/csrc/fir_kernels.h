@@ -234,9 +234,14 @@ struct BufSink {
     int32_t ldy4, ldq, nsc;  // row strides (bytes)
     __device__ __forceinline__ void y(int u, const V& v) const {
         constexpr int aux = NT ? kNtAux : 0;
+        // 16-byte stores take the row offset in the VGPR: the compiler leaves no
+        // wait state between a store of more than 8 bytes with an SGPR offset and
+        // the next write of its data registers, and the chip then stored the
+        // overwritten first 8 bytes in lanes 12-15 of each 16 (1-3 frames in
+        // 10^5).  With a constant offset it does.
         if constexpr (VEC == 4)
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((ext_vector_type(4))) uint32_t, v),
-                                                   ry, vy, u * ldy4, aux);
+                                                   ry, vy + (uint32_t)(u * ldy4), 0, aux);
         else if constexpr (VEC == 2)
             __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(__attribute__((ext_vector_type(2))) uint32_t, v),
                                                   ry, vy, u * ldy4, aux);
