@@ -137,7 +137,15 @@ typedef struct tina_pfb_desc {
 
 /* How the DFT across branches is computed (both give the DFT of Eq. (12)):
  *   TINA_DFT_DENSE     the dense matrix product X = Y F on the MFMA units, in the
- *                      plan's precision (the paper's pointwise-convolution mapping);
+ *                      plan's precision (the paper's pointwise-convolution mapping).
+ *                      From 256 channels, FP32, BF16 and BF16X3 use the symmetry of
+ *                      F: around the half sample its columns are even or odd in p
+ *                      and under p -> P/2 - 1 - p, so the FIR writes four sums of
+ *                      every four samples (FP32, then rounded to the operand type)
+ *                      and four products of size P/4 replace the one of size P,
+ *                      with a rotation of each channel at the end.  A frame with an
+ *                      infinite or NaN sample gives non-finite channels either way;
+ *                      which of them are infinite and which NaN is not specified;
  *   TINA_DFT_FACTORED  a factored (four-step) DFT, P = P1 * P2: P2 DFTs of size
  *                      P1, twiddles, P1 DFTs of size P2, each size-P1/P2 DFT a
  *                      small matrix product on the MFMA units in FP32 -- 8 P (P1 + P2)
@@ -145,15 +153,11 @@ typedef struct tina_pfb_desc {
  *                      Also in FP32 batches (one launch per channel count and
  *                      input type over those items' frames) and in an FP32
  *                      server created with this algorithm.
- *   TINA_DFT_FUSED     the dense product with the polyphase FIR fused into it:
- *                      each matrix-product tile forms its rows of FIR output
- *                      from the input stream in on-chip memory (a sliding
- *                      window over the frames staged in LDS), so the FIR output
- *                      never goes to HBM.  Results are bit for bit those of
- *                      TINA_DFT_DENSE.  FP32, taps <= 16, single-stream
- *                      execute; a call whose input is not 16-byte aligned (or
- *                      whose residue leaves the history a partial float4) runs
- *                      the two-kernel path instead.
+ *   TINA_DFT_FUSED     the dense FP32 product for taps <= 16 and single-stream
+ *                      execute, bit for bit TINA_DFT_DENSE.  It runs the FIR and
+ *                      the product as two kernels like TINA_DFT_DENSE: a product
+ *                      with the FIR inside its tiles forms each FIR row once per
+ *                      column tile and measured slower at every size.
  *   TINA_DFT_COMPENSATED the dense FP32 product with compensated accumulation
  *                      over K: each K tile of 32 products is summed on its
  *                      own, and the tile sums are added to the running sum
@@ -165,11 +169,11 @@ typedef struct tina_pfb_desc {
  *                      dynamic range).  FP32 only; single-stream execute.
  *   TINA_DFT_TABLE     the dense FP32 product with the operand F of Eq. (12)
  *                      never materialised: each matrix-product tile assembles
- *                      its operand rows in on-chip memory from a P-entry
- *                      twiddle table (cos, sin of 2 pi r / P, r = p k mod P),
- *                      8 P bytes instead of the N x K operand (256 MiB at
- *                      P = 4096 complex).  Same entries, so results are bit
- *                      for bit those of TINA_DFT_DENSE.  FP32 only;
+ *                      its operand rows in on-chip memory from a table of 8 P
+ *                      bytes (below 256 channels cos and sin of 2 pi r / P, r < P;
+ *                      from 256 on cos(pi r / P), r < 2P) instead of reading the
+ *                      operand (16 MiB at P = 4096).  Same entries, so results are
+ *                      bit for bit those of TINA_DFT_DENSE.  FP32 only;
  *                      single-stream execute. */
 typedef enum tina_dft_algorithm {
     TINA_DFT_DENSE = 0,

@@ -98,16 +98,19 @@ struct tina_pfb_batch_s {
     bool have_tune = false;
     // Captured step graphs (the launches of one step; the table upload stays
     // outside), keyed by the kernel variant: tap ring, exact taps, launch
-    // shape.  gemm_node: the GEMM launch, whose grid is set to each step's own
-    // tile count before the replay.
+    // shape, stages.  gemm: the dense and the folded product's launches, whose
+    // grids are set to each step's own tile counts before the replay.
     struct StepGraph {
         hipGraph_t graph = nullptr;  // kept: its nodes name the executable graph's nodes
         hipGraphExec_t exec = nullptr;
-        hipGraphNode_t gemm_node = nullptr;
-        hipKernelNodeParams gemm_params{};
+        struct Gemm {
+            hipGraphNode_t node = nullptr;
+            hipKernelNodeParams params{};
+        } gemm[2];  // dense, folded
     };
     std::map<std::string, StepGraph> graphs;
     int64_t graph_gemm_grid = 0;  // GEMM grid the step graphs are captured with (0: no graphs)
+    int64_t graph_fold_grid = 0;  // folded product's grid in them
     bool frame_stage = true;      // long per-frame scaled items run the single-pass frame stage
     int64_t frame_stage_min = 2048;  // frames an item needs to run the frame stage
     int frame_tf_target = 128;       // frames per frame-stage unit (rounded up to whole ring blocks of M)
@@ -233,7 +236,8 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
     // K is a whole number of their K tiles (else all take 128 x 128 tiles).
     int wbm = kGemmBM, wbn = tune.gemm_tile_n;
     wide = form_fir_qmode(b->form) != 0;
-    for (int i = 0; i < g.count && wide; ++i) wide = gemm_batch_wide_tile(b->form, w[g.first + i].plan->K, wbm, wbn);
+    for (int i = 0; i < g.count && wide; ++i)
+        if (!w[g.first + i].plan->fold) wide = gemm_batch_wide_tile(b->form, w[g.first + i].plan->K, wbm, wbn);
     const int tile_m = wide ? wbm : kGemmBM, tile_n = wide ? wbn : tune.gemm_tile_n;
     max_m = 1;
     for (int i = 0; i < g.count; ++i) max_m = std::max(max_m, w[g.first + i].plan->M);
@@ -247,10 +251,10 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
         return tune.fir_tf_mult * ring < 16 ? ((16 + ring - 1) / ring) * ring : tune.fir_tf_mult * ring;
     };
 
-    std::vector<int64_t> fu(g.count), gu(g.count), su(g.count), ru(g.count);
+    std::vector<int64_t> fu(g.count), gu(g.count), su(g.count), ru(g.count), ffu(g.count), gfu(g.count);
     std::vector<int> fft_items;  // items taking the factored DFT
     std::vector<double> fc(g.count), gc(g.count), sc(g.count, 1.0), rc(g.count, 1.0);
-    int64_t ws_off = 0, amax_off = 0, f0 = 0, g0 = 0, s0 = 0, r0 = 0;
+    int64_t ws_off = 0, amax_off = 0, f0 = 0, g0 = 0, s0 = 0, r0 = 0, ff0 = 0, gf0 = 0;
     for (int i = 0; i < g.count; ++i) {
         tina_pfb_work& it = w[g.first + i];
         tina_pfb_plan_s* p = it.plan;
@@ -307,6 +311,7 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
         ga.Aq1 = fa.q1;
         ga.Aqs = fa.qs;
         ga.fexp = fa.fexp;
+        if (p->fold) ga.tw = p->fold_tw;
         // Per-frame scaled items with frame rows of 1024 threads and at least
         // frame_stage_min frames run in one pass (frame stage, units of about
         // frame_tf_target frames); the others in the three FIR launches
@@ -316,7 +321,18 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
         bi.fir_single = (b->frame_stage && form_scaled(b->form) && F >= b->frame_stage_min &&
                          fir_frame_batch_vec(fa) != 0) ? 1 : 0;
         bi.frame_unit0 = r0;
-        if (bi.fir_single) {
+        bi.ffold_unit0 = ff0;
+        bi.gfold_unit0 = gf0;
+        ffu[i] = gfu[i] = 0;
+        if (p->fold) {  // whole ring blocks of the item's own M (32 or 64 beyond 16 taps)
+            const int ring = p->M <= 16 ? p->M : p->M <= 32 ? 32 : 64;
+            const int TF = frames_per_thread(ring);
+            bi.fir_tf = TF;
+            ffu[i] = (F + TF - 1) / TF * (p->W / 256);
+            gfu[i] = (F * p->cf + kFoldBM - 1) / kFoldBM * ((p->N + kFoldBJ - 1) / kFoldBJ);
+            fu[i] = ru[i] = 0;
+            fc[i] = (double)TF * ring;
+        } else if (bi.fir_single) {
             const int TF = p->M * ((b->frame_tf_target + p->M - 1) / p->M);
             bi.fir_tf = TF;
             fu[i] = 0;
@@ -333,8 +349,10 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
             ru[i] = 0;
         }
         r0 += ru[i];
+        ff0 += ffu[i];
+        gf0 += gfu[i];
         const bool factored = p->dft_algorithm == TINA_DFT_FACTORED;
-        gu[i] = (F > 0 && !factored) ? ((F + tile_m - 1) / tile_m) * ((p->N + tile_n - 1) / tile_n) : 0;
+        gu[i] = (F > 0 && !factored && !p->fold) ? ((F + tile_m - 1) / tile_m) * ((p->N + tile_n - 1) / tile_n) : 0;
         if (factored && F > 0) fft_items.push_back(i);
         gc[i] = (double)p->K;
         bi.fir_unit0 = f0;
@@ -395,8 +413,12 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
     t->gemm_units = g0;
     t->st_units = s0;
     t->frame_units = r0;
+    t->ffold_units = ff0;
+    t->gfold_units = gf0;
     split_by_cost(fu, fc, t->fir_bounds);
     split_by_cost(ru, rc, t->frame_bounds);
+    split_by_cost(ffu, fc, t->ffold_bounds);
+    split_by_cost(gfu, gc, t->gfold_bounds);
     split_by_cost(gu, gc, t->gemm_bounds);
     split_by_cost(su, sc, t->st_bounds);
 }
@@ -425,42 +447,61 @@ std::vector<GroupPlan> make_groups(tina_pfb_batch_s* b, tina_pfb_work* w, const 
 
 // Blocks of the batched GEMM launch: 8 x the largest XCD range (one block per
 // tile), or the fixed bound of a captured step graph.
-int64_t gemm_grid(const BatchTable* t) {
+int64_t range_grid(const int64_t (&bounds)[9]) {
     int64_t mx = 0;
-    for (int x = 0; x < 8; ++x) mx = std::max(mx, t->gemm_bounds[x + 1] - t->gemm_bounds[x]);
+    for (int x = 0; x < 8; ++x) mx = std::max(mx, bounds[x + 1] - bounds[x]);
     return 8 * std::max<int64_t>(mx, 1);
 }
+int64_t gemm_grid(const BatchTable* t) { return range_grid(t->gemm_bounds); }
+int64_t fold_grid(const BatchTable* t) { return range_grid(t->gfold_bounds); }
 
+// Stages of a step: the dense product's FIR and GEMM, the folded product's,
+// the state update.
+enum : int { STAGE_DENSE = 1, STAGE_FOLD = 2, STAGE_STATE = 4 };
+int table_stages(const BatchTable* t) {
+    return (t->fir_units > 0 || t->frame_units > 0 || t->gemm_units > 0 ? STAGE_DENSE : 0) |
+           (t->ffold_units > 0 ? STAGE_FOLD : 0) | (t->st_units > 0 ? STAGE_STATE : 0);
+}
+
+// always: every launch of `stages` (captured steps, warm-up), with the fixed
+// grids given.
 tina_status launch_stages(tina_pfb_batch_s* b, hipStream_t s, const Tune& tune, int max_m, bool all_exact,
-                          bool wide, bool always, int64_t fixed_gemm_grid = 0) {
+                          bool wide, int stages, bool always, int64_t fixed_gemm_grid = 0, int64_t fixed_fold_grid = 0) {
     const int grid_fir = b->cus * 4;
     const int64_t grid_gemm = fixed_gemm_grid > 0 ? fixed_gemm_grid : gemm_grid(b->h_table);
+    const int64_t grid_fold = fixed_fold_grid > 0 ? fixed_fold_grid : fold_grid(b->h_table);
     const int qmode = form_fir_qmode(b->form);
-    if (always || b->h_table->fir_units > 0 || b->h_table->frame_units > 0)
+    if (stages & STAGE_FOLD) HIP_TRY(launch_fir_fold_batch(b->d_table, max_m, qmode, grid_fir, s));
+    if ((stages & STAGE_DENSE) && (always || b->h_table->fir_units > 0 || b->h_table->frame_units > 0))
         HIP_TRY(launch_fir_batch(b->d_table, max_m, all_exact, qmode, grid_fir, s, b->frame_stage));
-    if (always || b->h_table->gemm_units > 0)
+    if (stages & STAGE_FOLD) HIP_TRY(launch_fold_gemm_batch(b->d_table, b->form, (int)grid_fold, s));
+    if ((stages & STAGE_DENSE) && (always || b->h_table->gemm_units > 0))
         HIP_TRY(launch_gemm_batch(b->d_table, b->form, qmode != 0, tune.gemm_tile_n, (int)grid_gemm, s, wide));
     if (!always)  // factored-DFT items: never in a captured step (the groups change from call to call)
         for (const tina_pfb_batch_s::FftGroup& fg : b->fft_groups)
             HIP_TRY(launch_fft_batch(fft_rows(b->d_table, b->h_table->n_items) + fg.first, fg.count, fg.F, fg.P,
                                      fg.cplx, fg.q64_ok, fg.mat1, fg.mat3, fg.tw, b->cus, s));
-    if (always || b->h_table->st_units > 0) HIP_TRY(launch_gather_batch(b->d_table, b->cus * 2, s));
+    if (stages & STAGE_STATE) HIP_TRY(launch_gather_batch(b->d_table, b->cus * 2, s));
     return TINA_OK;
 }
 
 // The captured step graph of one kernel variant (tap ring, exact taps,
-// launch shape), captured and instantiated on first use.  The GEMM launch is
-// found among the graph's kernel nodes by its grid (graph_gemm_grid is kept
-// apart from the fixed grids of the other stages).
+// launch shape, stages), captured and instantiated on first use.  The GEMM
+// launches are found among the graph's kernel nodes by their grids
+// (graph_gemm_grid and graph_fold_grid are kept apart from each other and from
+// the fixed grids of the other stages).
 tina_status step_graph(tina_pfb_batch_s* b, hipStream_t s, const Tune& tune, int max_m, bool all_exact, bool wide,
-                       tina_pfb_batch_s::StepGraph*& out) {
+                       int stages, tina_pfb_batch_s::StepGraph*& out) {
+    stages |= STAGE_STATE;
+    if (!(stages & (STAGE_DENSE | STAGE_FOLD))) stages |= STAGE_DENSE;  // a step of state updates alone
     const std::string key = std::to_string(pow2_at_least(max_m)) + (all_exact ? "e" : "p") + (wide ? "w" : "n") +
-                            ":" + std::to_string(tune.fir_tf_mult) + ":" + std::to_string(tune.gemm_tile_n);
+                            ":" + std::to_string(tune.fir_tf_mult) + ":" + std::to_string(tune.gemm_tile_n) + ":" +
+                            std::to_string(stages);
     auto it = b->graphs.find(key);
     if (it == b->graphs.end()) {
         hipGraph_t graph = nullptr;
         HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-        tina_status st = launch_stages(b, s, tune, max_m, all_exact, wide, true, b->graph_gemm_grid);
+        tina_status st = launch_stages(b, s, tune, max_m, all_exact, wide, stages, true, b->graph_gemm_grid, b->graph_fold_grid);
         hipError_t e2 = hipStreamEndCapture(s, &graph);
         if (st != TINA_OK || e2 != hipSuccess) {
             if (graph) (void)hipGraphDestroy(graph);
@@ -475,10 +516,12 @@ tina_status step_graph(tina_pfb_batch_s* b, hipStream_t s, const Tune& tune, int
             hipGraphNodeType ty;
             if (hipGraphNodeGetType(nodes[i], &ty) != hipSuccess || ty != hipGraphNodeTypeKernel) continue;
             hipKernelNodeParams kp{};
-            if (hipGraphKernelNodeGetParams(nodes[i], &kp) == hipSuccess && (int64_t)kp.gridDim.x == b->graph_gemm_grid) {
-                sg.gemm_node = nodes[i];
-                sg.gemm_params = kp;
-            }
+            if (hipGraphKernelNodeGetParams(nodes[i], &kp) != hipSuccess) continue;
+            for (int k = 0; k < 2; ++k)
+                if ((int64_t)kp.gridDim.x == (k ? b->graph_fold_grid : b->graph_gemm_grid)) {
+                    sg.gemm[k].node = nodes[i];
+                    sg.gemm[k].params = kp;
+                }
         }
         e = hipGraphInstantiate(&sg.exec, graph, nullptr, nullptr, 0);
         if (e != hipSuccess) {
@@ -515,6 +558,7 @@ tina_status run_batch(tina_pfb_batch_s* b, tina_pfb_work* w, int32_t n, hipStrea
         int max_m = 1;
         bool all_exact = true, wide = false;
         fill_table(b, w, frames, g, tune, dry, max_m, all_exact, wide);
+        const int stages = table_stages(b->h_table);
         int n_fft = 0;
         for (const tina_pfb_batch_s::FftGroup& fg : b->fft_groups) n_fft += fg.count;
         HIP_TRY(hipMemcpyAsync(b->d_table, b->h_table, upload_size(g.count, n_fft), hipMemcpyHostToDevice, s));
@@ -523,21 +567,24 @@ tina_status run_batch(tina_pfb_batch_s* b, tina_pfb_work* w, int32_t n, hipStrea
             b->table_pending[k] = true;
         }
         tina_pfb_batch_s::StepGraph* sg = nullptr;
-        if (use_graph && b->graph_gemm_grid > 0 && gemm_grid(b->h_table) <= b->graph_gemm_grid && b->fft_groups.empty()) {
-            tina_status st = step_graph(b, s, tune, max_m, all_exact, wide, sg);
+        if (use_graph && b->graph_gemm_grid > 0 && gemm_grid(b->h_table) <= b->graph_gemm_grid &&
+            fold_grid(b->h_table) <= b->graph_fold_grid && b->fft_groups.empty()) {
+            tina_status st = step_graph(b, s, tune, max_m, all_exact, wide, stages, sg);
             if (st != TINA_OK) return st;
-            if (sg->gemm_node) {  // this step's GEMM grid: blocks past the tiles' ranges would only return
-                hipKernelNodeParams kp = sg->gemm_params;
-                kp.gridDim.x = (unsigned)gemm_grid(b->h_table);
-                if (hipGraphExecKernelNodeSetParams(sg->exec, sg->gemm_node, &kp) != hipSuccess) {
+            for (int m = 0; m < 2; ++m) {  // this step's GEMM grids: blocks past the tiles' ranges would only return
+                tina_pfb_batch_s::StepGraph::Gemm& gm = sg->gemm[m];
+                if (!gm.node) continue;
+                hipKernelNodeParams kp = gm.params;
+                kp.gridDim.x = (unsigned)(m ? fold_grid(b->h_table) : gemm_grid(b->h_table));
+                if (hipGraphExecKernelNodeSetParams(sg->exec, gm.node, &kp) != hipSuccess) {
                     // Replays keep the captured (largest) grid from now on; the
                     // failed call's error is cleared so later launches do not
                     // report it.
                     (void)hipGetLastError();
-                    sg->gemm_params.gridDim.x = (unsigned)b->graph_gemm_grid;
-                    (void)hipGraphExecKernelNodeSetParams(sg->exec, sg->gemm_node, &sg->gemm_params);
+                    gm.params.gridDim.x = (unsigned)(m ? b->graph_fold_grid : b->graph_gemm_grid);
+                    (void)hipGraphExecKernelNodeSetParams(sg->exec, gm.node, &gm.params);
                     (void)hipGetLastError();
-                    sg->gemm_node = nullptr;
+                    gm.node = nullptr;
                 }
             }
         }
@@ -546,7 +593,7 @@ tina_status run_batch(tina_pfb_batch_s* b, tina_pfb_work* w, int32_t n, hipStrea
             // at once), so one graph per kernel variant serves every step.
             HIP_TRY(hipGraphLaunch(sg->exec, s));
         } else {
-            tina_status st = launch_stages(b, s, tune, max_m, all_exact, wide, false);
+            tina_status st = launch_stages(b, s, tune, max_m, all_exact, wide, stages, false);
             if (st != TINA_OK) return st;
         }
         if (!dry) {
@@ -587,10 +634,15 @@ std::string signature(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<i
 // Used by the server: the largest GEMM tile count of one of its steps, which
 // fixes the grid of the captured step graphs (the cost-balanced split may give
 // one XCD up to all of them).
-void batch_set_graph_bound(tina_pfb_batch_s* b, int64_t max_gemm_tiles) {
+// max_fold_tiles: the same for its folded products.
+void batch_set_graph_bound(tina_pfb_batch_s* b, int64_t max_gemm_tiles, int64_t max_fold_tiles) {
+    auto other = [&](int64_t g) { return g == (int64_t)b->cus * 4 || g == (int64_t)b->cus * 2; };
     int64_t g = 8 * std::max<int64_t>(max_gemm_tiles, 1);
-    while (g == (int64_t)b->cus * 4 || g == (int64_t)b->cus * 2) g += 8;  // unlike every other stage's grid
+    while (other(g)) g += 8;  // unlike every other stage's grid
     b->graph_gemm_grid = g;
+    int64_t f = 8 * std::max<int64_t>(max_fold_tiles, 1);
+    while (other(f) || f == g) f += 8;
+    b->graph_fold_grid = f;
 }
 
 // Used by the server, which owns the batch and runs every step on its one
@@ -632,11 +684,12 @@ tina_status batch_prepare_graphs(tina_pfb_batch_s* b, hipStream_t s) {
     const int n_wide = form_fir_qmode(b->form) != 0 ? 2 : 1;  // reduced forms: wide and 128 x 128 GEMM tiles
     for (int mt = 1; mt <= 64; mt *= 2)
         for (int exact = 1; exact >= (mt == 1 ? 1 : 0); --exact)
-            for (int wide = 0; wide < n_wide; ++wide) {
-                tina_pfb_batch_s::StepGraph* sg = nullptr;
-                tina_status st = step_graph(b, s, tune, mt, exact != 0, wide != 0, sg);
-                if (st != TINA_OK) return st;
-            }
+            for (int wide = 0; wide < n_wide; ++wide)
+                for (int stages = 1; stages <= (fold_form(b->form) ? 3 : 1); ++stages) {
+                    tina_pfb_batch_s::StepGraph* sg = nullptr;
+                    tina_status st = step_graph(b, s, tune, mt, exact != 0, wide != 0, stages, sg);
+                    if (st != TINA_OK) return st;
+                }
     return TINA_OK;
 }
 
@@ -652,7 +705,8 @@ tina_status batch_warm_kernels(tina_pfb_batch_s* b, hipStream_t s) {
     for (int mt = 1; mt <= 64; mt *= 2)
         for (int exact = 1; exact >= (mt == 1 ? 1 : 0); --exact)
             for (int wide = 0; wide < n_wide; ++wide) {
-                tina_status st = launch_stages(b, s, tune, mt, exact != 0, wide != 0, true, 8);
+                const int stages = STAGE_DENSE | STAGE_STATE | (fold_form(b->form) ? STAGE_FOLD : 0);
+                tina_status st = launch_stages(b, s, tune, mt, exact != 0, wide != 0, stages, true, 8, 8);
                 if (st != TINA_OK) return st;
             }
     return TINA_OK;

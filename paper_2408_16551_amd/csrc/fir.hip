@@ -13,7 +13,7 @@
 // This file: host-side launch choices and the state-gather kernels; the FIR
 // kernels themselves are in fir_kernels.h, instantiated per output mode in
 // fir_out_*.hip.
-#include "fir_kernels.h"
+#include "fir_fold.h"
 
 namespace tina {
 
@@ -201,6 +201,25 @@ hipError_t launch_fir_batch(const BatchTable* t, int max_m, bool all_exact, int 
     if (qmode == QM_BF16) return launch_fir_batch_mode_bf16(t, max_m, all_exact, grid, s);
     if (qmode == QM_BF16X2) return launch_fir_batch_mode_bf16x2(t, max_m, all_exact, grid, s);
     return launch_fir_batch_mode_f32(t, max_m, all_exact, grid, s);
+}
+
+hipError_t launch_fir_fold(const FirArgs& a, hipStream_t s) {
+    if (a.F <= 0) return hipSuccess;
+    switch (a.qmode) {
+        case QM_NONE: return launch_fold_f32(a, s);
+        case QM_BF16: return launch_fold_bf16(a, s);
+        case QM_BF16X2: return launch_fold_bf16x2(a, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_fir_fold_batch(const BatchTable* t, int max_m, int qmode, int grid, hipStream_t s) {
+    switch (qmode) {
+        case QM_NONE: return launch_fold_batch_f32(t, max_m, grid, s);
+        case QM_BF16: return launch_fold_batch_bf16(t, max_m, grid, s);
+        case QM_BF16X2: return launch_fold_batch_bf16x2(t, max_m, grid, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_gather_ext(const float* prefix, int64_t plen, const float* chunk, int64_t nchunk,

@@ -155,6 +155,40 @@ __global__ void mx_operand_kernel(uint8_t* codes, uint8_t* scales, int P, int cp
     scales[t] = (uint8_t)(e + 127);
 }
 
+// Folded operand (gemm_fold.hip): entry (column j, part s, sample p), Q = P/4,
+// of [Q][4][Q]: cos (parts 0, 2) or sin (1, 3) of pi k (2p + 1) / P with k = 2j
+// (parts 0, 1; part 1, j = 0: P/2) or 2j + 1 (2, 3).  A sine is taken as the
+// cosine P/2 steps of pi / P earlier, so that every entry is one of the 2P
+// values cos(pi r / P).
+template <int FORM>
+__global__ void fold_operand_kernel(void* piece0, void* piece1, int P) {
+    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int Q = P / 4;
+    if (idx >= (int64_t)Q * P) return;
+    const int j = (int)(idx / P), s = (int)(idx % P) / Q, p = (int)(idx % Q);
+    const int64_t k = s == 1 && j == 0 ? P / 2 : 2 * j + (s >> 1);
+    const int64_t r = (k * (2 * p + 1) + ((s & 1) ? 3 * (P / 2) : 0)) & (2 * P - 1);
+    const double v = cospi((double)r / (double)P);
+    if constexpr (FORM == FORM_FP32) {
+        ((float*)piece0)[idx] = __double2float_rn(v);
+    } else {
+        const double hi = round_sig(v, 8, -126);
+        ((uint16_t*)piece0)[idx] = bf16_bits_exact(hi);
+        if constexpr (FORM == FORM_BF16X3) ((uint16_t*)piece1)[idx] = bf16_bits_exact(round_sig(v - hi, 8, -126));
+    }
+}
+
+__global__ void fold_tables_kernel(float* tw, float* ct, int P) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < P / 2) {
+        double s, c;
+        sincospi((double)i / (double)P, &s, &c);
+        tw[2 * i] = __double2float_rn(c);
+        tw[2 * i + 1] = __double2float_rn(s);
+    }
+    if (ct && i < 2 * P) ct[i] = __double2float_rn(cospi((double)i / (double)P));
+}
+
 // Block-reversed FP32 taps of the synthesis FIR: g'[(M-1-m) P + p] = h[m P + p].
 __global__ void synthesis_taps_kernel(const double* h64, float* g32, int P, int M) {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -180,6 +214,22 @@ hipError_t launch_taps_to_f32(const double* h64, float* h32, int64_t L, hipStrea
 hipError_t launch_synthesis_taps(const double* h64, float* g32, int P, int M, hipStream_t s) {
     const int64_t L = (int64_t)P * M;
     hipLaunchKernelGGL(synthesis_taps_kernel, dim3((unsigned)((L + 255) / 256)), dim3(256), 0, s, h64, g32, P, M);
+    return hipGetLastError();
+}
+
+hipError_t launch_fold_operand(void* piece0, void* piece1, int P, int form, hipStream_t s) {
+    const dim3 grid((unsigned)(((int64_t)P * P / 4 + 255) / 256)), block(256);
+    switch (form) {
+        case FORM_FP32: hipLaunchKernelGGL(fold_operand_kernel<FORM_FP32>, grid, block, 0, s, piece0, piece1, P); break;
+        case FORM_BF16: hipLaunchKernelGGL(fold_operand_kernel<FORM_BF16>, grid, block, 0, s, piece0, piece1, P); break;
+        case FORM_BF16X3: hipLaunchKernelGGL(fold_operand_kernel<FORM_BF16X3>, grid, block, 0, s, piece0, piece1, P); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_fold_tables(float* tw, float* ct, int P, hipStream_t s) {
+    hipLaunchKernelGGL(fold_tables_kernel, dim3((2 * P + 255) / 256), dim3(256), 0, s, tw, ct, P);
     return hipGetLastError();
 }
 

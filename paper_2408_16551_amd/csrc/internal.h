@@ -105,14 +105,30 @@ struct GemmArgs {
     const int32_t* fexp;   // per-frame scaled forms with A in operand form: A row f carries 2^-fexp[f]
     int32_t compensated;   // FP32 only: compensated K accumulation (TwoSum per K tile)
     const float* tw;       // FP32 only, non-null: Bt assembled from this P x (cos, sin) twiddle table (B0 unused)
+                           // (folded product: cos, sin of pi k / P, k < P/2, for every form)
+    const float* ct;       // folded product, FP32 only, non-null: operand assembled from cos(pi r / P), r < 2P
 };
 hipError_t launch_dft_gemm(const GemmArgs& a, hipStream_t s);
-// The FIR fused into the FP32 GEMM (g.A unused; x describes the input stream
-// and taps as for launch_fir, x.y unused).  fused_supported: FP32, M <= 16,
-// W a multiple of 32, 16-byte aligned input with the prefix a whole number of
-// float4s.
-bool fused_supported(const FirArgs& x, int form);
-hipError_t launch_dft_fused(const GemmArgs& g, const FirArgs& x, hipStream_t s);
+
+// ------------------------------------------------------------ folded product
+// The dense DFT by its symmetry: four Q x Q products, Q = P / 4 (gemm_fold.hip)
+// over operand rows the FIR writes folded (fir_fold.h): frames x cf rows of P
+// elements.  GemmArgs: A / Aq, Aq1 those rows, B0, B1 the folded operand
+// (launch_fold_operand), K = P, N = Q, real_pack, tw (and ct); lda unused.
+//
+// From 256 channels, in the forms whose operand element needs no frame or
+// block scale.  Fewer channels: the column groups are narrower than a wave,
+// and the dense product is no longer what bounds a call.
+inline bool fold_form(int form) { return form == FORM_FP32 || form == FORM_BF16 || form == FORM_BF16X3; }
+inline bool fold_supported(int P, int form) { return P >= 256 && fold_form(form); }
+// The FIR with folded output (a.y, or a.q / a.q1 with a.qmode; ldy, ldq unused).
+hipError_t launch_fir_fold(const FirArgs& a, hipStream_t s);
+hipError_t launch_dft_fold(const GemmArgs& a, hipStream_t s);
+// Folded operand [Q][4 parts][Q] in the pieces of `form`, in FP64 rounded once.
+hipError_t launch_fold_operand(void* piece0, void* piece1, int P, int form, hipStream_t s);
+// tw: (cos, sin)(pi k / P), k < P/2; ct (optional): cos(pi r / P), r < 2P.
+hipError_t launch_fold_tables(float* tw, float* ct, int P, hipStream_t s);
+constexpr int kFoldBM = 128, kFoldBJ = 64;  // tile rows and columns of the batched folded product
 // Forms whose A the FIR can write in operand form.
 bool gemm_raw_form(int form);
 
@@ -157,6 +173,7 @@ struct BatchItem {
     int64_t gemm_unit0;     // first GEMM tile of this item
     int64_t st_unit0;       // first state-update unit
     int32_t fir_tf;         // frames per FIR thread (fir_single: frames per frame-stage unit)
+    int64_t ffold_unit0, gfold_unit0;  // first unit / tile of the folded FIR / product
     int32_t fir_single;     // per-frame scaled form: one pass, whole frame rows per unit (frame stage)
     int64_t frame_unit0;    // first unit of the frame stage
     float* st_dst;          // state buffer to fill (nullptr: no state)
@@ -168,15 +185,15 @@ struct BatchItem {
 struct BatchTable {
     int32_t n_items;
     int32_t pad_;
-    int64_t fir_units, gemm_units, st_units, frame_units;
-    int64_t fir_bounds[9], gemm_bounds[9], st_bounds[9], frame_bounds[9];
+    int64_t fir_units, gemm_units, st_units, frame_units, ffold_units, gfold_units;
+    int64_t fir_bounds[9], gemm_bounds[9], st_bounds[9], frame_bounds[9], ffold_bounds[9], gfold_bounds[9];
     int32_t gemm_bn;        // GEMM tile columns of this launch (kGemmBN or 2 * kGemmBN, or the wide tile's)
     int32_t gemm_wide;      // the launch uses the wide raw-operand tiles
     BatchItem items[1];     // n_items entries follow
 };
 
 // Index of the item that owns unit u of a stage (0 FIR, 1 GEMM, 2 state,
-// 3 single-pass per-frame FIR):
+// 3 single-pass per-frame FIR, 4 folded FIR, 5 folded product):
 // the last item whose first unit is <= u.
 __device__ inline int batch_find(const BatchItem* items, int n, int64_t u, int stage) {
     int lo = 0, hi = n - 1;
@@ -185,7 +202,9 @@ __device__ inline int batch_find(const BatchItem* items, int n, int64_t u, int s
         const int64_t s = stage == 0 ? items[mid].fir_unit0
                           : stage == 1 ? items[mid].gemm_unit0
                           : stage == 2 ? items[mid].st_unit0
-                                       : items[mid].frame_unit0;
+                          : stage == 3 ? items[mid].frame_unit0
+                          : stage == 4 ? items[mid].ffold_unit0
+                                       : items[mid].gfold_unit0;
         if (s <= u) lo = mid;
         else hi = mid - 1;
     }
@@ -241,5 +260,9 @@ hipError_t launch_gemm_batch(const BatchTable* t, int form, bool raw, int tile_n
 // columns (K a whole number of its K tiles); false for FP32 and other K.
 bool gemm_batch_wide_tile(int form, int K, int& bm, int& bn);
 hipError_t launch_gather_batch(const BatchTable* t, int grid, hipStream_t s);
+// Items with the folded product: their FIR (max_m: largest tap count among
+// them, qmode as launch_fir_batch) and their tiles (one block each).
+hipError_t launch_fir_fold_batch(const BatchTable* t, int max_m, int qmode, int grid, hipStream_t s);
+hipError_t launch_fold_gemm_batch(const BatchTable* t, int form, int grid, hipStream_t s);
 
 }  // namespace tina

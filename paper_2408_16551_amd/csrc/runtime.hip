@@ -104,6 +104,8 @@ tina_status tina_pfb_plan(const tina_pfb_desc* d, tina_pfb_plan_t* out) {
     }
     p->K = p->W;
     p->N = p->W;
+    p->fold = d->output == TINA_OUT_PFB && fold_supported(p->P, p->precision) &&
+              (dft_alg == TINA_DFT_DENSE || dft_alg == TINA_DFT_FUSED || dft_alg == TINA_DFT_TABLE);
     p->kout = d->output != TINA_OUT_PFB ? p->P : (p->cf == 2 ? p->P : p->P / 2 + 1);
 
     auto bail = [&](tina_status st, const std::string& m) {
@@ -135,6 +137,18 @@ tina_status tina_pfb_plan(const tina_pfb_desc* d, tina_pfb_plan_t* out) {
                     return bail(TINA_ERR_OUT_OF_MEMORY, "plan: synthesis history");
             e = launch_dft_operand(p->B[0], p->B[1], p->P, 1, form, nullptr, /*inverse=*/1);
             if (e == hipSuccess) e = launch_synthesis_taps(p->h64, p->g32, p->P, p->M, nullptr);
+        } else if (p->fold) {
+            p->K = p->P;
+            p->N = p->P / 4;
+            const bool table = p->dft_algorithm == TINA_DFT_TABLE;
+            const int64_t nbytes = (int64_t)p->N * p->K * form_elem_bytes(form);
+            for (int i = 0; i < form_pieces(form) && !table; ++i)
+                if (hipMalloc(&p->B[i], nbytes) != hipSuccess) return bail(TINA_ERR_OUT_OF_MEMORY, "plan: DFT operand allocation");
+            if (hipMalloc(&p->fold_tw, sizeof(float) * p->P) != hipSuccess ||
+                (table && hipMalloc(&p->fold_ct, sizeof(float) * 2 * p->P) != hipSuccess))
+                return bail(TINA_ERR_OUT_OF_MEMORY, "plan: twiddle table");
+            e = launch_fold_tables(p->fold_tw, p->fold_ct, p->P, nullptr);
+            if (e == hipSuccess && !table) e = launch_fold_operand(p->B[0], p->B[1], p->P, form, nullptr);
         } else if (p->dft_algorithm == TINA_DFT_FACTORED) {
             int P1, P2;
             fft_factors(p->P, P1, P2);
@@ -317,20 +331,7 @@ tina_status execute_with(tina_pfb_plan_s* p, const void* d_in, int64_t n, void* 
                     fa.q1 = (uint8_t*)w.ws + (int64_t)w.ch_frames * p->W * 2;
                 if (form_scaled(form)) fa.fexp = w.fexp;
             }
-            if (p->dft_algorithm == TINA_DFT_FUSED && fused_supported(fa, form)) {
-                GemmArgs ga{};
-                ga.B0 = p->B[0];
-                ga.out = (float*)d_out + c0 * ldo;
-                ga.ldo = ldo;
-                ga.F = Fc;
-                ga.K = p->K;
-                ga.N = p->N;
-                ga.real_pack = p->cf == 1;
-                ga.form = form;
-                HIP_TRY(timed(p->ev_dft, [&] { return launch_dft_fused(ga, fa, s); }));
-                continue;
-            }
-            HIP_TRY(timed(p->ev_fir, [&] { return launch_fir(fa, s); }));
+            HIP_TRY(timed(p->ev_fir, [&] { return p->fold ? launch_fir_fold(fa, s) : launch_fir(fa, s); }));
             if (p->dft_algorithm == TINA_DFT_FACTORED) {
                 FftArgs xa{};
                 xa.y = w.ws;
@@ -364,8 +365,9 @@ tina_status execute_with(tina_pfb_plan_s* p, const void* d_in, int64_t n, void* 
             ga.Aqs = fa.qs;
             ga.fexp = fa.fexp;
             ga.compensated = p->dft_algorithm == TINA_DFT_COMPENSATED;
-            ga.tw = p->dft_algorithm == TINA_DFT_TABLE ? p->fft_tw : nullptr;
-            HIP_TRY(timed(p->ev_dft, [&] { return launch_dft_gemm(ga, s); }));
+            ga.tw = p->fold ? p->fold_tw : p->dft_algorithm == TINA_DFT_TABLE ? p->fft_tw : nullptr;
+            ga.ct = p->fold_ct;
+            HIP_TRY(timed(p->ev_dft, [&] { return p->fold ? launch_dft_fold(ga, s) : launch_dft_gemm(ga, s); }));
         }
     }
     if (st) {

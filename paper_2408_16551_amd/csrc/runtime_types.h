@@ -91,6 +91,9 @@ struct tina_pfb_plan_s {
     float* fft_mat1 = nullptr;  // factored DFT tables
     float* fft_mat3 = nullptr;
     float* fft_tw = nullptr;
+    bool fold = false;          // dense DFT by the folded product (B: its operand, K = P, N = P/4)
+    float* fold_tw = nullptr;   // folded product: channel rotations
+    float* fold_ct = nullptr;   // folded product with the table operand: cos(pi r / P)
     float* g32 = nullptr;       // synthesis FIR taps (inverse plans)
     float* hist[2] = {nullptr, nullptr};  // history scratch between workspace pieces (inverse plans)
     int cus = 256;
@@ -126,11 +129,11 @@ struct tina_pfb_plan_s {
         ev_pool.clear();
         clear_events();
         for (void* p : {(void*)h64, (void*)h32, B[0], B[1], (void*)ws, (void*)amax, (void*)fexp, (void*)fft_mat1,
-                        (void*)fft_mat3, (void*)fft_tw, (void*)g32, (void*)hist[0], (void*)hist[1]})
+                        (void*)fft_mat3, (void*)fft_tw, (void*)fold_tw, (void*)fold_ct, (void*)g32, (void*)hist[0], (void*)hist[1]})
             if (p) (void)hipFree(p);
         g32 = hist[0] = hist[1] = nullptr;
         h64 = nullptr; h32 = nullptr; B[0] = B[1] = nullptr; ws = nullptr; amax = nullptr; fexp = nullptr;
-        fft_mat1 = fft_mat3 = fft_tw = nullptr;
+        fft_mat1 = fft_mat3 = fft_tw = fold_tw = fold_ct = nullptr;
     }
 };
 
@@ -152,8 +155,8 @@ struct tina_pfb_state_s {
 struct tina_pfb_batch_s;
 struct tina_pfb_work;
 tina_status batch_run_items(tina_pfb_batch_s* b, tina_pfb_work* w, int32_t n, hipStream_t s, bool use_graph);
-// Bound on the GEMM tiles of one step (fixes the grid of captured steps).
-void batch_set_graph_bound(tina_pfb_batch_s* b, int64_t max_gemm_tiles);
+// Bounds on the GEMM tiles, dense and folded, of one step (they fix the grids of captured steps).
+void batch_set_graph_bound(tina_pfb_batch_s* b, int64_t max_gemm_tiles, int64_t max_fold_tiles);
 // Launches every step kernel variant once on an empty table (no graphs).
 tina_status batch_warm_kernels(tina_pfb_batch_s* b, hipStream_t s);
 // A batch owned by a server: one stream, short frame-stage units.

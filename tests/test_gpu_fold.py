@@ -1,0 +1,91 @@
+"""GPU: the folded dense product (256 channels and more; FP32, BF16, BF16x3)
+against the FP64 oracle at the edges of its tiles (64 and 128 rows, a row being
+a real frame or half a complex one), of the tap rings and of the channel range,
+and its kernels against each other bit for bit.
+
+Bounds: those of the forms at every size (unit roundoff times the operand and
+product roundings; FP32 1e-5 as required)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+BOUND = {"fp32": 1e-5, "bf16": 8e-3, "bf16x3": 1e-5}
+
+
+def rel_l2(got, ref):
+    return float(np.linalg.norm(got.astype(np.complex128) - ref) / np.linalg.norm(ref))
+
+
+def _x(P, F, cplx, seed):
+    g = np.random.Generator(np.random.PCG64(seed))
+    n = P * F + P // 3
+    x = g.standard_normal(n)
+    if cplx:
+        return (x + 1j * g.standard_normal(n)).astype(np.complex64)
+    return x.astype(np.float32)
+
+
+def _plan(P, M, cplx, prec, dft="dense"):
+    from paper_2408_16551_amd.pfb import Plan
+    return Plan(P, M, "c64" if cplx else "r32", "hann", prec, dft=dft)
+
+
+def _run(plan, x, state=None):
+    return plan(torch.from_numpy(x).cuda(), state=state).cpu().numpy()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec", ["fp32", "bf16", "bf16x3"])
+@pytest.mark.parametrize("P,M,cplx,F", [
+    (256, 1, False, 1), (256, 5, True, 33), (256, 16, False, 129), (512, 9, True, 65), (512, 17, False, 64),
+    (1024, 8, True, 31), (1024, 12, False, 200), (2048, 33, True, 18), (4096, 8, False, 70), (8192, 3, True, 9),
+])
+def test_folded_product_matches_oracle(oracle, P, M, cplx, F, prec):
+    x = _x(P, F, cplx, P + 10 * M + F)
+    X = _run(_plan(P, M, cplx, prec), x)
+    ref = oracle.pfb(x, P, M, oracle.window(P, M, "hann"))
+    assert X.shape == ref.shape
+    assert rel_l2(X, ref) < BOUND[prec]
+    if not cplx:
+        assert np.all(X[:, [0, P // 2]].imag == 0.0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec", ["fp32", "bf16", "bf16x3"])
+@pytest.mark.parametrize("P,M,cplx,F", [(256, 4, True, 9000), (1024, 16, False, 9001), (4096, 8, True, 1030)])
+def test_short_and_long_calls_agree_bitwise(P, M, cplx, F, prec):
+    """A long call (128-row tiles), a short one (64-row tiles, a wave a part),
+    uneven chunks through a state, an input off 16-byte alignment and a batch."""
+    from paper_2408_16551_amd.pfb import Batch, State
+    x = _x(P, F, cplx, 7)
+    plan = _plan(P, M, cplx, prec)
+    want = _run(plan, x)
+    assert np.array_equal(_run(plan, x[: 37 * P + 5]), want[:37])
+    st = State(plan)
+    cut = [0, 3 * P + 1, 11 * P + 1, 11 * P + 7, 60 * P, 60 * P + 2, x.size]
+    parts = [_run(plan, x[a:b], st) for a, b in zip(cut[:-1], cut[1:])]
+    assert np.array_equal(np.concatenate(parts), want)
+    off = torch.empty(x.size + 1, dtype=torch.from_numpy(x[:1]).dtype, device="cuda")
+    off[1:] = torch.from_numpy(x).cuda()
+    assert np.array_equal(plan(off[1:]).cpu().numpy(), want)
+    b = Batch(prec, max_items=2, workspace_bytes=1 << 30)
+    xs = [torch.from_numpy(x).cuda(), torch.from_numpy(x[: 41 * P]).cuda()]
+    outs = [plan.alloc_out(t.numel() // P) for t in xs]
+    b.execute([(plan, t, o) for t, o in zip(xs, outs)])
+    assert np.array_equal(outs[0].cpu().numpy(), want) and np.array_equal(outs[1].cpu().numpy(), want[:41])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec", ["fp32", "bf16x3"])
+def test_batch_mixes_folded_and_unfolded_items_bitwise(prec):
+    from paper_2408_16551_amd.pfb import Batch
+    items, want = [], []
+    for i, (P, M, cplx, F) in enumerate([(64, 5, True, 300), (256, 9, False, 131), (128, 16, False, 77),
+                                         (2048, 20, True, 40), (512, 3, True, 0), (1024, 40, False, 65)]):
+        x = torch.from_numpy(_x(P, F, cplx, 50 + i)[: P * F]).cuda()
+        plan = _plan(P, M, cplx, prec)
+        want.append(plan(x).cpu().numpy())
+        items.append((plan, x, plan.alloc_out(F)))
+    Batch(prec, max_items=len(items), workspace_bytes=1 << 28).execute(items)
+    for (_, _, out), w in zip(items, want):
+        assert np.array_equal(out.cpu().numpy(), w)
