@@ -146,10 +146,9 @@ typedef struct tina_pfb_desc {
  *                      with a rotation of each channel at the end.  A frame with an
  *                      infinite or NaN sample gives non-finite channels either way;
  *                      which of them are infinite and which NaN is not specified;
- *   TINA_DFT_FACTORED  a factored (four-step) DFT, P = P1 * P2: P2 DFTs of size
- *                      P1, twiddles, P1 DFTs of size P2, each size-P1/P2 DFT a
- *                      small matrix product on the MFMA units in FP32 -- 8 P (P1 + P2)
- *                      flops per frame instead of 8 P^2.  FP32 only; 256 <= P <= 4096.
+ *   TINA_DFT_FACTORED  a factored DFT (mixed-radix FFT, passes of radix 2 to 16
+ *                      in FP32): about 5 P log2 P flops per frame instead of
+ *                      8 P^2.  FP32 only; 256 <= P <= 4096.
  *                      Also in FP32 batches (one launch per channel count and
  *                      input type over those items' frames) and in an FP32
  *                      server created with this algorithm.

@@ -119,10 +119,10 @@ struct tina_pfb_batch_s {
     // the table buffer after the items (fft_offset).
     struct FftGroup {
         int P;
-        bool cplx, q64_ok;
+        bool cplx;
         int first, count;  // rows [first, first + count) of the table's FftItem array
         int64_t F;         // frames of the group's items
-        const float *mat1, *mat3, *tw;
+        const float* tw;
     };
     std::vector<FftGroup> fft_groups;
     bool one_stream = false;      // every call comes on one stream: no order event is recorded
@@ -387,12 +387,9 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
             tina_pfb_batch_s::FftGroup fg;
             fg.P = p->P;
             fg.cplx = p->cf == 2;
-            fg.q64_ok = true;
             fg.first = (int)k;
             fg.count = 0;
             fg.F = 0;
-            fg.mat1 = p->fft_mat1;
-            fg.mat3 = p->fft_mat3;
             fg.tw = p->fft_tw;
             b->fft_groups.push_back(fg);
         }
@@ -403,7 +400,6 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
         r.ldy = bi.fir.ldy;
         r.ldo = bi.gemm.ldo;
         r.f0 = fg.F;
-        fg.q64_ok = fg.q64_ok && r.ldy % 4 == 0 && ((uintptr_t)r.y & 15) == 0;
         fg.F += bi.gemm.F;
         fg.count += 1;
     }
@@ -480,7 +476,7 @@ tina_status launch_stages(tina_pfb_batch_s* b, hipStream_t s, const Tune& tune, 
     if (!always)  // factored-DFT items: never in a captured step (the groups change from call to call)
         for (const tina_pfb_batch_s::FftGroup& fg : b->fft_groups)
             HIP_TRY(launch_fft_batch(fft_rows(b->d_table, b->h_table->n_items) + fg.first, fg.count, fg.F, fg.P,
-                                     fg.cplx, fg.q64_ok, fg.mat1, fg.mat3, fg.tw, b->cus, s));
+                                     fg.cplx, fg.tw, b->cus, s));
     if (stages & STAGE_STATE) HIP_TRY(launch_gather_batch(b->d_table, b->cus * 2, s));
     return TINA_OK;
 }

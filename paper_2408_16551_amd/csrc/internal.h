@@ -137,16 +137,12 @@ struct FftArgs {
     const float* y;        // FIR output [F][ldy] (P real or P complex values per frame)
     int64_t ldy;
     int64_t F;
-    const float* mat1;     // realified DFT_{P1} (2 P1 x 2 P1)
-    const float* mat3;     // realified DFT_{P2} (2 P2 x 2 P2); unused when P1 == P2
     const float* tw;       // cos, sin of 2 pi r / P
     float* out;            // output rows (complex64), row stride ldo floats
     int64_t ldo;
     int32_t P, cplx, cus;
 };
 bool fft_supported(int P);
-void fft_factors(int P, int& P1, int& P2);
-hipError_t launch_fft_tables(float* mat1, float* mat3, float* tw, int P, hipStream_t s);
 // tw (P x 2): cos, sin of 2 pi r / P in FP64, rounded to FP32.
 hipError_t launch_twiddle_table(float* tw, int P, hipStream_t s);
 hipError_t launch_fft_dft(const FftArgs& a, hipStream_t s);
@@ -158,10 +154,9 @@ struct FftItem {
     float* out;
     int64_t ldy, ldo, f0;
 };
-// Every frame of n items with the same P and input type (F frames in all);
-// q64_ok: every y row is 16-byte aligned with ldy a multiple of 4 floats.
-hipError_t launch_fft_batch(const FftItem* items, int n, int64_t F, int P, bool cplx, bool q64_ok, const float* mat1,
-                            const float* mat3, const float* tw, int cus, hipStream_t s);
+// Every frame of n items with the same P and input type (F frames in all).
+hipError_t launch_fft_batch(const FftItem* items, int n, int64_t F, int P, bool cplx, const float* tw, int cus,
+                            hipStream_t s);
 
 // --------------------------------------------------------------- batched path
 // One item of a batched launch: the FIR and GEMM arguments of one stream

@@ -149,15 +149,7 @@ tina_status tina_pfb_plan(const tina_pfb_desc* d, tina_pfb_plan_t* out) {
                 return bail(TINA_ERR_OUT_OF_MEMORY, "plan: twiddle table");
             e = launch_fold_tables(p->fold_tw, p->fold_ct, p->P, nullptr);
             if (e == hipSuccess && !table) e = launch_fold_operand(p->B[0], p->B[1], p->P, form, nullptr);
-        } else if (p->dft_algorithm == TINA_DFT_FACTORED) {
-            int P1, P2;
-            fft_factors(p->P, P1, P2);
-            if (hipMalloc(&p->fft_mat1, sizeof(float) * 4 * P1 * P1) != hipSuccess ||
-                (P1 != P2 && hipMalloc(&p->fft_mat3, sizeof(float) * 4 * P2 * P2) != hipSuccess) ||
-                hipMalloc(&p->fft_tw, sizeof(float) * 2 * p->P) != hipSuccess)
-                return bail(TINA_ERR_OUT_OF_MEMORY, "plan: factored DFT tables");
-            e = launch_fft_tables(p->fft_mat1, p->fft_mat3, p->fft_tw, p->P, nullptr);
-        } else if (p->dft_algorithm == TINA_DFT_TABLE) {  // no N x K operand: P twiddles
+        } else if (p->dft_algorithm == TINA_DFT_FACTORED || p->dft_algorithm == TINA_DFT_TABLE) {  // P twiddles alone
             if (hipMalloc(&p->fft_tw, sizeof(float) * 2 * p->P) != hipSuccess)
                 return bail(TINA_ERR_OUT_OF_MEMORY, "plan: twiddle table");
             e = launch_twiddle_table(p->fft_tw, p->P, nullptr);
@@ -337,8 +329,6 @@ tina_status execute_with(tina_pfb_plan_s* p, const void* d_in, int64_t n, void* 
                 xa.y = w.ws;
                 xa.ldy = p->W;
                 xa.F = Fc;
-                xa.mat1 = p->fft_mat1;
-                xa.mat3 = p->fft_mat3;
                 xa.tw = p->fft_tw;
                 xa.out = (float*)d_out + c0 * ldo;
                 xa.ldo = ldo;

@@ -88,9 +88,7 @@ struct tina_pfb_plan_s {
     float* h32 = nullptr;
     void* B[2] = {nullptr, nullptr};
     int dft_algorithm = 0;
-    float* fft_mat1 = nullptr;  // factored DFT tables
-    float* fft_mat3 = nullptr;
-    float* fft_tw = nullptr;
+    float* fft_tw = nullptr;    // cos, sin of 2 pi r / P (factored DFT, table operand below 256 channels)
     bool fold = false;          // dense DFT by the folded product (B: its operand, K = P, N = P/4)
     float* fold_tw = nullptr;   // folded product: channel rotations
     float* fold_ct = nullptr;   // folded product with the table operand: cos(pi r / P)
@@ -128,12 +126,12 @@ struct tina_pfb_plan_s {
         for (hipEvent_t e : ev_pool) (void)hipEventDestroy(e);
         ev_pool.clear();
         clear_events();
-        for (void* p : {(void*)h64, (void*)h32, B[0], B[1], (void*)ws, (void*)amax, (void*)fexp, (void*)fft_mat1,
-                        (void*)fft_mat3, (void*)fft_tw, (void*)fold_tw, (void*)fold_ct, (void*)g32, (void*)hist[0], (void*)hist[1]})
+        for (void* p : {(void*)h64, (void*)h32, B[0], B[1], (void*)ws, (void*)amax, (void*)fexp, (void*)fft_tw,
+                         (void*)fold_tw, (void*)fold_ct, (void*)g32, (void*)hist[0], (void*)hist[1]})
             if (p) (void)hipFree(p);
         g32 = hist[0] = hist[1] = nullptr;
         h64 = nullptr; h32 = nullptr; B[0] = B[1] = nullptr; ws = nullptr; amax = nullptr; fexp = nullptr;
-        fft_mat1 = fft_mat3 = fft_tw = fold_tw = fold_ct = nullptr;
+        fft_tw = fold_tw = fold_ct = nullptr;
     }
 };
 
