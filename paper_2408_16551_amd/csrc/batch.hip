@@ -329,7 +329,9 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
             const int TF = frames_per_thread(ring);
             bi.fir_tf = TF;
             ffu[i] = (F + TF - 1) / TF * (p->W / 256);
-            gfu[i] = (F * p->cf + kFoldBM - 1) / kFoldBM * ((p->N + kFoldBJ - 1) / kFoldBJ);
+            int64_t bm, bj;
+            fold_batch_tile(b->form, p->N, bm, bj);
+            gfu[i] = (F * p->cf + bm - 1) / bm * ((p->N + bj - 1) / bj);
             fu[i] = ru[i] = 0;
             fc[i] = (double)TF * ring;
         } else if (bi.fir_single) {

@@ -27,14 +27,14 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float fvec2 __attribute__((ext_vector_type(2)));
 typedef float f32x4_a8 __attribute__((ext_vector_type(4), aligned(8)));  // channel pairs lie on 8 bytes
 
-// EB: bytes per element; NP: pieces; ROWB: bytes of a row per K tile and piece.
+// EB: bytes per element; NP: pieces.
 template <int FORM> struct FF;
-template <> struct FF<FORM_FP32> { static constexpr int EB = 4, NP = 1, ROWB = 128; };
-template <> struct FF<FORM_BF16> { static constexpr int EB = 2, NP = 1, ROWB = 128; };
-template <> struct FF<FORM_BF16X3> { static constexpr int EB = 2, NP = 2, ROWB = 64; };
+template <> struct FF<FORM_FP32> { static constexpr int EB = 4, NP = 1; };
+template <> struct FF<FORM_BF16> { static constexpr int EB = 2, NP = 1; };
+template <> struct FF<FORM_BF16X3> { static constexpr int EB = 2, NP = 2; };
 
 constexpr int SLAB = 32;      // bytes of a row per MFMA step (8 FP32 or 16 bf16 of K)
-constexpr int GROUP_M = 16;   // m-tiles swept per column of j-tiles
+constexpr int GROUP_M = 8;    // m-tiles swept per column of j-tiles (4096 complex, BF16: 439 us; 470, 463, 532 at 4, 16, 32)
 
 // FP32 sums every K tile of 32 products by itself and adds the tile sums: C and
 // S of a strong channel are as large as the channel, and what their running
@@ -124,21 +124,32 @@ __device__ __forceinline__ int fold_index(int k, int p, bool sine, int P) {
     return (k * (2 * p + 1) + (sine ? 3 * (P / 2) : 0)) & (2 * P - 1);
 }
 
-template <int FORM, int WGN>
+// A block of WGM x WGN waves, each 64 rows x 32 columns of all four parts (128
+// accumulators).  FP32: 128 x 64, 256 threads, two blocks a CU (128 x 128 took
+// the same time).  16-bit forms: 128 x 128, one block a CU, or 256 x 64 for the
+// 64 columns of 256 channels.  Their LDS reads are the bound (three 16-byte
+// reads per two products), so long K tiles, few barriers and fewer operand
+// bytes from L2 count: 545 / 1212 us for BF16 / BF16x3 at 4096 complex channels
+// with the FP32 tile, 439 / 895 us with this one; a second K tile of loads in
+// flight made no difference.
+// ROWB: bytes of a row per K tile and piece; 128 where two stages fit the LDS.
+template <int FORM, int WGM, int WGN>
 struct FoldTile {
-    static constexpr int NP = FF<FORM>::NP, EB = FF<FORM>::EB, ROWB = FF<FORM>::ROWB;
-    static constexpr int BMR = 128, BJ = 32 * WGN, NTH = 128 * WGN;   // 2 x WGN waves of 64 rows x 32 j
+    static constexpr int NP = FF<FORM>::NP, EB = FF<FORM>::EB;
+    static constexpr int BMR = 64 * WGM, BJ = 32 * WGN, NTH = 64 * WGM * WGN;
+    static constexpr int ROWB = 2 * NP * (BMR + BJ) * 144 <= 160 * 1024 ? 128 : 64;
+    static_assert(2 * NP * (BMR + BJ) * (ROWB + 16) <= 160 * 1024, "two stages fit the LDS");
     static constexpr int RS = ROWB + 16, CPR = ROWB / 16, NSLAB = ROWB / SLAB;
-    static constexpr int QCH = BMR * CPR / NTH, BCH = BJ * CPR / NTH;  // chunks per thread and piece
+    static constexpr int QCH = BMR * CPR / NTH, BCH = (BJ * CPR + NTH - 1) / NTH;  // chunks per thread and piece
     static constexpr int STAGE = NP * (BMR + BJ) * RS;
-    static_assert(BMR * CPR % NTH == 0 && BJ * CPR % NTH == 0, "whole chunks per thread");
+    static_assert(BMR * CPR % NTH == 0, "whole chunks per thread");
 };
 
 // One tile (rows m0.., columns n0..), called by every thread of the block.
 // lds: two stages of K tiles.  TABLE: the B rows are assembled from ct.
-template <int FORM, bool CPLX, int WGN, bool TABLE>
+template <int FORM, bool CPLX, int WGM, int WGN, bool TABLE>
 __device__ __forceinline__ void fold_tile(const GemmArgs& g, int64_t m0, int64_t n0, uint8_t* lds, const float* ct) {
-    using G = FoldTile<FORM, WGN>;
+    using G = FoldTile<FORM, WGM, WGN>;
     constexpr int NP = G::NP, RS = G::RS, CPR = G::CPR, NTH = G::NTH, BMR = G::BMR, BJ = G::BJ;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WGN, wn = wave % WGN, lr = lane & 31, lh = lane >> 5;
@@ -198,8 +209,9 @@ __device__ __forceinline__ void fold_tile(const GemmArgs& g, int64_t m0, int64_t
             }
 #pragma unroll
             for (int i = 0; i < G::BCH; ++i) {
-                const int c = tid + i * NTH;
-                *reinterpret_cast<uint4*>(Bs + p * BJ * RS + (c / CPR) * RS + (c % CPR) * 16) = r.b[p][i];
+                const int c = tid + i * NTH;  // past the tile's rows: loaded as zeros, not stored
+                if (BJ * CPR % NTH == 0 || c < BJ * CPR)
+                    *reinterpret_cast<uint4*>(Bs + p * BJ * RS + (c / CPR) * RS + (c % CPR) * 16) = r.b[p][i];
             }
         }
     };
@@ -281,19 +293,18 @@ __device__ __forceinline__ void fold_tile(const GemmArgs& g, int64_t m0, int64_t
 }
 
 // Few rows: blocks of 64 rows x 32 columns, one wave per part, so that a short
-// call still spreads over the chip (a 128 x 64 tile does 4 x 2 as much work
-// per wave).  Operand rows go from memory straight to the MFMA registers; the
+// call still spreads over the chip (a wave of the large tile does four times
+// as much).  Operand rows go from memory straight to the MFMA registers; the
 // four parts meet in LDS.  Same K order, same bits as fold_tile.
 template <int FORM, bool CPLX>
 __device__ __forceinline__ void fold_tile_small(const GemmArgs& g, int64_t m0, int64_t n0, float* ex) {
-    using G = FoldTile<FORM, 2>;
-    constexpr int NP = G::NP, U = 4;  // slabs in flight
+    constexpr int NP = FF<FORM>::NP, EB = FF<FORM>::EB, U = 4;  // slabs in flight
     const int lane = threadIdx.x & 63, s = threadIdx.x >> 6, lr = lane & 31, lh = lane >> 5;
     const int P = g.K, Q = g.N;
-    const int64_t R = g.F * (CPLX ? 2 : 1), pitch = (int64_t)P * G::EB;
+    const int64_t R = g.F * (CPLX ? 2 : 1), pitch = (int64_t)P * EB;
     const uint8_t* Ap[2] = {FORM == FORM_FP32 ? (const uint8_t*)g.A : g.Aq, g.Aq1};
     const uint8_t* Bp[2] = {(const uint8_t*)g.B0, (const uint8_t*)g.B1};
-    const int part0 = s * Q * G::EB + lh * 16;
+    const int part0 = s * Q * EB + lh * 16;
     int64_t ao[2];
 #pragma unroll
     for (int bm = 0; bm < 2; ++bm) {
@@ -303,8 +314,8 @@ __device__ __forceinline__ void fold_tile_small(const GemmArgs& g, int64_t m0, i
     const int64_t bo = (n0 + lr) * pitch + part0;  // Q is a multiple of 32
     f32x16 acc[2], ts[2];
     zero(acc);
-    static_assert(!kTileSums<FORM> || U * SLAB == G::ROWB, "one K tile per round");
-    const int ns = Q * G::EB / SLAB;  // a multiple of U
+    static_assert(!kTileSums<FORM> || U * SLAB == 128, "one K tile per round");
+    const int ns = Q * EB / SLAB;  // a multiple of U
     uint4 a[U][2][NP], b[U][NP];
     auto load = [&](int u, int sl) {
 #pragma unroll
@@ -360,15 +371,15 @@ __device__ __forceinline__ void fold_place(int64_t L, int64_t nm, int64_t nn, in
     n0 = (in / gsz) * bj;
 }
 
-template <int FORM, bool CPLX, int WGN>
-__global__ __launch_bounds__((FoldTile<FORM, WGN>::NTH)) __attribute__((amdgpu_waves_per_eu(2)))
+template <int FORM, bool CPLX, int WGM, int WGN>
+__global__ __launch_bounds__((FoldTile<FORM, WGM, WGN>::NTH)) __attribute__((amdgpu_waves_per_eu(2)))
 void fold_gemm_kernel(GemmArgs g) {
-    using G = FoldTile<FORM, WGN>;
+    using G = FoldTile<FORM, WGM, WGN>;
     __shared__ __attribute__((aligned(16))) uint8_t lds[2 * G::STAGE];
     const int64_t nm = (g.F * (CPLX ? 2 : 1) + G::BMR - 1) / G::BMR, nn = (g.N + G::BJ - 1) / G::BJ;
     int64_t m0, n0;
     fold_place(xcd_logical_block(blockIdx.x, gridDim.x), nm, nn, G::BMR, G::BJ, m0, n0);
-    fold_tile<FORM, CPLX, WGN, false>(g, m0, n0, lds, nullptr);
+    fold_tile<FORM, CPLX, WGM, WGN, false>(g, m0, n0, lds, nullptr);
 }
 
 template <int FORM, bool CPLX>
@@ -384,7 +395,7 @@ __global__ __launch_bounds__(256) void fold_gemm_small_kernel(GemmArgs g) {
 // copied to LDS after the K tiles) instead of read: same entries, same bits.
 template <bool CPLX>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void fold_gemm_table_kernel(GemmArgs g) {
-    using G = FoldTile<FORM_FP32, 2>;
+    using G = FoldTile<FORM_FP32, 2, 2>;
     extern __shared__ __attribute__((aligned(16))) uint8_t dyn[];
     float* ct = reinterpret_cast<float*>(dyn + 2 * G::STAGE);
     for (int r = threadIdx.x; r < 2 * g.K; r += G::NTH) ct[r] = g.ct[r];
@@ -392,48 +403,63 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
     const int64_t nm = (g.F * (CPLX ? 2 : 1) + G::BMR - 1) / G::BMR, nn = (g.N + G::BJ - 1) / G::BJ;
     int64_t m0, n0;
     fold_place(xcd_logical_block(blockIdx.x, gridDim.x), nm, nn, G::BMR, G::BJ, m0, n0);
-    fold_tile<FORM_FP32, CPLX, 2, true>(g, m0, n0, dyn, ct);
+    fold_tile<FORM_FP32, CPLX, 2, 2, true>(g, m0, n0, dyn, ct);
 }
 
 // Batched: block b serves tile b / 8 of XCD b % 8's range of the table's
-// folded tiles (128 rows x 64 columns).
+// folded tiles (fold_batch_tile).
 template <int FORM>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ __launch_bounds__(FORM == FORM_FP32 ? 256 : 512) __attribute__((amdgpu_waves_per_eu(2)))
 void fold_gemm_batch_kernel(const BatchTable* __restrict__ t) {
-    using G = FoldTile<FORM, 2>;
-    static_assert(G::BMR == kFoldBM && G::BJ == kFoldBJ, "batch planner and kernel agree on the tile");
-    __shared__ __attribute__((aligned(16))) uint8_t lds[2 * G::STAGE];
+    constexpr bool F32 = FORM == FORM_FP32;
+    using G = FoldTile<FORM, 2, F32 ? 2 : 4>;
+    using G64 = FoldTile<FORM, F32 ? 2 : 4, 2>;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[2 * (G::STAGE > G64::STAGE ? G::STAGE : G64::STAGE)];
     const int x = blockIdx.x & 7;
     const int64_t u = t->gfold_bounds[x] + (blockIdx.x >> 3);
     if (u >= t->gfold_bounds[x + 1]) return;
     const int it = batch_find(t->items, t->n_items, u, /*stage=*/5);
     const GemmArgs g = t->items[it].gemm;
-    const int64_t cf = g.real_pack ? 1 : 2;
-    const int64_t nm = (g.F * cf + G::BMR - 1) / G::BMR, nn = (g.N + G::BJ - 1) / G::BJ;
-    int64_t m0, n0;
-    fold_place(u - t->items[it].gfold_unit0, nm, nn, G::BMR, G::BJ, m0, n0);
-    if (g.real_pack) fold_tile<FORM, false, 2, false>(g, m0, n0, lds, nullptr);
-    else fold_tile<FORM, true, 2, false>(g, m0, n0, lds, nullptr);
+    int64_t bm, bj, m0, n0;
+    const int64_t rows = g.F * (g.real_pack ? 1 : 2);
+    fold_batch_tile(FORM, g.N, bm, bj);
+    fold_place(u - t->items[it].gfold_unit0, (rows + bm - 1) / bm, (g.N + bj - 1) / bj, bm, bj, m0, n0);
+    if (!F32 && g.N == 64) {
+        if (g.real_pack) fold_tile<FORM, false, F32 ? 2 : 4, 2, false>(g, m0, n0, lds, nullptr);
+        else fold_tile<FORM, true, F32 ? 2 : 4, 2, false>(g, m0, n0, lds, nullptr);
+    } else {
+        if (g.real_pack) fold_tile<FORM, false, 2, F32 ? 2 : 4, false>(g, m0, n0, lds, nullptr);
+        else fold_tile<FORM, true, 2, F32 ? 2 : 4, false>(g, m0, n0, lds, nullptr);
+    }
 }
 
+template <int FORM, bool CPLX, int WGM, int WGN>
+hipError_t launch_fold_wide(const GemmArgs& g, hipStream_t s) {
+    using G = FoldTile<FORM, WGM, WGN>;
+    const int64_t nm = (g.F * (CPLX ? 2 : 1) + G::BMR - 1) / G::BMR, nn = (g.N + G::BJ - 1) / G::BJ;
+    hipLaunchKernelGGL((fold_gemm_kernel<FORM, CPLX, WGM, WGN>), dim3((unsigned)(nm * nn)), dim3(G::NTH), 0, s, g);
+    return hipGetLastError();
+}
+
+// Below 96 tiles of 128 x 128 most CUs would have no large tile (4096 complex
+// channels, FP32: 64 of them take 106 us either way, 128 take 166 us against
+// 201 us with the small ones; 1024 real channels, BF16x3: 64 take 35 us against
+// 31 us, 128 37 us against 58 us).
 template <int FORM, bool CPLX>
 hipError_t launch_fold_form(const GemmArgs& g, hipStream_t s) {
     const int64_t R = g.F * (CPLX ? 2 : 1);
-    if ((R + 127) / 128 * ((g.N + 63) / 64) < 256) {
+    if (R * g.N < 96 * 128 * 128) {
         const int64_t blocks = (R + 63) / 64 * (g.N / 32);
         hipLaunchKernelGGL((fold_gemm_small_kernel<FORM, CPLX>), dim3((unsigned)blocks), dim3(256), 0, s, g);
         return hipGetLastError();
     }
-    constexpr int WGN = 2;
-    using G = FoldTile<FORM, WGN>;
-    const int64_t nm = (R + G::BMR - 1) / G::BMR, nn = (g.N + G::BJ - 1) / G::BJ;
-    hipLaunchKernelGGL((fold_gemm_kernel<FORM, CPLX, WGN>), dim3((unsigned)(nm * nn)), dim3(G::NTH), 0, s, g);
-    return hipGetLastError();
+    if constexpr (FORM == FORM_FP32) return launch_fold_wide<FORM, CPLX, 2, 2>(g, s);
+    else return g.N == 64 ? launch_fold_wide<FORM, CPLX, 4, 2>(g, s) : launch_fold_wide<FORM, CPLX, 2, 4>(g, s);
 }
 
 template <bool CPLX>
 hipError_t launch_fold_table(const GemmArgs& g, hipStream_t s) {
-    using G = FoldTile<FORM_FP32, 2>;
+    using G = FoldTile<FORM_FP32, 2, 2>;
     const int64_t nm = (g.F * (CPLX ? 2 : 1) + G::BMR - 1) / G::BMR, nn = (g.N + G::BJ - 1) / G::BJ;
     static const hipError_t attr = hipFuncSetAttribute((const void*)fold_gemm_table_kernel<CPLX>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -464,8 +490,8 @@ hipError_t launch_dft_fold(const GemmArgs& g, hipStream_t s) {
 hipError_t launch_fold_gemm_batch(const BatchTable* t, int form, int grid, hipStream_t s) {
     switch (form) {
         case FORM_FP32: hipLaunchKernelGGL((fold_gemm_batch_kernel<FORM_FP32>), dim3(grid), dim3(256), 0, s, t); break;
-        case FORM_BF16: hipLaunchKernelGGL((fold_gemm_batch_kernel<FORM_BF16>), dim3(grid), dim3(256), 0, s, t); break;
-        case FORM_BF16X3: hipLaunchKernelGGL((fold_gemm_batch_kernel<FORM_BF16X3>), dim3(grid), dim3(256), 0, s, t); break;
+        case FORM_BF16: hipLaunchKernelGGL((fold_gemm_batch_kernel<FORM_BF16>), dim3(grid), dim3(512), 0, s, t); break;
+        case FORM_BF16X3: hipLaunchKernelGGL((fold_gemm_batch_kernel<FORM_BF16X3>), dim3(grid), dim3(512), 0, s, t); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -128,7 +128,11 @@ hipError_t launch_dft_fold(const GemmArgs& a, hipStream_t s);
 hipError_t launch_fold_operand(void* piece0, void* piece1, int P, int form, hipStream_t s);
 // tw: (cos, sin)(pi k / P), k < P/2; ct (optional): cos(pi r / P), r < 2P.
 hipError_t launch_fold_tables(float* tw, float* ct, int P, hipStream_t s);
-constexpr int kFoldBM = 128, kFoldBJ = 64;  // tile rows and columns of the batched folded product
+// Tile rows and columns of the batched folded product for N columns.
+__host__ __device__ inline void fold_batch_tile(int form, int64_t N, int64_t& bm, int64_t& bj) {
+    bm = form != FORM_FP32 && N == 64 ? 256 : 128;
+    bj = form == FORM_FP32 || N == 64 ? 64 : 128;
+}
 // Forms whose A the FIR can write in operand form.
 bool gemm_raw_form(int form);
 
