@@ -328,7 +328,7 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
             const int ring = p->M <= 16 ? p->M : p->M <= 32 ? 32 : 64;
             const int TF = frames_per_thread(ring);
             bi.fir_tf = TF;
-            ffu[i] = (F + TF - 1) / TF * (p->W / 256);
+            ffu[i] = (F + TF - 1) / TF * (p->W / (256 * fold_batch_vec(b->form, p->cf, p->M)));
             int64_t bm, bj;
             fold_batch_tile(b->form, p->N, bm, bj);
             gfu[i] = (F * p->cf + bm - 1) / bm * ((p->N + bj - 1) / bj);

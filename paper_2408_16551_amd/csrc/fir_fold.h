@@ -47,25 +47,22 @@ __device__ __forceinline__ fvec4 fold_mirror(const fvec4& v, bool cplx) {
     return cplx ? __builtin_shufflevector(v, v, 2, 3, 0, 1) : __builtin_shufflevector(v, v, 3, 2, 1, 0);
 }
 
-// N consecutive elements (N = 2 or 4) of a part row, in the operand type.
-template <int QM, int N>
-__device__ __forceinline__ void fold_put(const FirArgs& a, int64_t el, const float (&v)[N]) {
+// Four consecutive elements of a part row, in the operand type.
+template <int QM>
+__device__ __forceinline__ void fold_put(const FirArgs& a, int64_t el, const float (&v)[4]) {
     if constexpr (QM == QM_NONE) {
-        if constexpr (N == 4) st<true>(reinterpret_cast<fvec4*>(a.y + el), fvec4{v[0], v[1], v[2], v[3]});
-        else st<true>(reinterpret_cast<fvec2*>(a.y + el), fvec2{v[0], v[1]});
+        st<true>(reinterpret_cast<fvec4*>(a.y + el), fvec4{v[0], v[1], v[2], v[3]});
     } else {
         static_assert(QM == QM_BF16 || QM == QM_BF16X2, "operand types of the folded product");
-        uint32_t hi[N], lo[N];
+        uint32_t hi[4], lo[4];
 #pragma unroll
-        for (int i = 0; i < N; ++i) {
+        for (int i = 0; i < 4; ++i) {
             hi[i] = bf16_bits(v[i]);
             lo[i] = bf16_bits(v[i] - __builtin_bit_cast(float, hi[i] << 16));
         }
-        auto put = [&](uint8_t* base, const uint32_t (&h)[N]) {
-            if constexpr (N == 4)
-                st<true>(reinterpret_cast<uint64_t*>(base + el * 2),
-                         (uint64_t)(h[0] | (h[1] << 16)) | ((uint64_t)(h[2] | (h[3] << 16)) << 32));
-            else st<true>(reinterpret_cast<uint32_t*>(base + el * 2), h[0] | (h[1] << 16));
+        auto put = [&](uint8_t* base, const uint32_t (&h)[4]) {
+            st<true>(reinterpret_cast<uint64_t*>(base + el * 2),
+                     (uint64_t)(h[0] | (h[1] << 16)) | ((uint64_t)(h[2] | (h[3] << 16)) << 32));
         };
         put(a.q, hi);
         if constexpr (QM == QM_BF16X2) put(a.q1, lo);
@@ -73,33 +70,46 @@ __device__ __forceinline__ void fold_put(const FirArgs& a, int64_t el, const flo
 }
 
 // Folds and stores `cnt` frames (first frame f0) of LDS buffer ys: column
-// block at sample/float offset c0 of each quarter frame.
+// block at float offset c0 of each quarter frame.  A thread stores four
+// elements of a part at a time: real frames four samples' four parts, complex
+// ones two of the parts (even or odd channels) of four samples.
 template <int VEC, int GW, int QM>
 __device__ __forceinline__ void fold_store(const FirArgs& a, const float (&ys)[FoldGeom<VEC, GW>::SB][4 * FoldGeom<VEC, GW>::GF],
                                            int64_t f0, int cnt, int c0) {
     using G = FoldGeom<VEC, GW>;
     constexpr int X4 = G::GF / 4;  // float4 positions per group
-    const bool cplx = a.cf == 2;
     const int Q = a.P / 4;
-    for (int it = threadIdx.x; it < cnt * X4; it += G::NTH) {
-        const int fr = it / X4, x = it % X4;
-        const fvec4* row = reinterpret_cast<const fvec4*>(ys[fr]);
-        const fvec4 A = row[x], B = fold_mirror(row[X4 + X4 - 1 - x], cplx);
-        const fvec4 C = row[2 * X4 + x], D = fold_mirror(row[3 * X4 + X4 - 1 - x], cplx);
-        const fvec4 e = A + D, e2 = B + C, o = A - D, o2 = B - C;
-        const fvec4 part[4] = {e + e2, o - o2, e - e2, o + o2};
-        const int64_t el = (f0 + fr) * (int64_t)a.W;
-        if (cplx) {
-            const int64_t pos = el + c0 / 2 + 2 * x;
+    if (a.cf == 2) {
+        for (int it = threadIdx.x; it < cnt * X4; it += G::NTH) {
+            const int fr = it / X4, h = (it % X4) / (X4 / 2), x = it % (X4 / 2);  // h: odd channels
+            const fvec4* row = reinterpret_cast<const fvec4*>(ys[fr]);
+            fvec4 c[2], s[2];
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                fold_put<QM, 2>(a, pos + s * Q, {part[s][0], part[s][2]});
-                fold_put<QM, 2>(a, pos + a.P + s * Q, {part[s][1], part[s][3]});
+            for (int i = 0; i < 2; ++i) {
+                const int q = 2 * x + i;
+                const fvec4 A = row[q], B = fold_mirror(row[X4 + X4 - 1 - q], true);
+                const fvec4 C = row[2 * X4 + q], D = fold_mirror(row[3 * X4 + X4 - 1 - q], true);
+                const fvec4 e = A + D, e2 = B + C, o = A - D, o2 = B - C;
+                c[i] = h ? e - e2 : e + e2;
+                s[i] = h ? o + o2 : o - o2;
             }
-        } else {
+            const int64_t el = (f0 + fr) * (int64_t)a.W + c0 / 2 + 4 * x + 2 * h * Q;
+            fold_put<QM>(a, el, {c[0][0], c[0][2], c[1][0], c[1][2]});
+            fold_put<QM>(a, el + Q, {s[0][0], s[0][2], s[1][0], s[1][2]});
+            fold_put<QM>(a, el + a.P, {c[0][1], c[0][3], c[1][1], c[1][3]});
+            fold_put<QM>(a, el + a.P + Q, {s[0][1], s[0][3], s[1][1], s[1][3]});
+        }
+    } else {
+        for (int it = threadIdx.x; it < cnt * X4; it += G::NTH) {
+            const int fr = it / X4, x = it % X4;
+            const fvec4* row = reinterpret_cast<const fvec4*>(ys[fr]);
+            const fvec4 A = row[x], B = fold_mirror(row[X4 + X4 - 1 - x], false);
+            const fvec4 C = row[2 * X4 + x], D = fold_mirror(row[3 * X4 + X4 - 1 - x], false);
+            const fvec4 e = A + D, e2 = B + C, o = A - D, o2 = B - C;
+            const fvec4 part[4] = {e + e2, o - o2, e - e2, o + o2};
+            const int64_t el = (f0 + fr) * (int64_t)a.W + c0 + 4 * x;
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
-                fold_put<QM, 4>(a, el + c0 + 4 * x + s * Q, {part[s][0], part[s][1], part[s][2], part[s][3]});
+            for (int s = 0; s < 4; ++s) fold_put<QM>(a, el + s * Q, {part[s][0], part[s][1], part[s][2], part[s][3]});
         }
     }
 }
@@ -196,20 +206,25 @@ __global__ __launch_bounds__((FoldGeom<VEC, GW>::NTH)) void fir_fold_kernel(FirA
     fir_fold_unit<VEC, GW, MT, EXACT, QM>(a, TF, xcd_logical_block(blockIdx.x, gridDim.x), sm, ph);
 }
 
-template <int M0, int MT, int QM>
-__device__ __forceinline__ void fir_fold_unit_own_m(const FirArgs& a, int TF, int64_t blk, FoldSmem<1, 1>& sm, int& ph) {
+template <int VEC, int M0, int MT, int QM>
+__device__ __forceinline__ void fir_fold_unit_own_m(const FirArgs& a, int TF, int64_t blk, FoldSmem<VEC, 1>& sm, int& ph) {
     if constexpr (M0 <= MT) {
-        if (a.M == M0) fir_fold_unit<1, 1, M0, true, QM>(a, TF, blk, sm, ph);
-        else fir_fold_unit_own_m<M0 + 1, MT, QM>(a, TF, blk, sm, ph);
+        if (a.M == M0) fir_fold_unit<VEC, 1, M0, true, QM>(a, TF, blk, sm, ph);
+        else fir_fold_unit_own_m<VEC, M0 + 1, MT, QM>(a, TF, blk, sm, ph);
     }
 }
 
-// Persistent batched form, over the table's folded FIR units: one float per
-// thread (any alignment), the ring unrolled for the item's own tap count up
-// to 16, else 32 or 64 with the taps beyond M switched off.
+// Persistent batched form, over the table's folded FIR units, with the ring
+// unrolled for the item's own tap count up to 16, else 32 or 64 with the taps
+// beyond M switched off.  One float per thread (any alignment); two, a complex
+// sample, in the 16-bit forms (whole 128-byte lines of a part row).
 template <int MAXM, int QM>
 __global__ __launch_bounds__(256) void fir_fold_batch_kernel(const BatchTable* __restrict__ t) {
-    __shared__ __attribute__((aligned(16))) FoldSmem<1, 1> sm;
+    constexpr int CV = QM == QM_NONE ? 1 : 2;  // floats per thread of complex items
+    __shared__ __attribute__((aligned(16))) union {
+        FoldSmem<1, 1> one;
+        FoldSmem<CV, 1> cplx;
+    } sm;
     int ph = 0;
     const int x = blockIdx.x & 7, i = blockIdx.x >> 3, nbx = gridDim.x >> 3;
     const int64_t end = t->ffold_bounds[x + 1];
@@ -219,10 +234,11 @@ __global__ __launch_bounds__(256) void fir_fold_batch_kernel(const BatchTable* _
         const FirArgs fa = b.fir;
         const int64_t blk = u - b.ffold_unit0;
         if (MAXM <= 16 || fa.M <= 16) {
-            fir_fold_unit_own_m<1, 16, QM>(fa, b.fir_tf, blk, sm, ph);
+            if (CV == 2 && fa.cf == 2) fir_fold_unit_own_m<CV, 1, 16, QM>(fa, b.fir_tf, blk, sm.cplx, ph);
+            else fir_fold_unit_own_m<1, 1, 16, QM>(fa, b.fir_tf, blk, sm.one, ph);
         } else {
-            if constexpr (MAXM == 32) fir_fold_unit<1, 1, 32, false, QM>(fa, b.fir_tf, blk, sm, ph);
-            if constexpr (MAXM == 64) fir_fold_unit<1, 1, 64, false, QM>(fa, b.fir_tf, blk, sm, ph);
+            if constexpr (MAXM == 32) fir_fold_unit<1, 1, 32, false, QM>(fa, b.fir_tf, blk, sm.one, ph);
+            if constexpr (MAXM == 64) fir_fold_unit<1, 1, 64, false, QM>(fa, b.fir_tf, blk, sm.one, ph);
         }
     }
 }
@@ -254,6 +270,10 @@ hipError_t launch_fold_qm(const FirArgs& a, hipStream_t s) {
     auto aligned = [&](const void* p) { return ((uintptr_t)p & 15) == 0; };
     const bool al16 = a.plen % 4 == 0 && aligned(a.chunk) && (!a.prefix || aligned(a.prefix));
     if (a.M <= 8 && al16 && a.W >= 1024) return launch_fold_m<4, 1, 1, 8, QM>(a, s);
+    // 16-bit complex rows: 128 lanes a group, so that a part row's piece of 64
+    // samples fills a 128-byte line (1024 channels, 16 taps, 2^25 samples, BF16x3:
+    // 163 us with 64 lanes and half lines, 129 us; FP32 rows the same either way).
+    if (QM != QM_NONE && a.cf == 2 && a.M <= 16) return launch_fold_m<1, 2, 1, 16, QM>(a, s);
     if (a.M <= 16) return launch_fold_m<1, 1, 1, 16, QM>(a, s);
     if (a.M <= 32) return launch_fold_one<1, 1, 32, false, QM>(a, s);
     if (a.M <= 64) return launch_fold_one<1, 1, 64, false, QM>(a, s);

@@ -128,6 +128,8 @@ hipError_t launch_dft_fold(const GemmArgs& a, hipStream_t s);
 hipError_t launch_fold_operand(void* piece0, void* piece1, int P, int form, hipStream_t s);
 // tw: (cos, sin)(pi k / P), k < P/2; ct (optional): cos(pi r / P), r < 2P.
 hipError_t launch_fold_tables(float* tw, float* ct, int P, hipStream_t s);
+// Floats per thread of the batched folded FIR (its column blocks are 256 times as wide).
+inline int fold_batch_vec(int form, int cf, int M) { return form != FORM_FP32 && cf == 2 && M <= 16 ? 2 : 1; }
 // Tile rows and columns of the batched folded product for N columns.
 __host__ __device__ inline void fold_batch_tile(int form, int64_t N, int64_t& bm, int64_t& bj) {
     bm = form != FORM_FP32 && N == 64 ? 256 : 128;
