@@ -99,20 +99,31 @@ __device__ __forceinline__ void fold_out_real(float* row, int P, int j, const fl
     }
 }
 // Complex frames: index 0 = real row, 1 = imaginary row.
-__device__ __forceinline__ void fold_out_cplx(float* row, int P, int j, const float4& w, const float (&c0)[2],
+// inv != 0: the inverse DFT, the same values times inv = 1/P in the order of
+// -k (w already holds the factor, a power of two).
+__device__ __forceinline__ void fold_out_cplx(float* row, int P, int j, const float4& w, float inv, const float (&c0)[2],
                                               const float (&s0)[2], const float (&c1)[2], const float (&s1)[2]) {
     const float ur = c1[0] + s1[1], ui = c1[1] - s1[0];  // C - iS
     const float vr = c1[0] - s1[1], vi = c1[1] + s1[0];  // C + iS
     const float x1r = mul2(w.z, ur, -w.w, ui), x1i = mul2(w.w, ur, w.z, ui);
     const float y1r = mul2(w.z, vr, w.w, vi), y1i = mul2(w.z, vi, -w.w, vr);
     if (j == 0) {  // X_0 = C_0, X_{P/2} = S_{P/2}
-        put16(row, c0[0], c0[1], x1r, x1i);
-        *reinterpret_cast<fvec2*>(row + P) = fvec2{s0[0], s0[1]};
-        *reinterpret_cast<fvec2*>(row + 2 * (P - 1)) = fvec2{y1r, y1i};
+        const float sc = inv != 0.0f ? inv : 1.0f;
+        put16(row, sc * c0[0], sc * c0[1], inv != 0.0f ? y1r : x1r, inv != 0.0f ? y1i : x1i);
+        *reinterpret_cast<fvec2*>(row + P) = fvec2{sc * s0[0], sc * s0[1]};
+        *reinterpret_cast<fvec2*>(row + 2 * (P - 1)) = inv != 0.0f ? fvec2{x1r, x1i} : fvec2{y1r, y1i};
     } else {
         const float pr = c0[0] + s0[1], pi = c0[1] - s0[0], mr = c0[0] - s0[1], mi = c0[1] + s0[0];
-        put16(row + 4 * j, mul2(w.x, pr, -w.y, pi), mul2(w.y, pr, w.x, pi), x1r, x1i);
-        put16(row + 2 * (P - 1 - 2 * j), y1r, y1i, mul2(w.x, mr, w.y, mi), mul2(w.x, mi, -w.y, mr));
+        const float x0r = mul2(w.x, pr, -w.y, pi), x0i = mul2(w.y, pr, w.x, pi);
+        const float y0r = mul2(w.x, mr, w.y, mi), y0i = mul2(w.x, mi, -w.y, mr);
+        float *up = row + 4 * j, *down = row + 2 * (P - 1 - 2 * j);
+        if (inv != 0.0f) {
+            put16(up, y0r, y0i, y1r, y1i);
+            put16(down, x1r, x1i, x0r, x0i);
+        } else {
+            put16(up, x0r, x0i, x1r, x1i);
+            put16(down, y1r, y1i, y0r, y0i);
+        }
     }
 }
 
@@ -279,7 +290,7 @@ __device__ __forceinline__ void fold_tile(const GemmArgs& g, int64_t m0, int64_t
             if (f < g.F) {
                 const float c0[2] = {acc[0][0][v], acc[0][1][v]}, s0[2] = {acc[1][0][v], acc[1][1][v]};
                 const float c1[2] = {acc[2][0][v], acc[2][1][v]}, s1[2] = {acc[3][0][v], acc[3][1][v]};
-                fold_out_cplx(g.out + f * g.ldo, P, j, w, c0, s0, c1, s1);
+                fold_out_cplx(g.out + f * g.ldo, P, j, w, g.inv, c0, s0, c1, s1);
             }
         } else {
 #pragma unroll
@@ -354,7 +365,7 @@ __device__ __forceinline__ void fold_tile_small(const GemmArgs& g, int64_t m0, i
         if constexpr (CPLX) {
             const float c0[2] = {at(0, i), at(0, 32 + i)}, s0[2] = {at(1, i), at(1, 32 + i)};
             const float c1[2] = {at(2, i), at(2, 32 + i)}, s1[2] = {at(3, i), at(3, 32 + i)};
-            fold_out_cplx(row, P, j, w, c0, s0, c1, s1);
+            fold_out_cplx(row, P, j, w, g.inv, c0, s0, c1, s1);
         } else {
             fold_out_real(row, P, j, w, at(0, i), at(1, i), at(2, i), at(3, i));
         }

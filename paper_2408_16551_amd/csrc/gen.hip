@@ -178,14 +178,15 @@ __global__ void fold_operand_kernel(void* piece0, void* piece1, int P) {
     }
 }
 
-__global__ void fold_tables_kernel(float* tw, float* ct, int P) {
+__global__ void fold_tables_kernel(float* tw, float* ct, float* ones, int P, float scale) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < P / 2) {
         double s, c;
         sincospi((double)i / (double)P, &s, &c);
-        tw[2 * i] = __double2float_rn(c);
-        tw[2 * i + 1] = __double2float_rn(s);
+        tw[2 * i] = scale * __double2float_rn(c);
+        tw[2 * i + 1] = scale * __double2float_rn(s);
     }
+    if (ones && i < P) ones[i] = 1.0f;
     if (ct && i < 2 * P) ct[i] = __double2float_rn(cospi((double)i / (double)P));
 }
 
@@ -228,8 +229,8 @@ hipError_t launch_fold_operand(void* piece0, void* piece1, int P, int form, hipS
     return hipGetLastError();
 }
 
-hipError_t launch_fold_tables(float* tw, float* ct, int P, hipStream_t s) {
-    hipLaunchKernelGGL(fold_tables_kernel, dim3((2 * P + 255) / 256), dim3(256), 0, s, tw, ct, P);
+hipError_t launch_fold_tables(float* tw, float* ct, float* ones, int P, float scale, hipStream_t s) {
+    hipLaunchKernelGGL(fold_tables_kernel, dim3((2 * P + 255) / 256), dim3(256), 0, s, tw, ct, ones, P, scale);
     return hipGetLastError();
 }
 

@@ -107,6 +107,7 @@ struct GemmArgs {
     const float* tw;       // FP32 only, non-null: Bt assembled from this P x (cos, sin) twiddle table (B0 unused)
                            // (folded product: cos, sin of pi k / P, k < P/2, for every form)
     const float* ct;       // folded product, FP32 only, non-null: operand assembled from cos(pi r / P), r < 2P
+    float inv;             // folded product, complex: 1/P for the inverse DFT (tw times 1/P), else 0
 };
 hipError_t launch_dft_gemm(const GemmArgs& a, hipStream_t s);
 
@@ -126,8 +127,9 @@ hipError_t launch_fir_fold(const FirArgs& a, hipStream_t s);
 hipError_t launch_dft_fold(const GemmArgs& a, hipStream_t s);
 // Folded operand [Q][4 parts][Q] in the pieces of `form`, in FP64 rounded once.
 hipError_t launch_fold_operand(void* piece0, void* piece1, int P, int form, hipStream_t s);
-// tw: (cos, sin)(pi k / P), k < P/2; ct (optional): cos(pi r / P), r < 2P.
-hipError_t launch_fold_tables(float* tw, float* ct, int P, hipStream_t s);
+// tw: (cos, sin)(pi k / P) times scale (a power of two), k < P/2; ct (optional):
+// cos(pi r / P), r < 2P; ones (optional): P times 1.
+hipError_t launch_fold_tables(float* tw, float* ct, float* ones, int P, float scale, hipStream_t s);
 // Floats per thread of the batched folded FIR (its column blocks are 256 times as wide).
 inline int fold_batch_vec(int form, int cf, int M) { return form != FORM_FP32 && cf == 2 && M <= 16 ? 2 : 1; }
 // Tile rows and columns of the batched folded product for N columns.

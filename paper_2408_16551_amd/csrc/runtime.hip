@@ -104,7 +104,7 @@ tina_status tina_pfb_plan(const tina_pfb_desc* d, tina_pfb_plan_t* out) {
     }
     p->K = p->W;
     p->N = p->W;
-    p->fold = d->output == TINA_OUT_PFB && fold_supported(p->P, p->precision) &&
+    p->fold = d->output != TINA_OUT_FIR_ONLY && fold_supported(p->P, p->precision) &&
               (dft_alg == TINA_DFT_DENSE || dft_alg == TINA_DFT_FUSED || dft_alg == TINA_DFT_TABLE);
     p->kout = d->output != TINA_OUT_PFB ? p->P : (p->cf == 2 ? p->P : p->P / 2 + 1);
 
@@ -128,14 +128,26 @@ tina_status tina_pfb_plan(const tina_pfb_desc* d, tina_pfb_plan_t* out) {
     if (p->output != TINA_OUT_FIR_ONLY) {
         const int form = p->precision;
         if (p->output == TINA_OUT_INVERSE) {
+            if (p->fold) {
+                p->K = p->P;
+                p->N = p->P / 4;
+            }
             const int64_t nbytes = (int64_t)p->N * p->K * form_elem_bytes(form);
             for (int i = 0; i < form_pieces(form); ++i)
                 if (hipMalloc(&p->B[i], nbytes) != hipSuccess) return bail(TINA_ERR_OUT_OF_MEMORY, "plan: IDFT operand allocation");
+            if (p->fold && (hipMalloc(&p->fold_tw, sizeof(float) * p->P) != hipSuccess ||
+                            hipMalloc(&p->fold_one, sizeof(float) * p->P) != hipSuccess))
+                return bail(TINA_ERR_OUT_OF_MEMORY, "plan: twiddle table");
             if (hipMalloc(&p->g32, L * sizeof(float)) != hipSuccess) return bail(TINA_ERR_OUT_OF_MEMORY, "plan: synthesis taps");
             for (int i = 0; i < 2; ++i)
                 if (hipMalloc(&p->hist[i], std::max<int64_t>(1, (int64_t)(p->M - 1) * p->W) * sizeof(float)) != hipSuccess)
                     return bail(TINA_ERR_OUT_OF_MEMORY, "plan: synthesis history");
-            e = launch_dft_operand(p->B[0], p->B[1], p->P, 1, form, nullptr, /*inverse=*/1);
+            if (p->fold) {
+                e = launch_fold_tables(p->fold_tw, nullptr, p->fold_one, p->P, 1.0f / (float)p->P, nullptr);
+                if (e == hipSuccess) e = launch_fold_operand(p->B[0], p->B[1], p->P, form, nullptr);
+            } else {
+                e = launch_dft_operand(p->B[0], p->B[1], p->P, 1, form, nullptr, /*inverse=*/1);
+            }
             if (e == hipSuccess) e = launch_synthesis_taps(p->h64, p->g32, p->P, p->M, nullptr);
         } else if (p->fold) {
             p->K = p->P;
@@ -147,7 +159,7 @@ tina_status tina_pfb_plan(const tina_pfb_desc* d, tina_pfb_plan_t* out) {
             if (hipMalloc(&p->fold_tw, sizeof(float) * p->P) != hipSuccess ||
                 (table && hipMalloc(&p->fold_ct, sizeof(float) * 2 * p->P) != hipSuccess))
                 return bail(TINA_ERR_OUT_OF_MEMORY, "plan: twiddle table");
-            e = launch_fold_tables(p->fold_tw, p->fold_ct, p->P, nullptr);
+            e = launch_fold_tables(p->fold_tw, p->fold_ct, nullptr, p->P, 1.0f, nullptr);
             if (e == hipSuccess && !table) e = launch_fold_operand(p->B[0], p->B[1], p->P, form, nullptr);
         } else if (p->dft_algorithm == TINA_DFT_FACTORED || p->dft_algorithm == TINA_DFT_TABLE) {  // P twiddles alone
             if (hipMalloc(&p->fft_tw, sizeof(float) * 2 * p->P) != hipSuccess)
@@ -166,10 +178,12 @@ tina_status tina_pfb_plan(const tina_pfb_desc* d, tina_pfb_plan_t* out) {
         }
         if (e != hipSuccess) return bail(TINA_ERR_DEVICE, std::string("plan: DFT operand: ") + hipGetErrorString(e));
         const int64_t ws_bytes = ws_req == 0 ? kWorkspaceBytes : ws_req;
-        p->ch_frames = ws_bytes > 0 ? ws_bytes / ((int64_t)p->W * 4) : 0;
+        // Folded synthesis: a piece's folded channel frames lie after its inverse DFT.
+        const int64_t ws_rows = p->output == TINA_OUT_INVERSE && p->fold ? 2 : 1;
+        p->ch_frames = ws_bytes > 0 ? ws_bytes / (ws_rows * p->W * 4) : 0;
         p->ch_frames = p->ch_frames >= 128 ? (p->ch_frames / 128) * 128 : p->ch_frames;
         if (ws_bytes > 0 && p->ch_frames < 1) p->ch_frames = 1;
-        if (p->ch_frames > 0 && hipMalloc(&p->ws, p->ch_frames * p->W * sizeof(float)) != hipSuccess)
+        if (p->ch_frames > 0 && hipMalloc(&p->ws, ws_rows * p->ch_frames * p->W * sizeof(float)) != hipSuccess)
             return bail(TINA_ERR_OUT_OF_MEMORY, "plan: workspace allocation");
         if (p->ch_frames > 0 && form_scaled(form)) {
             p->amax_parts_cap = p->W / 32 > 1 ? p->W / 32 : 1;  // the most parts: one per 32 lanes at VEC = 1
@@ -512,7 +526,33 @@ tina_status tina_pfb_synthesize(tina_pfb_plan_t p, const void* d_X, int64_t F, v
         ga.N = p->N;
         ga.real_pack = 0;
         ga.form = p->precision;
-        HIP_TRY(launch_dft_gemm(ga, s));
+        if (p->fold) {
+            // The channel frames folded by the FIR kernel (one unit tap), then
+            // the forward product written in the order of -n, times 1/P.
+            FirArgs xa{};
+            xa.chunk = ga.A;
+            xa.nchunk = Fc * p->W;
+            xa.taps = p->fold_one;
+            xa.W = p->W;
+            xa.P = p->P;
+            xa.M = 1;
+            xa.cf = p->cf;
+            xa.F = Fc;
+            xa.qmode = form_fir_qmode(p->precision);
+            float* rows = p->ws + p->ch_frames * p->W;
+            if (xa.qmode == 0) xa.y = rows;
+            xa.q = (uint8_t*)rows;
+            xa.q1 = (uint8_t*)rows + p->ch_frames * p->W * 2;
+            HIP_TRY(launch_fir_fold(xa, s));
+            ga.A = xa.y;
+            ga.Aq = xa.q;
+            ga.Aq1 = xa.q1;
+            ga.tw = p->fold_tw;
+            ga.inv = 1.0f / (float)p->P;
+            HIP_TRY(launch_dft_fold(ga, s));
+        } else {
+            HIP_TRY(launch_dft_gemm(ga, s));
+        }
         FirArgs fa{};  // synthesis FIR across frames
         fa.prefix = prefix;
         fa.plen = hist_floats;

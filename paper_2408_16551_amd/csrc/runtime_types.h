@@ -92,6 +92,7 @@ struct tina_pfb_plan_s {
     bool fold = false;          // dense DFT by the folded product (B: its operand, K = P, N = P/4)
     float* fold_tw = nullptr;   // folded product: channel rotations
     float* fold_ct = nullptr;   // folded product with the table operand: cos(pi r / P)
+    float* fold_one = nullptr;  // P unit taps (synthesis: the channel frames are folded by the FIR)
     float* g32 = nullptr;       // synthesis FIR taps (inverse plans)
     float* hist[2] = {nullptr, nullptr};  // history scratch between workspace pieces (inverse plans)
     int cus = 256;
@@ -127,11 +128,11 @@ struct tina_pfb_plan_s {
         ev_pool.clear();
         clear_events();
         for (void* p : {(void*)h64, (void*)h32, B[0], B[1], (void*)ws, (void*)amax, (void*)fexp, (void*)fft_tw,
-                         (void*)fold_tw, (void*)fold_ct, (void*)g32, (void*)hist[0], (void*)hist[1]})
+                         (void*)fold_tw, (void*)fold_ct, (void*)fold_one, (void*)g32, (void*)hist[0], (void*)hist[1]})
             if (p) (void)hipFree(p);
         g32 = hist[0] = hist[1] = nullptr;
         h64 = nullptr; h32 = nullptr; B[0] = B[1] = nullptr; ws = nullptr; amax = nullptr; fexp = nullptr;
-        fft_tw = fold_tw = fold_ct = nullptr;
+        fft_tw = fold_tw = fold_ct = fold_one = nullptr;
     }
 };
 

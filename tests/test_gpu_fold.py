@@ -89,3 +89,24 @@ def test_batch_mixes_folded_and_unfolded_items_bitwise(prec):
     Batch(prec, max_items=len(items), workspace_bytes=1 << 28).execute(items)
     for (_, _, out), w in zip(items, want):
         assert np.array_equal(out.cpu().numpy(), w)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec", ["fp32", "bf16", "bf16x3"])
+@pytest.mark.parametrize("P,M,F", [(256, 3, 1), (256, 16, 129), (512, 8, 33), (1024, 1, 65), (4096, 5, 34), (8192, 2, 7)])
+def test_folded_synthesis_matches_oracle(oracle, P, M, F, prec):
+    """Synthesis through the folded inverse, also in workspace pieces and
+    chunks through a state, bit for bit."""
+    from paper_2408_16551_amd.pfb import Plan, State
+    g = np.random.Generator(np.random.PCG64(P + M + F))
+    X = (g.standard_normal((F, P)) + 1j * g.standard_normal((F, P))).astype(np.complex64)
+    plan = Plan(P, M, "c64", "hann", prec, "inverse")
+    Xd = torch.from_numpy(X).cuda()
+    got = plan.synthesize(Xd).cpu().numpy()
+    ref = oracle.synthesize(X.astype(np.complex128), P, M, oracle.window(P, M, "hann"))
+    assert rel_l2(got, ref) < BOUND[prec]
+    small = Plan(P, M, "c64", "hann", prec, "inverse", workspace_bytes=P * 16 * 5)
+    assert np.array_equal(small.synthesize(Xd).cpu().numpy(), got)
+    st, cut = State(plan), sorted({0, F // 3, F // 2, F})
+    parts = [plan.synthesize(Xd[a:b].clone(), state=st).cpu().numpy() for a, b in zip(cut[:-1], cut[1:])]
+    assert np.array_equal(np.concatenate(parts), got)
