@@ -88,7 +88,10 @@ typedef enum tina_window {
  *   FP16X3     float16 hi + lo pieces (lo scaled by 2^11), three products,
  *              same per-frame power-of-two scale.
  *   FP8_FRAME  operands in FP8 E4M3 (OCP), each frame scaled by a power of two
- *              so that its largest branch output maps to at most 448.
+ *              so that its largest branch output maps to at most 448.  From 256
+ *              channels the branch outputs are rounded to E4M3's four
+ *              significant bits, and their sums and the Fourier coefficients
+ *              (see TINA_DFT_DENSE) to bfloat16, whose range needs no scale.
  *   MXFP8      block-scaled FP8 (quantisation, Sec. 1): operands in E4M3 with
  *              one power-of-two scale per 32 consecutive entries along the
  *              summed axis (a frame's branch values, re/im interleaved for
@@ -138,7 +141,7 @@ typedef struct tina_pfb_desc {
 /* How the DFT across branches is computed (both give the DFT of Eq. (12)):
  *   TINA_DFT_DENSE     the dense matrix product X = Y F on the MFMA units, in the
  *                      plan's precision (the paper's pointwise-convolution mapping).
- *                      From 256 channels, FP32, BF16 and BF16X3 use the symmetry of
+ *                      From 256 channels, FP32, BF16, BF16X3 and FP8 use the symmetry of
  *                      F: around the half sample its columns are even or odd in p
  *                      and under p -> P/2 - 1 - p, so the FIR writes four sums of
  *                      every four samples (FP32, then rounded to the operand type)

@@ -311,7 +311,11 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
         ga.Aq1 = fa.q1;
         ga.Aqs = fa.qs;
         ga.fexp = fa.fexp;
-        if (p->fold) ga.tw = p->fold_tw;
+        if (p->fold) {
+            ga.tw = p->fold_tw;
+            ga.form = fold_operand_form(b->form);
+            fa.qmode = fold_fir_qmode(b->form);
+        }
         // Per-frame scaled items with frame rows of 1024 threads and at least
         // frame_stage_min frames run in one pass (frame stage, units of about
         // frame_tf_target frames); the others in the three FIR launches
@@ -328,6 +332,7 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
             const int ring = p->M <= 16 ? p->M : p->M <= 32 ? 32 : 64;
             const int TF = frames_per_thread(ring);
             bi.fir_tf = TF;
+            bi.fir_single = 1;  // no exponents to find for it
             ffu[i] = (F + TF - 1) / TF * (p->W / (256 * fold_batch_vec(b->form, p->cf, p->M)));
             int64_t bm, bj;
             fold_batch_tile(b->form, p->N, bm, bj);
@@ -469,10 +474,10 @@ tina_status launch_stages(tina_pfb_batch_s* b, hipStream_t s, const Tune& tune, 
     const int64_t grid_gemm = fixed_gemm_grid > 0 ? fixed_gemm_grid : gemm_grid(b->h_table);
     const int64_t grid_fold = fixed_fold_grid > 0 ? fixed_fold_grid : fold_grid(b->h_table);
     const int qmode = form_fir_qmode(b->form);
-    if (stages & STAGE_FOLD) HIP_TRY(launch_fir_fold_batch(b->d_table, max_m, qmode, grid_fir, s));
+    if (stages & STAGE_FOLD) HIP_TRY(launch_fir_fold_batch(b->d_table, max_m, fold_fir_qmode(b->form), grid_fir, s));
     if ((stages & STAGE_DENSE) && (always || b->h_table->fir_units > 0 || b->h_table->frame_units > 0))
         HIP_TRY(launch_fir_batch(b->d_table, max_m, all_exact, qmode, grid_fir, s, b->frame_stage));
-    if (stages & STAGE_FOLD) HIP_TRY(launch_fold_gemm_batch(b->d_table, b->form, (int)grid_fold, s));
+    if (stages & STAGE_FOLD) HIP_TRY(launch_fold_gemm_batch(b->d_table, fold_operand_form(b->form), (int)grid_fold, s));
     if ((stages & STAGE_DENSE) && (always || b->h_table->gemm_units > 0))
         HIP_TRY(launch_gemm_batch(b->d_table, b->form, qmode != 0, tune.gemm_tile_n, (int)grid_gemm, s, wide));
     if (!always)  // factored-DFT items: never in a captured step (the groups change from call to call)

@@ -209,6 +209,7 @@ hipError_t launch_fir_fold(const FirArgs& a, hipStream_t s) {
         case QM_NONE: return launch_fold_f32(a, s);
         case QM_BF16: return launch_fold_bf16(a, s);
         case QM_BF16X2: return launch_fold_bf16x2(a, s);
+        case QM_F8BF16: return launch_fold_f8bf16(a, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -218,6 +219,7 @@ hipError_t launch_fir_fold_batch(const BatchTable* t, int max_m, int qmode, int 
         case QM_NONE: return launch_fold_batch_f32(t, max_m, grid, s);
         case QM_BF16: return launch_fold_batch_bf16(t, max_m, grid, s);
         case QM_BF16X2: return launch_fold_batch_bf16x2(t, max_m, grid, s);
+        case QM_F8BF16: return launch_fold_batch_f8bf16(t, max_m, grid, s);
         default: return hipErrorInvalidValue;
     }
 }

@@ -53,7 +53,7 @@ __device__ __forceinline__ void fold_put(const FirArgs& a, int64_t el, const flo
     if constexpr (QM == QM_NONE) {
         st<true>(reinterpret_cast<fvec4*>(a.y + el), fvec4{v[0], v[1], v[2], v[3]});
     } else {
-        static_assert(QM == QM_BF16 || QM == QM_BF16X2, "operand types of the folded product");
+        static_assert(QM == QM_BF16 || QM == QM_BF16X2 || QM == QM_F8BF16, "operand types of the folded product");
         uint32_t hi[4], lo[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -67,6 +67,20 @@ __device__ __forceinline__ void fold_put(const FirArgs& a, int64_t el, const flo
         put(a.q, hi);
         if constexpr (QM == QM_BF16X2) put(a.q1, lo);
     }
+}
+
+// A value as the fold takes it: for FP8 rounded (to nearest even) to the 4
+// significant bits of E4M3, on the bit pattern.
+template <int VEC, int QM>
+__device__ __forceinline__ typename VecT<VEC>::T fold_value(typename VecT<VEC>::T v) {
+    if constexpr (QM == QM_F8BF16) {
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+            const uint32_t u = __builtin_bit_cast(uint32_t, vget<VEC>(v, i));
+            vset<VEC>(v, i, __builtin_bit_cast(float, (u + 0x7ffffu + ((u >> 20) & 1u)) & 0xfff00000u));
+        }
+    }
+    return v;
 }
 
 // Folds and stores `cnt` frames (first frame f0) of LDS buffer ys: column
@@ -157,7 +171,7 @@ __device__ __forceinline__ void fir_fold_unit(const FirArgs& a, int TF, int64_t 
     auto slow = [&](int64_t f0, int64_t f1) {
         for (int64_t f = f0; f < f1; f += SB) {
             const int cnt = (int)min((int64_t)SB, f1 - f);
-            for (int u = 0; u < cnt; ++u) *reinterpret_cast<V*>(&sm.ys[ph][u][slot]) = direct(f + u);
+            for (int u = 0; u < cnt; ++u) *reinterpret_cast<V*>(&sm.ys[ph][u][slot]) = fold_value<VEC, QM>(direct(f + u));
             flush(f, cnt);
         }
     };
@@ -191,7 +205,7 @@ __device__ __forceinline__ void fir_fold_unit(const FirArgs& a, int TF, int64_t 
                 const int u = sb + i;
                 if (u >= MT) continue;
                 win[u] = in[i];
-                *reinterpret_cast<V*>(&sm.ys[ph][i][slot]) = fir_point<VEC, MT, EXACT>(tp, win, u, M);
+                *reinterpret_cast<V*>(&sm.ys[ph][i][slot]) = fold_value<VEC, QM>(fir_point<VEC, MT, EXACT>(tp, win, u, M));
             }
             flush(fb + sb, MT - sb < SB ? MT - sb : SB);
         }
@@ -294,6 +308,8 @@ hipError_t launch_fold_batch_qm(const BatchTable* t, int max_m, int grid, hipStr
 hipError_t launch_fold_f32(const FirArgs& a, hipStream_t s);
 hipError_t launch_fold_bf16(const FirArgs& a, hipStream_t s);
 hipError_t launch_fold_bf16x2(const FirArgs& a, hipStream_t s);
+hipError_t launch_fold_f8bf16(const FirArgs& a, hipStream_t s);
+hipError_t launch_fold_batch_f8bf16(const BatchTable* t, int max_m, int grid, hipStream_t s);
 hipError_t launch_fold_batch_f32(const BatchTable* t, int max_m, int grid, hipStream_t s);
 hipError_t launch_fold_batch_bf16(const BatchTable* t, int max_m, int grid, hipStream_t s);
 hipError_t launch_fold_batch_bf16x2(const BatchTable* t, int max_m, int grid, hipStream_t s);

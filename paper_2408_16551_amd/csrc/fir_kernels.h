@@ -23,7 +23,8 @@ enum FirOut : int {
 // the frame's scale 2^-fexp[f] applied: FP8 E4M3 (saturated at 448), fp16,
 // fp16 hi + lo (lo = RNE((x - hi) 2^11)); or only the partial maxima.
 enum QMode : int {
-    QM_NONE = 0, QM_MX = 1, QM_BF16 = 2, QM_BF16X2 = 3, QM_FP8F = 4, QM_FP16F = 5, QM_FP16FX2 = 6, QM_AMAXONLY = 7
+    QM_NONE = 0, QM_MX = 1, QM_BF16 = 2, QM_BF16X2 = 3, QM_FP8F = 4, QM_FP16F = 5, QM_FP16FX2 = 6, QM_AMAXONLY = 7,
+    QM_F8BF16 = 8  // folded FIR only: values rounded to E4M3's 4 significant bits, their folded sums in bf16
 };
 constexpr int mode_qm(int mode) {
     return mode == FIR_OUT_MX ? QM_MX

@@ -120,7 +120,13 @@ hipError_t launch_dft_gemm(const GemmArgs& a, hipStream_t s);
 // From 256 channels, in the forms whose operand element needs no frame or
 // block scale.  Fewer channels: the column groups are narrower than a wave,
 // and the dense product is no longer what bounds a call.
-inline bool fold_form(int form) { return form == FORM_FP32 || form == FORM_BF16 || form == FORM_BF16X3; }
+inline bool fold_form(int form) {
+    return form == FORM_FP32 || form == FORM_BF16 || form == FORM_BF16X3 || form == FORM_FP8;
+}
+// Operand form of the folded product.  Per-frame FP8: sums of four E4M3 values
+// (whose powers of two need no common frame scale any more) and the
+// coefficients in bf16, a rounding an eighth of E4M3's.
+inline int fold_operand_form(int form) { return form == FORM_FP8 ? FORM_BF16 : form; }
 inline bool fold_supported(int P, int form) { return P >= 256 && fold_form(form); }
 // The FIR with folded output (a.y, or a.q / a.q1 with a.qmode; ldy, ldq unused).
 hipError_t launch_fir_fold(const FirArgs& a, hipStream_t s);
@@ -240,6 +246,8 @@ inline int form_fir_qmode(int form) {
         default: return 0;
     }
 }
+// ... and the folded FIR: as above, FP8 rounded to E4M3's 4 significant bits before folding, then bf16.
+inline int fold_fir_qmode(int form) { return form == FORM_FP8 ? 8 : form_fir_qmode(form); }
 // qmode values whose codes carry a per-frame scale.
 inline bool qmode_frame_scaled(int qm) { return qm >= 4 && qm <= 6; }
 

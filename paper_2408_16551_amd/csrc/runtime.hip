@@ -153,14 +153,14 @@ tina_status tina_pfb_plan(const tina_pfb_desc* d, tina_pfb_plan_t* out) {
             p->K = p->P;
             p->N = p->P / 4;
             const bool table = p->dft_algorithm == TINA_DFT_TABLE;
-            const int64_t nbytes = (int64_t)p->N * p->K * form_elem_bytes(form);
-            for (int i = 0; i < form_pieces(form) && !table; ++i)
+            const int64_t nbytes = (int64_t)p->N * p->K * form_elem_bytes(fold_operand_form(form));
+            for (int i = 0; i < form_pieces(fold_operand_form(form)) && !table; ++i)
                 if (hipMalloc(&p->B[i], nbytes) != hipSuccess) return bail(TINA_ERR_OUT_OF_MEMORY, "plan: DFT operand allocation");
             if (hipMalloc(&p->fold_tw, sizeof(float) * p->P) != hipSuccess ||
                 (table && hipMalloc(&p->fold_ct, sizeof(float) * 2 * p->P) != hipSuccess))
                 return bail(TINA_ERR_OUT_OF_MEMORY, "plan: twiddle table");
             e = launch_fold_tables(p->fold_tw, p->fold_ct, nullptr, p->P, 1.0f, nullptr);
-            if (e == hipSuccess && !table) e = launch_fold_operand(p->B[0], p->B[1], p->P, form, nullptr);
+            if (e == hipSuccess && !table) e = launch_fold_operand(p->B[0], p->B[1], p->P, fold_operand_form(form), nullptr);
         } else if (p->dft_algorithm == TINA_DFT_FACTORED || p->dft_algorithm == TINA_DFT_TABLE) {  // P twiddles alone
             if (hipMalloc(&p->fft_tw, sizeof(float) * 2 * p->P) != hipSuccess)
                 return bail(TINA_ERR_OUT_OF_MEMORY, "plan: twiddle table");
@@ -327,7 +327,7 @@ tina_status execute_with(tina_pfb_plan_s* p, const void* d_in, int64_t n, void* 
             // E4M3 codes (then the block scales), or the 16-bit piece(s) one
             // after the other; per-frame scaled forms also keep the frames'
             // exponents beside their partial maxima.
-            fa.qmode = form_fir_qmode(form);
+            fa.qmode = p->fold ? fold_fir_qmode(form) : form_fir_qmode(form);
             if (fa.qmode != 0) {
                 fa.y = nullptr;
                 fa.q = (uint8_t*)w.ws;
@@ -363,7 +363,7 @@ tina_status execute_with(tina_pfb_plan_s* p, const void* d_in, int64_t n, void* 
             ga.K = p->K;
             ga.N = p->N;
             ga.real_pack = p->cf == 1;
-            ga.form = form;
+            ga.form = p->fold ? fold_operand_form(form) : form;
             ga.Aq = fa.q;
             ga.Aq1 = fa.q1;
             ga.Aqs = fa.qs;

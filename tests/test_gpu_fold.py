@@ -1,15 +1,16 @@
-"""GPU: the folded dense product (256 channels and more; FP32, BF16, BF16x3)
+"""GPU: the folded dense product (256 channels and more; FP32, BF16, BF16x3, FP8)
 against the FP64 oracle at the edges of its tiles (64 and 128 rows, a row being
 a real frame or half a complex one), of the tap rings and of the channel range,
 and its kernels against each other bit for bit.
 
 Bounds: those of the forms at every size (unit roundoff times the operand and
-product roundings; FP32 1e-5 as required)."""
+product roundings; FP32 1e-5 as required; FP8 half an E4M3 step, 2^-4 / sqrt 12
+= 0.018 to 0.036 over a binade, 0.024 on average)."""
 import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
-BOUND = {"fp32": 1e-5, "bf16": 8e-3, "bf16x3": 1e-5}
+BOUND = {"fp32": 1e-5, "bf16": 8e-3, "bf16x3": 1e-5, "fp8": 0.03}
 
 
 def rel_l2(got, ref):
@@ -35,7 +36,7 @@ def _run(plan, x, state=None):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("prec", ["fp32", "bf16", "bf16x3"])
+@pytest.mark.parametrize("prec", list(BOUND))
 @pytest.mark.parametrize("P,M,cplx,F", [
     (256, 1, False, 1), (256, 5, True, 33), (256, 16, False, 129), (512, 9, True, 65), (512, 17, False, 64),
     (1024, 8, True, 31), (1024, 12, False, 200), (2048, 33, True, 18), (4096, 8, False, 70), (8192, 3, True, 9),
@@ -51,7 +52,7 @@ def test_folded_product_matches_oracle(oracle, P, M, cplx, F, prec):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("prec", ["fp32", "bf16", "bf16x3"])
+@pytest.mark.parametrize("prec", list(BOUND))
 @pytest.mark.parametrize("P,M,cplx,F", [(256, 4, True, 9000), (1024, 16, False, 9001), (4096, 8, True, 1030)])
 def test_short_and_long_calls_agree_bitwise(P, M, cplx, F, prec):
     """A long call (128-row tiles), a short one (64-row tiles, a wave a part),
@@ -76,7 +77,7 @@ def test_short_and_long_calls_agree_bitwise(P, M, cplx, F, prec):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("prec", ["fp32", "bf16x3"])
+@pytest.mark.parametrize("prec", ["fp32", "bf16x3", "fp8"])
 def test_batch_mixes_folded_and_unfolded_items_bitwise(prec):
     from paper_2408_16551_amd.pfb import Batch
     items, want = [], []
