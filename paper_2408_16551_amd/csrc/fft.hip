@@ -195,6 +195,11 @@ __global__ __launch_bounds__(256) void fft_kernel(const FA fa, const float* __re
 #pragma unroll
             for (int r = 1; r < R3; ++r) w3[b][r - 1] = w((t + b * T) * r * S);
     }
+    cf32 wu[CPLX ? 1 : 8];  // untangling
+    if constexpr (!CPLX) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) wu[i] = w(t + i * T);
+    }
     const int64_t step = (int64_t)gridDim.x * G::FPB;
     for (int64_t fb = (int64_t)blockIdx.x * G::FPB; fb < fa.F; fb += step) {  // the same turns for the whole block
         const int64_t f = fb + g;
@@ -267,7 +272,7 @@ __global__ __launch_bounds__(256) void fft_kernel(const FA fa, const float* __re
                     const int k = t + i * T;
                     const cf32 a = buf[pad16(k)], c = buf[pad16((N - k) & (N - 1))];
                     const cf32 e = {0.5f * (a.x + c.x), 0.5f * (a.y - c.y)}, d = {0.5f * (a.x - c.x), 0.5f * (a.y + c.y)};
-                    const cf32 wo = mul(mul_mi(d), w(k));
+                    const cf32 wo = mul(mul_mi(d), wu[i]);
                     if (k == 0) {
                         o[0] = {a.x + a.y, 0.0f};
                         o[N] = {a.x - a.y, 0.0f};

@@ -443,14 +443,16 @@ __device__ __forceinline__ void fir_unit(const FirArgs& a, int TF, int64_t blk) 
     };
 
     // Full blocks of MT frames, loaded SB frames at a time: the SB loads of a
-    // sub-block issue before its first FMA.  When a wave's lanes all work on
-    // the same frames (ct >= 64) and the block's first frame row lies in the
-    // chunk (so the whole block does), loads and stores go through buffer
-    // resources based at the block (BufSink) and the ring carries the input
-    // frames from block to block.  Other blocks go through pointers, choosing
-    // between prefix and chunk per load.  The choice is uniform over a frame
-    // row, so the lanes that share a block maximum of the block-scaled output
-    // take the same path.
+    // sub-block issue before its first FMA.  When the first frame row of every
+    // lane's block lies in the chunk (so the whole blocks do), loads and stores
+    // go through buffer resources based at the block of the wave's first lane
+    // (BufSink), the one of its earliest run, and the ring carries the input
+    // frames from block to block.  A wave holds one run of frames, or 64 / ct of
+    // them where a row is narrower than a wave (16 to 32 channels ran 2.5 to 7
+    // times as long while those took the other path).  Other blocks go through
+    // pointers, choosing between prefix and chunk per load.  The choice is
+    // uniform over the wave's active lanes, so the lanes that share a block
+    // maximum of the block-scaled output take the same path.
     constexpr int SB = (VEC == 4 ? 8 : 16) < MT ? (VEC == 4 ? 8 : 16) : MT;
     const int64_t nsc = a.W / 32;
     constexpr int QB = qm_bytes(QM);  // bytes per operand element
@@ -469,13 +471,14 @@ __device__ __forceinline__ void fir_unit(const FirArgs& a, int TF, int64_t blk) 
     int64_t fb = f_begin;
     for (; fb + MT <= f_end; fb += MT) {
         const int64_t e_row = (a.g0 + fb + a.M - 1) * (int64_t)a.W - a.plen;  // block's first float in the chunk
-        if (ct >= 64 && e_row >= 0) {
+        if (ct >= 64 ? e_row >= 0 : (bool)__all(e_row >= 0)) {
             if (!ring_ok) load_ring(fb);
             ring_ok = true;
             const int64_t fu = (int64_t)uniform64((uint64_t)fb);
+            const uint32_t ahead = ct >= 64 ? 0u : (uint32_t)(fb - fu);  // frames from the first lane's block to this one's
             const int64_t eu = (a.g0 + fu + a.M - 1) * (int64_t)a.W - a.plen;
             const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.chunk + eu, (a.nchunk - eu) * 4);
-            const uint32_t vin = (uint32_t)j0 * 4u;
+            const uint32_t vin = (uint32_t)(j0 + ahead * a.W) * 4u;
             const int32_t w4 = a.W * 4;
             BufSink<VEC, NT> o;
             if constexpr (QM == QM_AMAXONLY) {
@@ -484,13 +487,13 @@ __device__ __forceinline__ void fir_unit(const FirArgs& a, int TF, int64_t blk) 
                 o.rq[0] = make_rsrc(a.q + fu * a.ldq * QB, (a.F - fu) * a.ldq * QB);
                 if constexpr (qm_two_pieces(QM)) o.rq[1] = make_rsrc(a.q1 + fu * a.ldq * QB, (a.F - fu) * a.ldq * QB);
                 if constexpr (QM == QM_MX) o.rs = make_rsrc(a.qs + fu * nsc, (a.F - fu) * nsc);
-                o.vq = (uint32_t)(j0 * QB);
-                o.vs = (uint32_t)(j0 / 32);
+                o.vq = (uint32_t)((j0 + ahead * a.ldq) * QB);
+                o.vs = (uint32_t)(j0 / 32 + ahead * nsc);
                 o.ldq = (int32_t)(a.ldq * QB);
                 o.nsc = (int32_t)nsc;
             } else {
                 o.ry = make_rsrc(a.y + fu * a.ldy, (a.F - fu) * a.ldy * 4);
-                o.vy = (uint32_t)j0 * 4u;
+                o.vy = (uint32_t)(j0 + ahead * a.ldy) * 4u;
                 o.ldy4 = (int32_t)(a.ldy * 4);
             }
 #pragma unroll
@@ -562,6 +565,8 @@ hipError_t launch_one(FirArgs& a, hipStream_t s) {
     // A multiple of MT, so that every run is whole ring blocks (tap counts
     // that are not powers of two included).
     int TF = 2 * MT < 16 ? ((16 + MT - 1) / MT) * MT : 2 * MT;
+    // Short calls: fewer frames per thread while that leaves CUs without a block.
+    while (TF > MT && (a.F + TF - 1) / TF * ct < 512 * 256) TF -= MT;
     const FirTune tune = fir_tune();
     if (tune.tf > 0) TF = ((tune.tf + MT - 1) / MT) * MT;
     const int64_t runs = (a.F + TF - 1) / TF;
