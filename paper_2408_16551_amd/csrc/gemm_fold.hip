@@ -303,62 +303,68 @@ __device__ __forceinline__ void fold_tile(const GemmArgs& g, int64_t m0, int64_t
     }
 }
 
-// Few rows: blocks of 64 rows x 32 columns, one wave per part, so that a short
-// call still spreads over the chip (a wave of the large tile does four times
-// as much).  Operand rows go from memory straight to the MFMA registers; the
-// four parts meet in LDS.  Same K order, same bits as fold_tile.
-template <int FORM, bool CPLX>
+// Few rows: blocks of 32 TM rows x 32 columns (complex frames: TM = 2), one wave
+// per part, so that a short call still spreads over the chip (a
+// wave of the large tile does four to eight times as much).  Operand rows go
+// from memory straight to the MFMA registers, U slabs ahead: what bounds a short
+// call is how often it waits for memory.  The four parts meet in LDS.  Same K
+// order, same bits as fold_tile.
+template <int FORM, bool CPLX, int TM>
 __device__ __forceinline__ void fold_tile_small(const GemmArgs& g, int64_t m0, int64_t n0, float* ex) {
-    constexpr int NP = FF<FORM>::NP, EB = FF<FORM>::EB, U = 4;  // slabs in flight
+    constexpr int NP = FF<FORM>::NP, EB = FF<FORM>::EB, ROWS = 32 * TM;
+    constexpr int U = TM == 1 && NP == 1 ? 8 : 4;  // (with two row blocks the registers cost more waves than 8 gain)
     const int lane = threadIdx.x & 63, s = threadIdx.x >> 6, lr = lane & 31, lh = lane >> 5;
     const int P = g.K, Q = g.N;
     const int64_t R = g.F * (CPLX ? 2 : 1), pitch = (int64_t)P * EB;
     const uint8_t* Ap[2] = {FORM == FORM_FP32 ? (const uint8_t*)g.A : g.Aq, g.Aq1};
     const uint8_t* Bp[2] = {(const uint8_t*)g.B0, (const uint8_t*)g.B1};
     const int part0 = s * Q * EB + lh * 16;
-    int64_t ao[2];
+    int64_t ao[TM];
 #pragma unroll
-    for (int bm = 0; bm < 2; ++bm) {
-        int64_t row = m0 + (CPLX ? 2 * lr + bm : 32 * bm + lr);
+    for (int bm = 0; bm < TM; ++bm) {
+        const int64_t row = m0 + (CPLX ? 2 * lr + bm : 32 * bm + lr);
         ao[bm] = (row < R ? row : R - 1) * pitch + part0;  // rows past the end: read, never written
     }
     const int64_t bo = (n0 + lr) * pitch + part0;  // Q is a multiple of 32
-    f32x16 acc[2], ts[2];
+    f32x16 acc[TM], ts[TM];
     zero(acc);
-    static_assert(!kTileSums<FORM> || U * SLAB == 128, "one K tile per round");
-    const int ns = Q * EB / SLAB;  // a multiple of U
-    uint4 a[U][2][NP], b[U][NP];
+    const int ns = Q * EB / SLAB;  // 4 or a multiple of U
+    uint4 a[U][TM][NP], b[U][NP];
     auto load = [&](int u, int sl) {
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
 #pragma unroll
-            for (int bm = 0; bm < 2; ++bm) a[u][bm][p] = *reinterpret_cast<const uint4*>(Ap[p] + ao[bm] + sl * SLAB);
+            for (int bm = 0; bm < TM; ++bm) a[u][bm][p] = *reinterpret_cast<const uint4*>(Ap[p] + ao[bm] + sl * SLAB);
             b[u][p] = *reinterpret_cast<const uint4*>(Bp[p] + bo + sl * SLAB);
         }
     };
 #pragma unroll
-    for (int u = 0; u < U; ++u) load(u, u);
+    for (int u = 0; u < U; ++u) load(u, U <= 4 || u < ns ? u : 0);
     for (int sl = 0; sl < ns; sl += U) {
-        zero(ts);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if constexpr (kTileSums<FORM>) fold_mfma<FORM, NP, 2>(a[u], b[u], ts);
-            else fold_mfma<FORM, NP, 2>(a[u], b[u], acc);
-            load(u, sl + U < ns ? sl + U + u : u);  // past the last: repeats in-range reads
+            if (U > 4 && sl + u >= ns) break;  // 4 slabs in all
+            if constexpr (kTileSums<FORM>) {  // the K tiles of fold_tile: 4 slabs
+                if (u % 4 == 0) zero(ts);
+                fold_mfma<FORM, NP, TM>(a[u], b[u], ts);
+                if (u % 4 == 3) add_to(acc, ts);
+            } else {
+                fold_mfma<FORM, NP, TM>(a[u], b[u], acc);
+            }
+            load(u, sl + U + (U > 4 ? u : 0) < ns ? sl + U + u : u & 3);  // past the last: repeats in-range reads
         }
-        if constexpr (kTileSums<FORM>) add_to(acc, ts);
     }
     // ex[part][row][column], 33 floats a row.
 #pragma unroll
-    for (int bm = 0; bm < 2; ++bm)
+    for (int bm = 0; bm < TM; ++bm)
 #pragma unroll
         for (int v = 0; v < 16; ++v)
-            ex[(s * 64 + bm * 32 + 8 * (v >> 2) + 4 * lh + (v & 3)) * 33 + lr] = acc[bm][v];
+            ex[(s * ROWS + bm * 32 + 8 * (v >> 2) + 4 * lh + (v & 3)) * 33 + lr] = acc[bm][v];
     __syncthreads();
     const int jl = threadIdx.x & 31, j = (int)n0 + jl;
     const float4 w = reinterpret_cast<const float4*>(g.tw)[j];
-    auto at = [&](int part, int row) { return ex[(part * 64 + row) * 33 + jl]; };
-    for (int i = threadIdx.x >> 5; i < (CPLX ? 32 : 64); i += 8) {
+    auto at = [&](int part, int row) { return ex[(part * ROWS + row) * 33 + jl]; };
+    for (int i = threadIdx.x >> 5; i < (CPLX ? 32 : ROWS); i += 8) {
         const int64_t f = m0 / (CPLX ? 2 : 1) + i;
         if (f >= g.F) break;
         float* row = g.out + f * g.ldo;
@@ -393,13 +399,14 @@ void fold_gemm_kernel(GemmArgs g) {
     fold_tile<FORM, CPLX, WGM, WGN, false>(g, m0, n0, lds, nullptr);
 }
 
-template <int FORM, bool CPLX>
+template <int FORM, bool CPLX, int TM>
 __global__ __launch_bounds__(256) void fold_gemm_small_kernel(GemmArgs g) {
-    __shared__ float ex[4 * 64 * 33];
-    const int64_t nm = (g.F * (CPLX ? 2 : 1) + 63) / 64, nn = g.N / 32;
+    constexpr int ROWS = 32 * TM;
+    __shared__ float ex[4 * ROWS * 33];
+    const int64_t nm = (g.F * (CPLX ? 2 : 1) + ROWS - 1) / ROWS, nn = g.N / 32;
     int64_t m0, n0;
-    fold_place(xcd_logical_block(blockIdx.x, gridDim.x), nm, nn, 64, 32, m0, n0);
-    fold_tile_small<FORM, CPLX>(g, m0, n0, ex);
+    fold_place(xcd_logical_block(blockIdx.x, gridDim.x), nm, nn, ROWS, 32, m0, n0);
+    fold_tile_small<FORM, CPLX, TM>(g, m0, n0, ex);
 }
 
 // FP32 with the operand assembled from the 2P-entry cosine table (8 P bytes,
@@ -460,8 +467,18 @@ template <int FORM, bool CPLX>
 hipError_t launch_fold_form(const GemmArgs& g, hipStream_t s) {
     const int64_t R = g.F * (CPLX ? 2 : 1);
     if (R * g.N < 96 * 128 * 128) {
+        // Real frames: 32 rows a block until those are 512 blocks (1024 channels,
+        // FP32: 1024 frames 17 us against 21 us with 64 rows, 4096 frames 49 us
+        // against 35 us).
+        if constexpr (!CPLX) {
+            const int64_t blocks = (R + 31) / 32 * (g.N / 32);
+            if (blocks <= 512) {
+                hipLaunchKernelGGL((fold_gemm_small_kernel<FORM, CPLX, 1>), dim3((unsigned)blocks), dim3(256), 0, s, g);
+                return hipGetLastError();
+            }
+        }
         const int64_t blocks = (R + 63) / 64 * (g.N / 32);
-        hipLaunchKernelGGL((fold_gemm_small_kernel<FORM, CPLX>), dim3((unsigned)blocks), dim3(256), 0, s, g);
+        hipLaunchKernelGGL((fold_gemm_small_kernel<FORM, CPLX, 2>), dim3((unsigned)blocks), dim3(256), 0, s, g);
         return hipGetLastError();
     }
     if constexpr (FORM == FORM_FP32) return launch_fold_wide<FORM, CPLX, 2, 2>(g, s);
