@@ -114,17 +114,11 @@ struct tina_pfb_batch_s {
     bool frame_stage = true;      // long per-frame scaled items run the single-pass frame stage
     int64_t frame_stage_min = 2048;  // frames an item needs to run the frame stage
     int frame_tf_target = 128;       // frames per frame-stage unit (rounded up to whole ring blocks of M)
-    // Items whose plan takes the factored DFT (FP32): one launch per (P,
-    // input type) over their frames, with the items' FftItem rows stored in
-    // the table buffer after the items (fft_offset).
-    struct FftGroup {
-        int P;
-        bool cplx;
-        int first, count;  // rows [first, first + count) of the table's FftItem array
-        int64_t F;         // frames of the group's items
-        const float* tw;
-    };
-    std::vector<FftGroup> fft_groups;
+    // Items whose plan takes the factored DFT (FP32): one launch over their
+    // frames, with the items' FftItem rows stored in the table buffer after the
+    // items (fft_offset).
+    int fft_n = 0;          // rows
+    int64_t fft_units = 0;  // units of the launch
     bool one_stream = false;      // every call comes on one stream: no order event is recorded
     StreamOrder order;            // every call shares ws, amax, fexp and d_table
 
@@ -247,8 +241,14 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
     // Frames per FIR thread, a whole number of the unit's ring blocks: the
     // ring is MT frames long, or the item's own M when mixed tap counts up to
     // 16 run per-M units.
+    // Half of the tuned number where its units would be fewer than two per block
+    // of the persistent grid: a short step lasts as long as its last unit.
+    int64_t all_floats = 0;
+    for (int i = 0; i < g.count; ++i) all_floats += frames[g.first + i] * w[g.first + i].plan->W;
     auto frames_per_thread = [&](int ring) {
-        return tune.fir_tf_mult * ring < 16 ? ((16 + ring - 1) / ring) * ring : tune.fir_tf_mult * ring;
+        int tf = tune.fir_tf_mult * ring < 16 ? ((16 + ring - 1) / ring) * ring : tune.fir_tf_mult * ring;
+        while (tf > ring && all_floats / (256 * (int64_t)tf) < 8 * (int64_t)b->cus) tf -= ring;
+        return tf;
     };
 
     std::vector<int64_t> fu(g.count), gu(g.count), su(g.count), ru(g.count), ffu(g.count), gfu(g.count);
@@ -378,37 +378,40 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
         }
         s0 += su[i];
     }
-    // Factored-DFT rows, grouped by (P, input type) in item order; a group's
-    // rows number its frames one item after the other.
-    b->fft_groups.clear();
+    // Factored-DFT rows, the longest frames first.  A unit is one block's
+    // frames while that leaves blocks idle, and up to 8 times that: a unit
+    // loads its twiddles once.
     std::stable_sort(fft_items.begin(), fft_items.end(), [&](int x, int y) {
-        const tina_pfb_plan_s *px = w[g.first + x].plan, *py = w[g.first + y].plan;
-        return px->P != py->P ? px->P < py->P : px->cf < py->cf;
+        return w[g.first + x].plan->W > w[g.first + y].plan->W;
     });
+    int64_t all_turns = 0;
+    auto turns_of = [&](int i) {
+        const tina_pfb_plan_s* p = w[g.first + i].plan;
+        const int64_t fpb = fft_frames_per_block(p->P, p->cf == 2);
+        return (t->items[i].gemm.F + fpb - 1) / fpb;
+    };
+    for (int i : fft_items) all_turns += turns_of(i);
+    const int64_t per_unit = std::max<int64_t>(1, std::min<int64_t>(8, all_turns / (8 * (int64_t)b->cus)));
     FftItem* rows = fft_rows(t, g.count);
+    b->fft_n = (int)fft_items.size();
+    b->fft_units = 0;
     for (size_t k = 0; k < fft_items.size(); ++k) {
         const int i = fft_items[k];
         const tina_pfb_plan_s* p = w[g.first + i].plan;
         const BatchItem& bi = t->items[i];
-        if (b->fft_groups.empty() || b->fft_groups.back().P != p->P || b->fft_groups.back().cplx != (p->cf == 2)) {
-            tina_pfb_batch_s::FftGroup fg;
-            fg.P = p->P;
-            fg.cplx = p->cf == 2;
-            fg.first = (int)k;
-            fg.count = 0;
-            fg.F = 0;
-            fg.tw = p->fft_tw;
-            b->fft_groups.push_back(fg);
-        }
-        tina_pfb_batch_s::FftGroup& fg = b->fft_groups.back();
         FftItem& r = rows[k];
         r.y = bi.fir.y;
         r.out = bi.gemm.out;
+        r.tw = p->fft_tw;
         r.ldy = bi.fir.ldy;
         r.ldo = bi.gemm.ldo;
-        r.f0 = fg.F;
-        fg.F += bi.gemm.F;
-        fg.count += 1;
+        r.F = bi.gemm.F;
+        r.unit0 = b->fft_units;
+        r.P = p->P;
+        r.cplx = p->cf == 2;
+        r.turns = (int32_t)per_unit;
+        r.pad_ = 0;
+        b->fft_units += (turns_of(i) + per_unit - 1) / per_unit;
     }
     t->gemm_bn = tile_n;
     t->gemm_wide = wide ? 1 : 0;
@@ -480,10 +483,8 @@ tina_status launch_stages(tina_pfb_batch_s* b, hipStream_t s, const Tune& tune, 
     if (stages & STAGE_FOLD) HIP_TRY(launch_fold_gemm_batch(b->d_table, fold_operand_form(b->form), (int)grid_fold, s));
     if ((stages & STAGE_DENSE) && (always || b->h_table->gemm_units > 0))
         HIP_TRY(launch_gemm_batch(b->d_table, b->form, qmode != 0, tune.gemm_tile_n, (int)grid_gemm, s, wide));
-    if (!always)  // factored-DFT items: never in a captured step (the groups change from call to call)
-        for (const tina_pfb_batch_s::FftGroup& fg : b->fft_groups)
-            HIP_TRY(launch_fft_batch(fft_rows(b->d_table, b->h_table->n_items) + fg.first, fg.count, fg.F, fg.P,
-                                     fg.cplx, fg.tw, b->cus, s));
+    if (!always)  // factored-DFT items: never in a captured step (their rows change from call to call)
+        HIP_TRY(launch_fft_batch(fft_rows(b->d_table, b->h_table->n_items), b->fft_n, b->fft_units, b->cus, s));
     if (stages & STAGE_STATE) HIP_TRY(launch_gather_batch(b->d_table, b->cus * 2, s));
     return TINA_OK;
 }
@@ -562,16 +563,14 @@ tina_status run_batch(tina_pfb_batch_s* b, tina_pfb_work* w, int32_t n, hipStrea
         bool all_exact = true, wide = false;
         fill_table(b, w, frames, g, tune, dry, max_m, all_exact, wide);
         const int stages = table_stages(b->h_table);
-        int n_fft = 0;
-        for (const tina_pfb_batch_s::FftGroup& fg : b->fft_groups) n_fft += fg.count;
-        HIP_TRY(hipMemcpyAsync(b->d_table, b->h_table, upload_size(g.count, n_fft), hipMemcpyHostToDevice, s));
+        HIP_TRY(hipMemcpyAsync(b->d_table, b->h_table, upload_size(g.count, b->fft_n), hipMemcpyHostToDevice, s));
         if (!tables_retired || groups.size() > 1) {
             HIP_TRY(hipEventRecord(b->table_free[k], s));
             b->table_pending[k] = true;
         }
         tina_pfb_batch_s::StepGraph* sg = nullptr;
         if (use_graph && b->graph_gemm_grid > 0 && gemm_grid(b->h_table) <= b->graph_gemm_grid &&
-            fold_grid(b->h_table) <= b->graph_fold_grid && b->fft_groups.empty()) {
+            fold_grid(b->h_table) <= b->graph_fold_grid && b->fft_n == 0) {
             tina_status st = step_graph(b, s, tune, max_m, all_exact, wide, stages, sg);
             if (st != TINA_OK) return st;
             for (int m = 0; m < 2; ++m) {  // this step's GEMM grids: blocks past the tiles' ranges would only return

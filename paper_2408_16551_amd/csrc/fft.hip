@@ -19,6 +19,8 @@
 // of the peak).
 #include <math.h>
 
+#include <type_traits>
+
 #include "internal.h"
 
 namespace tina {
@@ -113,39 +115,6 @@ __global__ void fft_twiddle_kernel(float* tw, int P) {
     tw[2 * r + 1] = __double2float_rn(s);
 }
 
-// Where frame f of a launch lives.  OneChunk: the frames of one call (rows
-// of y and out).  ItemFrames: the frames of several batch items with the
-// same P, one after the other (item i owns launch frames [f0_i, f0_i + F_i));
-// each frame is found by a binary search over the items' first frames.  The
-// arithmetic per frame is the same for both, so a batched item's output is
-// bit for bit that of its own call.
-struct OneChunk {
-    const float* y;
-    int64_t ldy;
-    float* out;
-    int64_t ldo, F;
-    __device__ void rows(int64_t f, const float*& yr, float*& orow) const {
-        yr = y + f * ldy;
-        orow = out + f * ldo;
-    }
-};
-struct ItemFrames {
-    const FftItem* it;
-    int n;
-    int64_t F;
-    __device__ void rows(int64_t f, const float*& yr, float*& orow) const {
-        int lo = 0, hi = n - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (it[mid].f0 <= f) lo = mid;
-            else hi = mid - 1;
-        }
-        const FftItem& x = it[lo];
-        yr = x.y + (f - x.f0) * x.ldy;
-        orow = x.out + (f - x.f0) * x.ldo;
-    }
-};
-
 template <int N, bool CPLX>
 struct FftGeom {
     static constexpr int P = CPLX ? N : 2 * N;
@@ -170,14 +139,20 @@ __device__ __forceinline__ void frame_sync() {
     }
 }
 
-template <int N, bool CPLX, class FA>
-__global__ __launch_bounds__(256) void fft_kernel(const FA fa, const float* __restrict__ twf) {
+constexpr int kFftLds = 256 * 17;  // points: FPB * ROW of every N
+
+// Frames f0 + g, f0 + g + step, ... below F of y and out (g < FPB: the thread's
+// place in the block), by every thread of the block.
+template <int N, bool CPLX>
+__device__ __forceinline__ void fft_frames(const float* __restrict__ y, int64_t ldy, float* __restrict__ out, int64_t ldo,
+                                           int64_t f0, int64_t F, int64_t step, const float* __restrict__ twf, cf32* lds,
+                                           int tid) {
     using G = FftGeom<N, CPLX>;
     constexpr int T = G::T, R2 = G::R2, R3 = G::R3;
     constexpr int B2 = 16 / R2, B3 = R3 > 1 ? 16 / R3 : 1;  // butterflies per thread
-    __shared__ __attribute__((aligned(16))) cf32 lds[G::FPB * G::ROW];
+    static_assert(G::FPB * G::ROW == kFftLds, "every N fills the same LDS");
     const cf32* tw = reinterpret_cast<const cf32*>(twf);
-    const int t = threadIdx.x % T, g = threadIdx.x / T;
+    const int t = tid % T, g = tid / T;
     cf32* buf = lds + g * G::ROW;
     constexpr int S = G::P / N;  // W_N^x = table entry S x
     auto w = [&](int x) {
@@ -200,16 +175,13 @@ __global__ __launch_bounds__(256) void fft_kernel(const FA fa, const float* __re
 #pragma unroll
         for (int i = 0; i < 8; ++i) wu[i] = w(t + i * T);
     }
-    const int64_t step = (int64_t)gridDim.x * G::FPB;
-    for (int64_t fb = (int64_t)blockIdx.x * G::FPB; fb < fa.F; fb += step) {  // the same turns for the whole block
+    for (int64_t fb = f0; fb < F; fb += step) {  // the same turns for the whole block
         const int64_t f = fb + g;
-        const bool on = f < fa.F;
-        const float* yr = nullptr;
-        float* orow = nullptr;
+        const bool on = f < F;
+        float* const orow = out + f * ldo;
         cf32 v[16];
         if (on) {
-            fa.rows(f, yr, orow);
-            const cf32* z = reinterpret_cast<const cf32*>(yr);
+            const cf32* z = reinterpret_cast<const cf32*>(y + f * ldy);
 #pragma unroll
             for (int r = 0; r < 16; ++r) v[r] = z[t + r * T];
         } else {
@@ -289,26 +261,63 @@ __global__ __launch_bounds__(256) void fft_kernel(const FA fa, const float* __re
     }
 }
 
-template <int N, bool CPLX, class FA>
-hipError_t launch_fft_n(const FA& fa, const float* tw, int cus, hipStream_t s) {
-    using G = FftGeom<N, CPLX>;
-    const int64_t turns = (fa.F + G::FPB - 1) / G::FPB;
-    const int64_t grid = turns < 4 * (int64_t)cus ? turns : 4 * (int64_t)cus;  // four blocks per CU (34 KiB of LDS each)
-    hipLaunchKernelGGL((fft_kernel<N, CPLX, FA>), dim3((unsigned)grid), dim3(256), 0, s, fa, tw);
-    return hipGetLastError();
+template <int N, bool CPLX>
+__global__ __launch_bounds__(256) void fft_kernel(FftArgs a) {
+    __shared__ __attribute__((aligned(16))) cf32 lds[kFftLds];
+    constexpr int64_t FPB = FftGeom<N, CPLX>::FPB;
+    fft_frames<N, CPLX>(a.y, a.ldy, a.out, a.ldo, blockIdx.x * FPB, a.F, gridDim.x * FPB, a.tw, lds, threadIdx.x);
 }
 
-template <class FA>
-hipError_t launch_fft_any(const FA& fa, int P, bool cplx, const float* tw, int cus, hipStream_t s) {
-    if (fa.F <= 0) return hipSuccess;
-    switch (P) {
-        case 256: return cplx ? launch_fft_n<256, true>(fa, tw, cus, s) : launch_fft_n<128, false>(fa, tw, cus, s);
-        case 512: return cplx ? launch_fft_n<512, true>(fa, tw, cus, s) : launch_fft_n<256, false>(fa, tw, cus, s);
-        case 1024: return cplx ? launch_fft_n<1024, true>(fa, tw, cus, s) : launch_fft_n<512, false>(fa, tw, cus, s);
-        case 2048: return cplx ? launch_fft_n<2048, true>(fa, tw, cus, s) : launch_fft_n<1024, false>(fa, tw, cus, s);
-        case 4096: return cplx ? launch_fft_n<4096, true>(fa, tw, cus, s) : launch_fft_n<2048, false>(fa, tw, cus, s);
-        default: return hipErrorInvalidValue;
+// The frames of several batch items in one launch, whatever their channel
+// counts (one launch per count took 7-16 us each in a server's steps, most of
+// it latency): a unit is `turns` times as many frames of one item as a block
+// holds.  The arithmetic of a frame is fft_kernel's: a batched item's output is
+// bit for bit that of its own call.
+__global__ __launch_bounds__(256) void fft_batch_kernel(const FftItem* __restrict__ items, int n, int64_t units) {
+    __shared__ __attribute__((aligned(16))) cf32 lds[kFftLds];
+    for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
+        int lo = 0, hi = n - 1;
+        while (lo < hi) {  // the last item whose first unit is <= u
+            const int mid = (lo + hi + 1) >> 1;
+            if (items[mid].unit0 <= u) lo = mid;
+            else hi = mid - 1;
+        }
+        const FftItem it = items[lo];
+        // A thread index the compiler cannot see through, so that it does not move
+        // the address arithmetic of all ten cases out of the loop (512 registers).
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        auto go = [&](auto n_tag, auto c_tag) {
+            constexpr int N = decltype(n_tag)::value;
+            constexpr bool CPLX = decltype(c_tag)::value;
+            constexpr int64_t FPB = FftGeom<N, CPLX>::FPB;
+            const int64_t f0 = (u - it.unit0) * it.turns * FPB, f1 = min(it.F, f0 + it.turns * FPB);
+            fft_frames<N, CPLX>(it.y, it.ldy, it.out, it.ldo, f0, f1, FPB, it.tw, lds, tid);
+        };
+        __syncthreads();  // the previous unit's reads of LDS are done (its frames may have lain in single waves)
+        using std::integral_constant;
+        switch (it.cplx ? it.P : -it.P) {
+            case 256: go(integral_constant<int, 256>{}, std::true_type{}); break;
+            case 512: go(integral_constant<int, 512>{}, std::true_type{}); break;
+            case 1024: go(integral_constant<int, 1024>{}, std::true_type{}); break;
+            case 2048: go(integral_constant<int, 2048>{}, std::true_type{}); break;
+            case 4096: go(integral_constant<int, 4096>{}, std::true_type{}); break;
+            case -256: go(integral_constant<int, 128>{}, std::false_type{}); break;
+            case -512: go(integral_constant<int, 256>{}, std::false_type{}); break;
+            case -1024: go(integral_constant<int, 512>{}, std::false_type{}); break;
+            case -2048: go(integral_constant<int, 1024>{}, std::false_type{}); break;
+            default: go(integral_constant<int, 2048>{}, std::false_type{}); break;
+        }
     }
+}
+
+template <int N, bool CPLX>
+hipError_t launch_fft_n(const FftArgs& a, hipStream_t s) {
+    constexpr int64_t FPB = FftGeom<N, CPLX>::FPB;
+    const int64_t turns = (a.F + FPB - 1) / FPB;
+    const int64_t grid = turns < 4 * (int64_t)a.cus ? turns : 4 * (int64_t)a.cus;  // four blocks per CU (34 KiB of LDS each)
+    hipLaunchKernelGGL((fft_kernel<N, CPLX>), dim3((unsigned)grid), dim3(256), 0, s, a);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -320,15 +329,25 @@ hipError_t launch_twiddle_table(float* tw, int P, hipStream_t s) {
     return hipGetLastError();
 }
 
+int fft_frames_per_block(int P, bool cplx) { return 4096 / (cplx ? P : P / 2); }
+
 hipError_t launch_fft_dft(const FftArgs& a, hipStream_t s) {
-    const OneChunk fa{a.y, a.ldy, a.out, a.ldo, a.F};
-    return launch_fft_any(fa, a.P, a.cplx != 0, a.tw, a.cus, s);
+    if (a.F <= 0) return hipSuccess;
+    switch (a.P) {
+        case 256: return a.cplx ? launch_fft_n<256, true>(a, s) : launch_fft_n<128, false>(a, s);
+        case 512: return a.cplx ? launch_fft_n<512, true>(a, s) : launch_fft_n<256, false>(a, s);
+        case 1024: return a.cplx ? launch_fft_n<1024, true>(a, s) : launch_fft_n<512, false>(a, s);
+        case 2048: return a.cplx ? launch_fft_n<2048, true>(a, s) : launch_fft_n<1024, false>(a, s);
+        case 4096: return a.cplx ? launch_fft_n<4096, true>(a, s) : launch_fft_n<2048, false>(a, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 
-hipError_t launch_fft_batch(const FftItem* items, int n, int64_t F, int P, bool cplx, const float* tw, int cus,
-                            hipStream_t s) {
-    const ItemFrames fa{items, n, F};
-    return launch_fft_any(fa, P, cplx, tw, cus, s);
+hipError_t launch_fft_batch(const FftItem* items, int n, int64_t units, int cus, hipStream_t s) {
+    if (units <= 0) return hipSuccess;
+    const int64_t grid = units < 4 * (int64_t)cus ? units : 4 * (int64_t)cus;
+    hipLaunchKernelGGL(fft_batch_kernel, dim3((unsigned)grid), dim3(256), 0, s, items, n, units);
+    return hipGetLastError();
 }
 
 }  // namespace tina

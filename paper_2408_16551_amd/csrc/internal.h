@@ -160,17 +160,19 @@ bool fft_supported(int P);
 // tw (P x 2): cos, sin of 2 pi r / P in FP64, rounded to FP32.
 hipError_t launch_twiddle_table(float* tw, int P, hipStream_t s);
 hipError_t launch_fft_dft(const FftArgs& a, hipStream_t s);
+// Frames a 256-thread block of the factored DFT holds at a time.
+int fft_frames_per_block(int P, bool cplx);
 // One batch item's frames in a batched factored-DFT launch (device array,
-// sorted by f0): FIR output rows y, output rows out, and the item's first
-// frame among the launch's frames.
+// sorted by unit0): FIR output rows y, output rows out, twiddles tw, and the
+// item's first unit of `turns` blocks' frames.
 struct FftItem {
     const float* y;
     float* out;
-    int64_t ldy, ldo, f0;
+    const float* tw;
+    int64_t ldy, ldo, F, unit0;
+    int32_t P, cplx, turns, pad_;
 };
-// Every frame of n items with the same P and input type (F frames in all).
-hipError_t launch_fft_batch(const FftItem* items, int n, int64_t F, int P, bool cplx, const float* tw, int cus,
-                            hipStream_t s);
+hipError_t launch_fft_batch(const FftItem* items, int n, int64_t units, int cus, hipStream_t s);
 
 // --------------------------------------------------------------- batched path
 // One item of a batched launch: the FIR and GEMM arguments of one stream
