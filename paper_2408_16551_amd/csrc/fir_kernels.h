@@ -293,6 +293,14 @@ __device__ __forceinline__ void fir_amax(const FirArgs& a, const typename VecT<V
     if ((col & (gw - 1)) == 0) a.amax[f * a.nparts + col / gw] = mx;
 }
 
+// What a rounded piece leaves of x, the value the other paths round: not the
+// unrounded product x may come from (one tap), which the compiler would take into
+// a fused multiply-subtract where it can.
+__device__ __forceinline__ float piece_rest(float x, float hi) {
+#pragma clang fp contract(off)
+    return x - hi;
+}
+
 __device__ __forceinline__ uint32_t bf16_bits(float x) { return __builtin_bit_cast(uint16_t, (__bf16)x); }
 
 // Row u of a block in a per-frame scaled operand form, the frame's values
@@ -326,7 +334,7 @@ __device__ __forceinline__ void fir_store_frame(const typename VecT<VEC>::T& acc
             const float x = vget<VEC>(acc, v) * sc;
             const _Float16 h = (_Float16)x;
             hi[v] = __builtin_bit_cast(uint16_t, h);
-            lo[v] = __builtin_bit_cast(uint16_t, (_Float16)((x - (float)h) * 2048.0f));
+            lo[v] = __builtin_bit_cast(uint16_t, (_Float16)(piece_rest(x, (float)h) * 2048.0f));
         }
         auto put = [&](int piece, const uint32_t (&h)[4]) {
             if constexpr (VEC == 4) out.q(piece, u, (uint64_t)(h[0] | (h[1] << 16)) | ((uint64_t)(h[2] | (h[3] << 16)) << 32));
@@ -386,7 +394,7 @@ __device__ __forceinline__ void fir_store(const FirArgs& a, const typename VecT<
         for (int v = 0; v < VEC; ++v) {
             const float x = vget<VEC>(acc, v);
             hi[v] = bf16_bits(x);
-            lo[v] = bf16_bits(x - __builtin_bit_cast(float, hi[v] << 16));
+            lo[v] = bf16_bits(piece_rest(x, __builtin_bit_cast(float, hi[v] << 16)));
         }
         auto put = [&](int piece, const uint32_t (&h)[4]) {
             if constexpr (VEC == 4) out.q(piece, u, (uint64_t)(h[0] | (h[1] << 16)) | ((uint64_t)(h[2] | (h[3] << 16)) << 32));

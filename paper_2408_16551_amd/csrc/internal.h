@@ -146,6 +146,11 @@ __host__ __device__ inline void fold_batch_tile(int form, int64_t N, int64_t& bm
 // Forms whose A the FIR can write in operand form.
 bool gemm_raw_form(int form);
 
+// FIR and dense product in one kernel for frames of at most 128 floats (x.y, x.q
+// and g.A unused); bit for bit the two kernels.
+bool narrow_supported(const FirArgs& x, const GemmArgs& g);
+hipError_t launch_narrow(const FirArgs& x, const GemmArgs& g, hipStream_t s);
+
 // ------------------------------------------------------------- factored DFT
 struct FftArgs {
     const float* y;        // FIR output [F][ldy] (P real or P complex values per frame)

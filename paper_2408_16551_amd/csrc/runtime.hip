@@ -337,6 +337,22 @@ tina_status execute_with(tina_pfb_plan_s* p, const void* d_in, int64_t n, void* 
                     fa.q1 = (uint8_t*)w.ws + (int64_t)w.ch_frames * p->W * 2;
                 if (form_scaled(form)) fa.fexp = w.fexp;
             }
+            if (!p->fold && (p->dft_algorithm == TINA_DFT_DENSE || p->dft_algorithm == TINA_DFT_FUSED)) {
+                GemmArgs na{};
+                na.B0 = p->B[0];
+                na.B1 = p->B[1];
+                na.out = (float*)d_out + c0 * ldo;
+                na.ldo = ldo;
+                na.F = Fc;
+                na.K = p->K;
+                na.N = p->N;
+                na.real_pack = p->cf == 1;
+                na.form = form;
+                if (narrow_supported(fa, na)) {
+                    HIP_TRY(timed(p->ev_dft, [&] { return launch_narrow(fa, na, s); }));
+                    continue;
+                }
+            }
             HIP_TRY(timed(p->ev_fir, [&] { return p->fold ? launch_fir_fold(fa, s) : launch_fir(fa, s); }));
             if (p->dft_algorithm == TINA_DFT_FACTORED) {
                 FftArgs xa{};
