@@ -251,10 +251,10 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
         return tf;
     };
 
-    std::vector<int64_t> fu(g.count), gu(g.count), su(g.count), ru(g.count), ffu(g.count), gfu(g.count);
+    std::vector<int64_t> fu(g.count), gu(g.count), su(g.count), ru(g.count), ffu(g.count), fsu(g.count), gfu(g.count);
     std::vector<int> fft_items;  // items taking the factored DFT
     std::vector<double> fc(g.count), gc(g.count), sc(g.count, 1.0), rc(g.count, 1.0);
-    int64_t ws_off = 0, amax_off = 0, f0 = 0, g0 = 0, s0 = 0, r0 = 0, ff0 = 0, gf0 = 0;
+    int64_t ws_off = 0, amax_off = 0, f0 = 0, g0 = 0, s0 = 0, r0 = 0, ff0 = 0, fs0 = 0, gf0 = 0;
     for (int i = 0; i < g.count; ++i) {
         tina_pfb_work& it = w[g.first + i];
         tina_pfb_plan_s* p = it.plan;
@@ -313,6 +313,8 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
         ga.fexp = fa.fexp;
         if (p->fold) {
             ga.tw = p->fold_tw;
+            ga.split = p->split;
+            fa.split_tw = p->split ? p->fft_tw : nullptr;
             ga.form = fold_operand_form(b->form);
             fa.qmode = fold_fir_qmode(b->form);
         }
@@ -326,17 +328,20 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
                          fir_frame_batch_vec(fa) != 0) ? 1 : 0;
         bi.frame_unit0 = r0;
         bi.ffold_unit0 = ff0;
+        bi.fsplit_unit0 = fs0;
         bi.gfold_unit0 = gf0;
-        ffu[i] = gfu[i] = 0;
+        ffu[i] = fsu[i] = gfu[i] = 0;
         if (p->fold) {  // whole ring blocks of the item's own M (32 or 64 beyond 16 taps)
             const int ring = p->M <= 16 ? p->M : p->M <= 32 ? 32 : 64;
             const int TF = frames_per_thread(ring);
             bi.fir_tf = TF;
             bi.fir_single = 1;  // no exponents to find for it
-            ffu[i] = (F + TF - 1) / TF * (p->W / (256 * fold_batch_vec(b->form, p->cf, p->M)));
+            const int64_t runs = (F + TF - 1) / TF;
+            if (p->split) fsu[i] = runs * (p->W / fold_split_cols(max_m));
+            else ffu[i] = runs * (p->W / (256 * fold_batch_vec(b->form, p->cf, p->M)));
             int64_t bm, bj;
             fold_batch_tile(b->form, p->N, bm, bj);
-            gfu[i] = (F * p->cf + bm - 1) / bm * ((p->N + bj - 1) / bj);
+            gfu[i] = (F * p->cf * (p->split ? 2 : 1) + bm - 1) / bm * ((p->N + bj - 1) / bj);
             fu[i] = ru[i] = 0;
             fc[i] = (double)TF * ring;
         } else if (bi.fir_single) {
@@ -357,6 +362,7 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
         }
         r0 += ru[i];
         ff0 += ffu[i];
+        fs0 += fsu[i];
         gf0 += gfu[i];
         const bool factored = p->dft_algorithm == TINA_DFT_FACTORED;
         gu[i] = (F > 0 && !factored && !p->fold) ? ((F + tile_m - 1) / tile_m) * ((p->N + tile_n - 1) / tile_n) : 0;
@@ -420,10 +426,12 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
     t->st_units = s0;
     t->frame_units = r0;
     t->ffold_units = ff0;
+    t->fsplit_units = fs0;
     t->gfold_units = gf0;
     split_by_cost(fu, fc, t->fir_bounds);
     split_by_cost(ru, rc, t->frame_bounds);
     split_by_cost(ffu, fc, t->ffold_bounds);
+    split_by_cost(fsu, fc, t->fsplit_bounds);
     split_by_cost(gfu, gc, t->gfold_bounds);
     split_by_cost(gu, gc, t->gemm_bounds);
     split_by_cost(su, sc, t->st_bounds);
@@ -466,7 +474,7 @@ int64_t fold_grid(const BatchTable* t) { return range_grid(t->gfold_bounds); }
 enum : int { STAGE_DENSE = 1, STAGE_FOLD = 2, STAGE_STATE = 4 };
 int table_stages(const BatchTable* t) {
     return (t->fir_units > 0 || t->frame_units > 0 || t->gemm_units > 0 ? STAGE_DENSE : 0) |
-           (t->ffold_units > 0 ? STAGE_FOLD : 0) | (t->st_units > 0 ? STAGE_STATE : 0);
+           (t->ffold_units + t->fsplit_units > 0 ? STAGE_FOLD : 0) | (t->st_units > 0 ? STAGE_STATE : 0);
 }
 
 // always: every launch of `stages` (captured steps, warm-up), with the fixed
@@ -477,7 +485,12 @@ tina_status launch_stages(tina_pfb_batch_s* b, hipStream_t s, const Tune& tune, 
     const int64_t grid_gemm = fixed_gemm_grid > 0 ? fixed_gemm_grid : gemm_grid(b->h_table);
     const int64_t grid_fold = fixed_fold_grid > 0 ? fixed_fold_grid : fold_grid(b->h_table);
     const int qmode = form_fir_qmode(b->form);
-    if (stages & STAGE_FOLD) HIP_TRY(launch_fir_fold_batch(b->d_table, max_m, fold_fir_qmode(b->form), grid_fir, s));
+    if (stages & STAGE_FOLD) {
+        if (always || b->h_table->fsplit_units > 0)
+            HIP_TRY(launch_fir_fold_batch(b->d_table, max_m, fold_fir_qmode(b->form), true, grid_fir / 2, s));
+        if (always || b->h_table->ffold_units > 0)
+            HIP_TRY(launch_fir_fold_batch(b->d_table, max_m, fold_fir_qmode(b->form), false, grid_fir, s));
+    }
     if ((stages & STAGE_DENSE) && (always || b->h_table->fir_units > 0 || b->h_table->frame_units > 0))
         HIP_TRY(launch_fir_batch(b->d_table, max_m, all_exact, qmode, grid_fir, s, b->frame_stage));
     if (stages & STAGE_FOLD) HIP_TRY(launch_fold_gemm_batch(b->d_table, fold_operand_form(b->form), (int)grid_fold, s));

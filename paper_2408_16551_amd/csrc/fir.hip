@@ -214,12 +214,12 @@ hipError_t launch_fir_fold(const FirArgs& a, hipStream_t s) {
     }
 }
 
-hipError_t launch_fir_fold_batch(const BatchTable* t, int max_m, int qmode, int grid, hipStream_t s) {
+hipError_t launch_fir_fold_batch(const BatchTable* t, int max_m, int qmode, bool split, int grid, hipStream_t s) {
     switch (qmode) {
-        case QM_NONE: return launch_fold_batch_f32(t, max_m, grid, s);
-        case QM_BF16: return launch_fold_batch_bf16(t, max_m, grid, s);
-        case QM_BF16X2: return launch_fold_batch_bf16x2(t, max_m, grid, s);
-        case QM_F8BF16: return launch_fold_batch_f8bf16(t, max_m, grid, s);
+        case QM_NONE: return launch_fold_batch_f32(t, max_m, split, grid, s);
+        case QM_BF16: return launch_fold_batch_bf16(t, max_m, split, grid, s);
+        case QM_BF16X2: return launch_fold_batch_bf16x2(t, max_m, split, grid, s);
+        case QM_F8BF16: return launch_fold_batch_f8bf16(t, max_m, split, grid, s);
         default: return hipErrorInvalidValue;
     }
 }

@@ -16,7 +16,9 @@
 // rounding of the operand costs what it did.
 //
 // A complex frame is two such rows (real, imaginary).  Output: row f * cf + ri,
-// P elements, part s at elements [s Q, (s+1) Q).
+// P elements, part s at elements [s Q, (s+1) Q).  Where fold_split says so a complex
+// frame takes one decimation in frequency first (fold_store_split) and is four rows
+// of P/2: its halves' real and imaginary parts.
 //
 // HBM-bound.  A block holds the four column groups that fold onto each other
 // (group g in wave(s) g, GF floats each), walks a run of frames through the
@@ -31,16 +33,16 @@
 namespace tina {
 namespace {
 
-template <int VEC, int GW>
+// VEC floats per thread, NG column groups (4; 8 for split frames) of GL lanes.
+template <int VEC, int NG, int GL>
 struct FoldGeom {
-    static constexpr int GL = 64 * GW;      // lanes per column group
-    static constexpr int GF = GL * VEC;     // floats per column group
-    static constexpr int NTH = 4 * GL;      // threads per block
-    static constexpr int SB = 16 / VEC;     // frames per LDS phase
+    static constexpr int GF = GL * VEC;                   // floats per column group
+    static constexpr int NTH = NG * GL;                   // threads per block
+    static constexpr int SB = NG == 4 ? 16 / VEC : 512 / GF;  // frames per LDS phase (16 to 32 KB a buffer)
 };
-template <int VEC, int GW>
+template <int VEC, int NG, int GL>
 struct FoldSmem {
-    float ys[2][FoldGeom<VEC, GW>::SB][4 * FoldGeom<VEC, GW>::GF];
+    float ys[2][FoldGeom<VEC, NG, GL>::SB][NG * FoldGeom<VEC, NG, GL>::GF];
 };
 
 __device__ __forceinline__ fvec4 fold_mirror(const fvec4& v, bool cplx) {
@@ -87,10 +89,11 @@ __device__ __forceinline__ typename VecT<VEC>::T fold_value(typename VecT<VEC>::
 // block at float offset c0 of each quarter frame.  A thread stores four
 // elements of a part at a time: real frames four samples' four parts, complex
 // ones two of the parts (even or odd channels) of four samples.
-template <int VEC, int GW, int QM>
-__device__ __forceinline__ void fold_store(const FirArgs& a, const float (&ys)[FoldGeom<VEC, GW>::SB][4 * FoldGeom<VEC, GW>::GF],
+template <int VEC, int GL, int QM>
+__device__ __forceinline__ void fold_store(const FirArgs& a,
+                                           const float (&ys)[FoldGeom<VEC, 4, GL>::SB][4 * FoldGeom<VEC, 4, GL>::GF],
                                            int64_t f0, int cnt, int c0) {
-    using G = FoldGeom<VEC, GW>;
+    using G = FoldGeom<VEC, 4, GL>;
     constexpr int X4 = G::GF / 4;  // float4 positions per group
     const int Q = a.P / 4;
     if (a.cf == 2) {
@@ -128,17 +131,86 @@ __device__ __forceinline__ void fold_store(const FirArgs& a, const float (&ys)[F
     }
 }
 
+// The same of split complex frames: u = y[p] + y[p + P/2] (even channels) and
+// v = (y[p] - y[p + P/2]) exp(-2 pi i p / P) (odd channels), p < P/2, each folded as
+// a frame of P/2.  Groups 0-3 hold the places that fold onto each other, groups
+// 4-7 the same P/2 samples later.  A thread takes four samples of one half (t)
+// and two of its parts (h).
+template <int VEC, int GL, int QM>
+__device__ __forceinline__ void fold_store_split(const FirArgs& a,
+                                                 const float (&ys)[FoldGeom<VEC, 8, GL>::SB][8 * FoldGeom<VEC, 8, GL>::GF],
+                                                 int64_t f0, int cnt, int c0) {
+    using G = FoldGeom<VEC, 8, GL>;
+    constexpr int X4 = G::GF / 4, X8 = G::GF / 8;
+    const int H = a.P / 2, Q = a.P / 8, n = cnt * X8;  // half's length, part's length, places
+    const fvec2* tw = reinterpret_cast<const fvec2*>(a.split_tw);
+    for (int it = threadIdx.x; it < 4 * n; it += G::NTH) {
+        const int sub = it / n, pl = it % n, t = sub >> 1, h = sub & 1, fr = pl / X8, x = pl % X8;
+        const fvec4* row = reinterpret_cast<const fvec4*>(ys[fr]);
+        const int p0 = c0 / 2 + 4 * x;
+        // z[g][i]: sample p0 + i of group g (mirrored groups in the order of their folds), as re, im.
+        fvec2 z[4][4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int q = 2 * x + i;
+                const bool mir = g & 1;
+                const int at = g * X4 + (mir ? X4 - 1 - q : q);
+                fvec4 y0 = row[at], y1 = row[at + 4 * X4];
+                fvec4 d = t ? y0 - y1 : y0 + y1;
+                if (mir) d = fold_mirror(d, true);
+                z[g][2 * i] = fvec2{d[0], d[1]};
+                z[g][2 * i + 1] = fvec2{d[2], d[3]};
+            }
+        if (t) {
+            // Twiddles of places p, P/4 - 1 - p, P/4 + p, P/2 - 1 - p by those of p and
+            // p + 1: w(p), -i w*(p + 1), -i w(p), -w*(p + 1).
+            fvec2 w = tw[p0];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const fvec2 w1 = tw[p0 + i + 1];
+                auto fwd = [](fvec2 d, fvec2 c) { return fvec2{fmaf(d[0], c[0], d[1] * c[1]), fmaf(d[1], c[0], -(d[0] * c[1]))}; };
+                auto bwd = [](fvec2 d, fvec2 c) { return fvec2{fmaf(d[0], c[0], -(d[1] * c[1])), fmaf(d[1], c[0], d[0] * c[1])}; };
+                z[0][i] = fwd(z[0][i], w);
+                const fvec2 b = bwd(z[1][i], w1), c = fwd(z[2][i], w), d = bwd(z[3][i], w1);
+                z[1][i] = fvec2{b[1], -b[0]};
+                z[2][i] = fvec2{c[1], -c[0]};
+                z[3][i] = fvec2{-d[0], -d[1]};
+                w = w1;
+            }
+        }
+        float cr[4], ci[4], sr[4], si[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const fvec2 e = z[0][i] + z[3][i], e2 = z[1][i] + z[2][i], o = z[0][i] - z[3][i], o2 = z[1][i] - z[2][i];
+            const fvec2 c = h ? e - e2 : e + e2, s = h ? o + o2 : o - o2;
+            cr[i] = c[0];
+            ci[i] = c[1];
+            sr[i] = s[0];
+            si[i] = s[1];
+        }
+        const int64_t el = (f0 + fr) * (int64_t)a.W + (int64_t)t * a.P + p0 + 2 * h * Q;
+        fold_put<QM>(a, el, cr);
+        fold_put<QM>(a, el + Q, sr);
+        fold_put<QM>(a, el + H, ci);
+        fold_put<QM>(a, el + H + Q, si);
+    }
+}
+
 // One unit: column block and run of logical block `blk`.  Every condition on
 // frames is the same for the whole block, so all its threads meet at each
 // barrier.  ph: the LDS buffer of the next phase (a buffer is written again
 // two phases later, after every thread has passed the barrier in between, so
 // one barrier per phase is enough, across units too).
-template <int VEC, int GW, int MT, bool EXACT, int QM>
-__device__ __forceinline__ void fir_fold_unit(const FirArgs& a, int TF, int64_t blk, FoldSmem<VEC, GW>& sm, int& ph) {
+template <int VEC, int NG, int GL, int MT, bool EXACT, int QM>
+__device__ __forceinline__ void fir_fold_unit(const FirArgs& a, int TF, int64_t blk, FoldSmem<VEC, NG, GL>& sm, int& ph) {
     using V = typename VecT<VEC>::T;
-    using G = FoldGeom<VEC, GW>;
+    using G = FoldGeom<VEC, NG, GL>;
     constexpr int SB = G::SB < MT ? G::SB : MT;
-    const int quarter = a.W / 4, ncb = quarter / G::GF;  // powers of two
+    // Floats that fold four-fold (a frame, or half of one), a quarter of them,
+    // and the column blocks of a quarter: powers of two.
+    const int span = NG == 8 ? a.W / 2 : a.W, quarter = span / 4, ncb = quarter / G::GF;
     const int cb = (int)(blk & (ncb - 1));
     const int64_t run = blk / ncb;
     const int64_t f_begin = run * TF;
@@ -146,8 +218,8 @@ __device__ __forceinline__ void fir_fold_unit(const FirArgs& a, int TF, int64_t 
     const int64_t f_end = min(a.F, f_begin + TF);
     const int M = EXACT ? MT : a.M;
     const int c0 = cb * G::GF;
-    const int g = threadIdx.x / G::GL, x = (threadIdx.x % G::GL) * VEC;
-    const int j0 = (g == 0 ? c0 : g == 1 ? 2 * quarter - c0 - G::GF : g == 2 ? 2 * quarter + c0 : a.W - c0 - G::GF) + x;
+    const int g = threadIdx.x / GL, x = (threadIdx.x % GL) * VEC, gg = g & 3;
+    const int j0 = (g >> 2) * span + (gg == 0 ? c0 : gg == 1 ? 2 * quarter - c0 - G::GF : gg == 2 ? 2 * quarter + c0 : span - c0 - G::GF) + x;
     const int slot = g * G::GF + x;  // this thread's floats in an LDS row
 
     V tp[MT];
@@ -156,14 +228,27 @@ __device__ __forceinline__ void fir_fold_unit(const FirArgs& a, int TF, int64_t 
     V win[MT];  // ring of input frames, as in fir_unit
     auto direct = [&](int64_t f) {
         V acc = V(0.0f);
+        if constexpr (EXACT) {
+            // All its loads in flight before the first FMA (195 frames of 1024
+            // channels, 12 taps, half of them such: 10 us; 20 us where the
+            // compiler puts waits between the loads).
+            V in[MT];
 #pragma unroll
-        for (int m = 0; m < MT; ++m)
-            if (EXACT || m < M) acc = __builtin_elementwise_fma(tp[m], load_frame<VEC, true>(a, a.g0 + f - m, j0), acc);
+            for (int m = 0; m < MT; ++m) in[m] = load_frame<VEC, true>(a, a.g0 + f - m, j0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int m = 0; m < MT; ++m) acc = __builtin_elementwise_fma(tp[m], in[m], acc);
+        } else {
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+                if (m < M) acc = __builtin_elementwise_fma(tp[m], load_frame<VEC, true>(a, a.g0 + f - m, j0), acc);
+        }
         return acc;
     };
     auto flush = [&](int64_t f0, int cnt) {
         __syncthreads();
-        fold_store<VEC, GW, QM>(a, sm.ys[ph], f0, cnt, c0);
+        if constexpr (NG == 8) fold_store_split<VEC, GL, QM>(a, sm.ys[ph], f0, cnt, c0);
+        else fold_store<VEC, GL, QM>(a, sm.ys[ph], f0, cnt, c0);
         ph ^= 1;
     };
     // Frames [f0, f1) straight from their input frames: blocks that straddle
@@ -213,18 +298,18 @@ __device__ __forceinline__ void fir_fold_unit(const FirArgs& a, int TF, int64_t 
     slow(fb, f_end);
 }
 
-template <int VEC, int GW, int MT, bool EXACT, int QM>
-__global__ __launch_bounds__((FoldGeom<VEC, GW>::NTH)) void fir_fold_kernel(FirArgs a, int TF) {
-    __shared__ __attribute__((aligned(16))) FoldSmem<VEC, GW> sm;
+template <int VEC, int NG, int GL, int MT, bool EXACT, int QM>
+__global__ __launch_bounds__((FoldGeom<VEC, NG, GL>::NTH)) void fir_fold_kernel(FirArgs a, int TF) {
+    __shared__ __attribute__((aligned(16))) FoldSmem<VEC, NG, GL> sm;
     int ph = 0;
-    fir_fold_unit<VEC, GW, MT, EXACT, QM>(a, TF, xcd_logical_block(blockIdx.x, gridDim.x), sm, ph);
+    fir_fold_unit<VEC, NG, GL, MT, EXACT, QM>(a, TF, xcd_logical_block(blockIdx.x, gridDim.x), sm, ph);
 }
 
-template <int VEC, int M0, int MT, int QM>
-__device__ __forceinline__ void fir_fold_unit_own_m(const FirArgs& a, int TF, int64_t blk, FoldSmem<VEC, 1>& sm, int& ph) {
+template <int VEC, int NG, int GL, int M0, int MT, int QM>
+__device__ __forceinline__ void fir_fold_unit_own_m(const FirArgs& a, int TF, int64_t blk, FoldSmem<VEC, NG, GL>& sm, int& ph) {
     if constexpr (M0 <= MT) {
-        if (a.M == M0) fir_fold_unit<VEC, 1, M0, true, QM>(a, TF, blk, sm, ph);
-        else fir_fold_unit_own_m<VEC, M0 + 1, MT, QM>(a, TF, blk, sm, ph);
+        if (a.M == M0) fir_fold_unit<VEC, NG, GL, M0, true, QM>(a, TF, blk, sm, ph);
+        else fir_fold_unit_own_m<VEC, NG, GL, M0 + 1, MT, QM>(a, TF, blk, sm, ph);
     }
 }
 
@@ -236,9 +321,10 @@ template <int MAXM, int QM>
 __global__ __launch_bounds__(256) void fir_fold_batch_kernel(const BatchTable* __restrict__ t) {
     constexpr int CV = QM == QM_NONE ? 1 : 2;  // floats per thread of complex items
     __shared__ __attribute__((aligned(16))) union {
-        FoldSmem<1, 1> one;
-        FoldSmem<CV, 1> cplx;
+        FoldSmem<1, 4, 64> one;
+        FoldSmem<CV, 4, 64> cplx;
     } sm;
+    static_assert(sizeof(FoldSmem<1, 4, 64>) == sizeof(FoldSmem<CV, 4, 64>), "their buffers coincide");
     int ph = 0;
     const int x = blockIdx.x & 7, i = blockIdx.x >> 3, nbx = gridDim.x >> 3;
     const int64_t end = t->ffold_bounds[x + 1];
@@ -248,33 +334,53 @@ __global__ __launch_bounds__(256) void fir_fold_batch_kernel(const BatchTable* _
         const FirArgs fa = b.fir;
         const int64_t blk = u - b.ffold_unit0;
         if (MAXM <= 16 || fa.M <= 16) {
-            if (CV == 2 && fa.cf == 2) fir_fold_unit_own_m<CV, 1, 16, QM>(fa, b.fir_tf, blk, sm.cplx, ph);
-            else fir_fold_unit_own_m<1, 1, 16, QM>(fa, b.fir_tf, blk, sm.one, ph);
+            if (CV == 2 && fa.cf == 2) fir_fold_unit_own_m<CV, 4, 64, 1, 16, QM>(fa, b.fir_tf, blk, sm.cplx, ph);
+            else fir_fold_unit_own_m<1, 4, 64, 1, 16, QM>(fa, b.fir_tf, blk, sm.one, ph);
         } else {
-            if constexpr (MAXM == 32) fir_fold_unit<1, 1, 32, false, QM>(fa, b.fir_tf, blk, sm.one, ph);
-            if constexpr (MAXM == 64) fir_fold_unit<1, 1, 64, false, QM>(fa, b.fir_tf, blk, sm.one, ph);
+            if constexpr (MAXM == 32) fir_fold_unit<1, 4, 64, 32, false, QM>(fa, b.fir_tf, blk, sm.one, ph);
+            if constexpr (MAXM == 64) fir_fold_unit<1, 4, 64, 64, false, QM>(fa, b.fir_tf, blk, sm.one, ph);
+        }
+    }
+}
+template <int MAXM, int QM>
+__global__ __launch_bounds__(MAXM <= 16 ? 512 : 256) void fir_fold_split_batch_kernel(const BatchTable* __restrict__ t) {
+    constexpr int GL = MAXM <= 16 ? 64 : 32;
+    __shared__ __attribute__((aligned(16))) FoldSmem<1, 8, GL> sm;
+    int ph = 0;
+    const int x = blockIdx.x & 7, i = blockIdx.x >> 3, nbx = gridDim.x >> 3;
+    const int64_t end = t->fsplit_bounds[x + 1];
+    for (int64_t u = t->fsplit_bounds[x] + i; u < end; u += nbx) {
+        const int it = batch_find(t->items, t->n_items, u, /*stage=*/6);
+        const BatchItem& b = t->items[it];
+        const FirArgs fa = b.fir;
+        const int64_t blk = u - b.fsplit_unit0;
+        if (MAXM <= 16 || fa.M <= 16) {
+            fir_fold_unit_own_m<1, 8, GL, 1, 16, QM>(fa, b.fir_tf, blk, sm, ph);
+        } else {
+            if constexpr (MAXM == 32) fir_fold_unit<1, 8, GL, 32, false, QM>(fa, b.fir_tf, blk, sm, ph);
+            if constexpr (MAXM == 64) fir_fold_unit<1, 8, GL, 64, false, QM>(fa, b.fir_tf, blk, sm, ph);
         }
     }
 }
 
-template <int VEC, int GW, int MT, bool EXACT, int QM>
+template <int VEC, int NG, int GL, int MT, bool EXACT, int QM>
 hipError_t launch_fold_one(const FirArgs& a, hipStream_t s) {
-    using G = FoldGeom<VEC, GW>;
-    const int ncb = a.W / 4 / G::GF;
+    using G = FoldGeom<VEC, NG, GL>;
+    const int ncb = a.W / NG / G::GF;
     // Frames per block: whole ring blocks, two of them (at least 16 frames) so
     // that the halo stays small; one while that leaves CUs without a block.
     int TF = 2 * MT < 16 ? ((16 + MT - 1) / MT) * MT : 2 * MT;
     while (TF > MT && TF > 4 && (a.F + TF - 1) / TF * ncb < 512) TF -= MT;
     const int64_t runs = (a.F + TF - 1) / TF;
-    hipLaunchKernelGGL((fir_fold_kernel<VEC, GW, MT, EXACT, QM>), dim3((unsigned)(runs * ncb)), dim3(G::NTH), 0, s, a, TF);
+    hipLaunchKernelGGL((fir_fold_kernel<VEC, NG, GL, MT, EXACT, QM>), dim3((unsigned)(runs * ncb)), dim3(G::NTH), 0, s, a, TF);
     return hipGetLastError();
 }
 
-template <int VEC, int GW, int M0, int MTOP, int QM>
+template <int VEC, int NG, int GL, int M0, int MTOP, int QM>
 hipError_t launch_fold_m(const FirArgs& a, hipStream_t s) {
     if constexpr (M0 <= MTOP) {
-        if (a.M == M0) return launch_fold_one<VEC, GW, M0, true, QM>(a, s);
-        return launch_fold_m<VEC, GW, M0 + 1, MTOP, QM>(a, s);
+        if (a.M == M0) return launch_fold_one<VEC, NG, GL, M0, true, QM>(a, s);
+        return launch_fold_m<VEC, NG, GL, M0 + 1, MTOP, QM>(a, s);
     }
     return hipErrorInvalidValue;
 }
@@ -283,23 +389,40 @@ template <int QM>
 hipError_t launch_fold_qm(const FirArgs& a, hipStream_t s) {
     auto aligned = [&](const void* p) { return ((uintptr_t)p & 15) == 0; };
     const bool al16 = a.plen % 4 == 0 && aligned(a.chunk) && (!a.prefix || aligned(a.prefix));
-    if (a.M <= 8 && al16 && a.W >= 1024) return launch_fold_m<4, 1, 1, 8, QM>(a, s);
-    // 16-bit complex rows: 128 lanes a group, so that a part row's piece of 64
-    // samples fills a 128-byte line (1024 channels, 16 taps, 2^25 samples, BF16x3:
-    // 163 us with 64 lanes and half lines, 129 us; FP32 rows the same either way).
-    if (QM != QM_NONE && a.cf == 2 && a.M <= 16) return launch_fold_m<1, 2, 1, 16, QM>(a, s);
-    if (a.M <= 16) return launch_fold_m<1, 1, 1, 16, QM>(a, s);
-    if (a.M <= 32) return launch_fold_one<1, 1, 32, false, QM>(a, s);
-    if (a.M <= 64) return launch_fold_one<1, 1, 64, false, QM>(a, s);
+    if (a.split_tw) {
+        // 64 samples a group (a part row's piece fills a 128-byte line in the
+        // 16-bit forms) in blocks of 256 threads while their registers hold two
+        // blocks a CU: 4096 channels, 2^25 samples, 8 taps, BF16x3: 123 us, 159
+        // with one float a thread.  Beyond 8 taps one float (1024 channels, 16
+        // taps, FP32: 131 us; 156 with four, 184 with two in 512 threads).
+        if (a.M <= 8 && al16) return launch_fold_m<4, 8, 32, 1, 8, QM>(a, s);
+        if (a.M <= 16) return launch_fold_m<1, 8, 64, 1, 16, QM>(a, s);
+        if (a.M <= 32) return launch_fold_one<1, 8, 32, 32, false, QM>(a, s);
+        if (a.M <= 64) return launch_fold_one<1, 8, 32, 64, false, QM>(a, s);
+        return hipErrorInvalidValue;
+    }
+    if (a.M <= 8 && al16 && a.W >= 1024) return launch_fold_m<4, 4, 64, 1, 8, QM>(a, s);
+    // 16-bit complex rows: 128 lanes a group, for whole lines as above (1024
+    // channels, 16 taps, 2^25 samples, BF16x3, unsplit: 163 us with 64 lanes and
+    // half lines, 129 us; FP32 rows the same either way).
+    if (QM != QM_NONE && a.cf == 2 && a.M <= 16) return launch_fold_m<1, 4, 128, 1, 16, QM>(a, s);
+    if (a.M <= 16) return launch_fold_m<1, 4, 64, 1, 16, QM>(a, s);
+    if (a.M <= 32) return launch_fold_one<1, 4, 64, 32, false, QM>(a, s);
+    if (a.M <= 64) return launch_fold_one<1, 4, 64, 64, false, QM>(a, s);
     return hipErrorInvalidValue;
 }
 
 template <int QM>
-hipError_t launch_fold_batch_qm(const BatchTable* t, int max_m, int grid, hipStream_t s) {
-    if (max_m <= 16) hipLaunchKernelGGL((fir_fold_batch_kernel<16, QM>), dim3(grid), dim3(256), 0, s, t);
-    else if (max_m <= 32) hipLaunchKernelGGL((fir_fold_batch_kernel<32, QM>), dim3(grid), dim3(256), 0, s, t);
-    else hipLaunchKernelGGL((fir_fold_batch_kernel<64, QM>), dim3(grid), dim3(256), 0, s, t);
-    return hipGetLastError();
+hipError_t launch_fold_batch_qm(const BatchTable* t, int max_m, bool split, int grid, hipStream_t s) {
+    auto go = [&](auto tag) {
+        constexpr int MAXM = decltype(tag)::value;
+        if (split) hipLaunchKernelGGL((fir_fold_split_batch_kernel<MAXM, QM>), dim3(grid), dim3(MAXM <= 16 ? 512 : 256), 0, s, t);
+        else hipLaunchKernelGGL((fir_fold_batch_kernel<MAXM, QM>), dim3(grid), dim3(256), 0, s, t);
+        return hipGetLastError();
+    };
+    if (max_m <= 16) return go(std::integral_constant<int, 16>{});
+    if (max_m <= 32) return go(std::integral_constant<int, 32>{});
+    return go(std::integral_constant<int, 64>{});
 }
 
 }  // namespace
@@ -309,9 +432,9 @@ hipError_t launch_fold_f32(const FirArgs& a, hipStream_t s);
 hipError_t launch_fold_bf16(const FirArgs& a, hipStream_t s);
 hipError_t launch_fold_bf16x2(const FirArgs& a, hipStream_t s);
 hipError_t launch_fold_f8bf16(const FirArgs& a, hipStream_t s);
-hipError_t launch_fold_batch_f8bf16(const BatchTable* t, int max_m, int grid, hipStream_t s);
-hipError_t launch_fold_batch_f32(const BatchTable* t, int max_m, int grid, hipStream_t s);
-hipError_t launch_fold_batch_bf16(const BatchTable* t, int max_m, int grid, hipStream_t s);
-hipError_t launch_fold_batch_bf16x2(const BatchTable* t, int max_m, int grid, hipStream_t s);
+hipError_t launch_fold_batch_f8bf16(const BatchTable* t, int max_m, bool split, int grid, hipStream_t s);
+hipError_t launch_fold_batch_f32(const BatchTable* t, int max_m, bool split, int grid, hipStream_t s);
+hipError_t launch_fold_batch_bf16(const BatchTable* t, int max_m, bool split, int grid, hipStream_t s);
+hipError_t launch_fold_batch_bf16x2(const BatchTable* t, int max_m, bool split, int grid, hipStream_t s);
 
 }  // namespace tina

@@ -3,7 +3,7 @@
 
 namespace tina {
 hipError_t launch_fold_f8bf16(const FirArgs& a, hipStream_t s) { return launch_fold_qm<QM_F8BF16>(a, s); }
-hipError_t launch_fold_batch_f8bf16(const BatchTable* t, int max_m, int grid, hipStream_t s) {
-    return launch_fold_batch_qm<QM_F8BF16>(t, max_m, grid, s);
+hipError_t launch_fold_batch_f8bf16(const BatchTable* t, int max_m, bool split, int grid, hipStream_t s) {
+    return launch_fold_batch_qm<QM_F8BF16>(t, max_m, split, grid, s);
 }
 }  // namespace tina

@@ -7,7 +7,9 @@
 //   X_k = exp(i pi k / P) (C_k - i S_k);  complex frames also
 //   X_{P-k} = exp(-i pi k / P) (C_k + i S_k), C and S complex.
 // P^2/2 (real) or P^2 (complex) flops a frame instead of 2 P^2 or 8 P^2, and an
-// operand of P^2/4 entries instead of P^2 or 4 P^2.
+// operand of P^2/4 entries instead of P^2 or 4 P^2.  Where fold_split says so,
+// complex frames arrive in two halves of P/2 (even and odd channels) and take the
+// product of size P/2 twice: half the flops again, a quarter of the operand.
 //
 // As a matrix product: rows r = frame * cf + (re/im), inner index (part, p) of
 // length P on both sides, columns j; the accumulator set changes with the
@@ -32,6 +34,11 @@ template <int FORM> struct FF;
 template <> struct FF<FORM_FP32> { static constexpr int EB = 4, NP = 1; };
 template <> struct FF<FORM_BF16> { static constexpr int EB = 2, NP = 1; };
 template <> struct FF<FORM_BF16X3> { static constexpr int EB = 2, NP = 2; };
+
+// What the rows are: real frames; complex ones, as real and imaginary row; complex
+// ones in two halves (one decimation in frequency, fir_fold.h), as four rows.
+enum Mode : int { REAL = 0, CPLX = 1, SPLIT = 2 };
+template <int MODE> constexpr int kRows = MODE == REAL ? 1 : MODE == CPLX ? 2 : 4;
 
 constexpr int SLAB = 32;      // bytes of a row per MFMA step (8 FP32 or 16 bf16 of K)
 constexpr int GROUP_M = 8;    // m-tiles swept per column of j-tiles (4096 complex, BF16: 439 us; 470, 463, 532 at 4, 16, 32)
@@ -127,6 +134,57 @@ __device__ __forceinline__ void fold_out_cplx(float* row, int P, int j, const fl
     }
 }
 
+// The channels of one j of a split frame of P channels (halves t of P/2: channel
+// 2k + t is the half's channel k): C, S of the half's channels 2j and 2j + 1 as
+// complex numbers, w as above for P/2.  Each store is the two halves' channels,
+// 16 bytes, and a lane's four stores are two runs of 32.
+struct Quad {
+    float c0[2], s0[2], c1[2], s1[2];
+};
+struct HalfOut {
+    float e[2], em[2], o[2], om[2];  // the half's channels 2j, P/2 - 2j, 2j + 1, P/2 - 2j - 1
+};
+__device__ __forceinline__ HalfOut fold_half(const Quad& q, const float4& w) {
+    HalfOut r;
+    const float ur = q.c1[0] + q.s1[1], ui = q.c1[1] - q.s1[0], vr = q.c1[0] - q.s1[1], vi = q.c1[1] + q.s1[0];
+    r.o[0] = mul2(w.z, ur, -w.w, ui);
+    r.o[1] = mul2(w.w, ur, w.z, ui);
+    r.om[0] = mul2(w.z, vr, w.w, vi);
+    r.om[1] = mul2(w.z, vi, -w.w, vr);
+    const float pr = q.c0[0] + q.s0[1], pi = q.c0[1] - q.s0[0], mr = q.c0[0] - q.s0[1], mi = q.c0[1] + q.s0[0];
+    r.e[0] = mul2(w.x, pr, -w.y, pi);
+    r.e[1] = mul2(w.y, pr, w.x, pi);
+    r.em[0] = mul2(w.x, mr, w.y, mi);
+    r.em[1] = mul2(w.x, mi, -w.y, mr);
+    return r;
+}
+__device__ __forceinline__ void fold_out_split(float* row, int P, int j, const float4& w, float inv, const Quad& t0,
+                                               const Quad& t1) {
+    const HalfOut a = fold_half(t0, w), b = fold_half(t1, w);
+    if (inv == 0.0f) {
+        put16(row + 2 * (4 * j + 2), a.o[0], a.o[1], b.o[0], b.o[1]);
+        put16(row + 2 * (P - 4 * j - 2), a.om[0], a.om[1], b.om[0], b.om[1]);
+        if (j == 0) {  // k = 0 is C_0; in its mirror's place, S of k = P/4
+            put16(row, t0.c0[0], t0.c0[1], t1.c0[0], t1.c0[1]);
+            put16(row + P, t0.s0[0], t0.s0[1], t1.s0[0], t1.s0[1]);
+        } else {
+            put16(row + 8 * j, a.e[0], a.e[1], b.e[0], b.e[1]);
+            put16(row + 2 * (P - 4 * j), a.em[0], a.em[1], b.em[0], b.em[1]);
+        }
+    } else {  // channel n to place P - n, times inv
+        put16(row + 2 * (P - 4 * j - 3), b.o[0], b.o[1], a.o[0], a.o[1]);
+        put16(row + 2 * (4 * j + 1), b.om[0], b.om[1], a.om[0], a.om[1]);
+        if (j == 0) {
+            *reinterpret_cast<fvec2*>(row) = fvec2{inv * t0.c0[0], inv * t0.c0[1]};
+            *reinterpret_cast<fvec2*>(row + 2 * (P - 1)) = fvec2{inv * t1.c0[0], inv * t1.c0[1]};
+            put16(row + 2 * (P / 2 - 1), inv * t1.s0[0], inv * t1.s0[1], inv * t0.s0[0], inv * t0.s0[1]);
+        } else {
+            put16(row + 2 * (P - 4 * j - 1), b.e[0], b.e[1], a.e[0], a.e[1]);
+            put16(row + 2 * (4 * j - 1), b.em[0], b.em[1], a.em[0], a.em[1]);
+        }
+    }
+}
+
 // Entry of the folded operand from the table ct[r] = cos(pi r / P), r < 2P:
 // part s, column j, sample p: the angle pi k (2p+1) / P, a sine as the cosine
 // P/2 steps earlier.
@@ -158,14 +216,15 @@ struct FoldTile {
 
 // One tile (rows m0.., columns n0..), called by every thread of the block.
 // lds: two stages of K tiles.  TABLE: the B rows are assembled from ct.
-template <int FORM, bool CPLX, int WGM, int WGN, bool TABLE>
+template <int FORM, int MODE, int WGM, int WGN, bool TABLE>
 __device__ __forceinline__ void fold_tile(const GemmArgs& g, int64_t m0, int64_t n0, uint8_t* lds, const float* ct) {
+    constexpr bool IM = MODE != REAL;  // rows in (real, imaginary) pairs
     using G = FoldTile<FORM, WGM, WGN>;
     constexpr int NP = G::NP, RS = G::RS, CPR = G::CPR, NTH = G::NTH, BMR = G::BMR, BJ = G::BJ;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WGN, wn = wave % WGN, lr = lane & 31, lh = lane >> 5;
     const int P = g.K, Q = g.N, lq = 31 - __clz(Q);  // inner length, columns (a power of two)
-    const int64_t R = g.F * (CPLX ? 2 : 1);
+    const int64_t R = g.F * kRows<MODE>;
     const int64_t pitch = (int64_t)P * G::EB;      // bytes per operand row
     const uint8_t* Ap[2] = {FORM == FORM_FP32 ? (const uint8_t*)g.A : g.Aq, g.Aq1};
     const uint8_t* Bp[2] = {(const uint8_t*)g.B0, (const uint8_t*)g.B1};
@@ -215,7 +274,7 @@ __device__ __forceinline__ void fold_tile(const GemmArgs& g, int64_t m0, int64_t
                 const int c = tid + i * NTH;
                 int row = c / CPR;
                 // Complex frames: a wave's 64 rows as 32 real, then 32 imaginary.
-                if (CPLX) row = (row & ~63) | ((row & 1) << 5) | ((row >> 1) & 31);
+                if (IM) row = (row & ~63) | ((row & 1) << 5) | ((row >> 1) & 31);
                 *reinterpret_cast<uint4*>(As + p * BMR * RS + row * RS + (c % CPR) * 16) = r.a[p][i];
             }
 #pragma unroll
@@ -281,11 +340,19 @@ __device__ __forceinline__ void fold_tile(const GemmArgs& g, int64_t m0, int64_t
     const int j = (int)n0 + wn * 32 + lr;
     if (j >= Q) return;
     const float4 w = reinterpret_cast<const float4*>(g.tw)[j];
-    const int64_t fr0 = (m0 + wm * 64) / (CPLX ? 2 : 1);
+    const int64_t fr0 = (m0 + wm * 64) / (IM ? 2 : 1);
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         const int rr = 8 * (v >> 2) + 4 * lh + (v & 3);
-        if constexpr (CPLX) {
+        if constexpr (MODE == SPLIT) {
+            const int64_t f = (fr0 + rr) / 2;  // rows rr and rr + 1: the frame's halves
+            if ((v & 1) == 0 && f < g.F) {
+                const Quad t0{{acc[0][0][v], acc[0][1][v]}, {acc[1][0][v], acc[1][1][v]}, {acc[2][0][v], acc[2][1][v]}, {acc[3][0][v], acc[3][1][v]}};
+                const Quad t1{{acc[0][0][v + 1], acc[0][1][v + 1]}, {acc[1][0][v + 1], acc[1][1][v + 1]},
+                              {acc[2][0][v + 1], acc[2][1][v + 1]}, {acc[3][0][v + 1], acc[3][1][v + 1]}};
+                fold_out_split(g.out + f * g.ldo, 2 * P, j, w, g.inv, t0, t1);
+            }
+        } else if constexpr (IM) {
             const int64_t f = fr0 + rr;
             if (f < g.F) {
                 const float c0[2] = {acc[0][0][v], acc[0][1][v]}, s0[2] = {acc[1][0][v], acc[1][1][v]};
@@ -309,20 +376,21 @@ __device__ __forceinline__ void fold_tile(const GemmArgs& g, int64_t m0, int64_t
 // from memory straight to the MFMA registers, U slabs ahead: what bounds a short
 // call is how often it waits for memory.  The four parts meet in LDS.  Same K
 // order, same bits as fold_tile.
-template <int FORM, bool CPLX, int TM>
+template <int FORM, int MODE, int TM>
 __device__ __forceinline__ void fold_tile_small(const GemmArgs& g, int64_t m0, int64_t n0, float* ex) {
+    constexpr bool IM = MODE != REAL;  // rows in (real, imaginary) pairs
     constexpr int NP = FF<FORM>::NP, EB = FF<FORM>::EB, ROWS = 32 * TM;
     constexpr int U = TM == 1 && NP == 1 ? 8 : 4;  // (with two row blocks the registers cost more waves than 8 gain)
     const int lane = threadIdx.x & 63, s = threadIdx.x >> 6, lr = lane & 31, lh = lane >> 5;
     const int P = g.K, Q = g.N;
-    const int64_t R = g.F * (CPLX ? 2 : 1), pitch = (int64_t)P * EB;
+    const int64_t R = g.F * kRows<MODE>, pitch = (int64_t)P * EB;
     const uint8_t* Ap[2] = {FORM == FORM_FP32 ? (const uint8_t*)g.A : g.Aq, g.Aq1};
     const uint8_t* Bp[2] = {(const uint8_t*)g.B0, (const uint8_t*)g.B1};
     const int part0 = s * Q * EB + lh * 16;
     int64_t ao[TM];
 #pragma unroll
     for (int bm = 0; bm < TM; ++bm) {
-        const int64_t row = m0 + (CPLX ? 2 * lr + bm : 32 * bm + lr);
+        const int64_t row = m0 + (IM ? 2 * lr + bm : 32 * bm + lr);
         ao[bm] = (row < R ? row : R - 1) * pitch + part0;  // rows past the end: read, never written
     }
     const int64_t bo = (n0 + lr) * pitch + part0;  // Q is a multiple of 32
@@ -364,11 +432,16 @@ __device__ __forceinline__ void fold_tile_small(const GemmArgs& g, int64_t m0, i
     const int jl = threadIdx.x & 31, j = (int)n0 + jl;
     const float4 w = reinterpret_cast<const float4*>(g.tw)[j];
     auto at = [&](int part, int row) { return ex[(part * ROWS + row) * 33 + jl]; };
-    for (int i = threadIdx.x >> 5; i < (CPLX ? 32 : ROWS); i += 8) {
-        const int64_t f = m0 / (CPLX ? 2 : 1) + i;
+    for (int i = threadIdx.x >> 5; i < (MODE == SPLIT ? 16 : IM ? 32 : ROWS); i += 8) {
+        const int64_t f = m0 / kRows<MODE> + i;
         if (f >= g.F) break;
         float* row = g.out + f * g.ldo;
-        if constexpr (CPLX) {
+        if constexpr (MODE == SPLIT) {
+            const int a = 2 * i, b = a + 1;
+            const Quad t0{{at(0, a), at(0, 32 + a)}, {at(1, a), at(1, 32 + a)}, {at(2, a), at(2, 32 + a)}, {at(3, a), at(3, 32 + a)}};
+            const Quad t1{{at(0, b), at(0, 32 + b)}, {at(1, b), at(1, 32 + b)}, {at(2, b), at(2, 32 + b)}, {at(3, b), at(3, 32 + b)}};
+            fold_out_split(row, 2 * P, j, w, g.inv, t0, t1);
+        } else if constexpr (IM) {
             const float c0[2] = {at(0, i), at(0, 32 + i)}, s0[2] = {at(1, i), at(1, 32 + i)};
             const float c1[2] = {at(2, i), at(2, 32 + i)}, s1[2] = {at(3, i), at(3, 32 + i)};
             fold_out_cplx(row, P, j, w, g.inv, c0, s0, c1, s1);
@@ -388,40 +461,40 @@ __device__ __forceinline__ void fold_place(int64_t L, int64_t nm, int64_t nn, in
     n0 = (in / gsz) * bj;
 }
 
-template <int FORM, bool CPLX, int WGM, int WGN>
+template <int FORM, int MODE, int WGM, int WGN>
 __global__ __launch_bounds__((FoldTile<FORM, WGM, WGN>::NTH)) __attribute__((amdgpu_waves_per_eu(2)))
 void fold_gemm_kernel(GemmArgs g) {
     using G = FoldTile<FORM, WGM, WGN>;
     __shared__ __attribute__((aligned(16))) uint8_t lds[2 * G::STAGE];
-    const int64_t nm = (g.F * (CPLX ? 2 : 1) + G::BMR - 1) / G::BMR, nn = (g.N + G::BJ - 1) / G::BJ;
+    const int64_t nm = (g.F * kRows<MODE> + G::BMR - 1) / G::BMR, nn = (g.N + G::BJ - 1) / G::BJ;
     int64_t m0, n0;
     fold_place(xcd_logical_block(blockIdx.x, gridDim.x), nm, nn, G::BMR, G::BJ, m0, n0);
-    fold_tile<FORM, CPLX, WGM, WGN, false>(g, m0, n0, lds, nullptr);
+    fold_tile<FORM, MODE, WGM, WGN, false>(g, m0, n0, lds, nullptr);
 }
 
-template <int FORM, bool CPLX, int TM>
+template <int FORM, int MODE, int TM>
 __global__ __launch_bounds__(256) void fold_gemm_small_kernel(GemmArgs g) {
     constexpr int ROWS = 32 * TM;
     __shared__ float ex[4 * ROWS * 33];
-    const int64_t nm = (g.F * (CPLX ? 2 : 1) + ROWS - 1) / ROWS, nn = g.N / 32;
+    const int64_t nm = (g.F * kRows<MODE> + ROWS - 1) / ROWS, nn = g.N / 32;
     int64_t m0, n0;
     fold_place(xcd_logical_block(blockIdx.x, gridDim.x), nm, nn, ROWS, 32, m0, n0);
-    fold_tile_small<FORM, CPLX, TM>(g, m0, n0, ex);
+    fold_tile_small<FORM, MODE, TM>(g, m0, n0, ex);
 }
 
 // FP32 with the operand assembled from the 2P-entry cosine table (8 P bytes,
 // copied to LDS after the K tiles) instead of read: same entries, same bits.
-template <bool CPLX>
+template <int MODE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void fold_gemm_table_kernel(GemmArgs g) {
     using G = FoldTile<FORM_FP32, 2, 2>;
     extern __shared__ __attribute__((aligned(16))) uint8_t dyn[];
     float* ct = reinterpret_cast<float*>(dyn + 2 * G::STAGE);
     for (int r = threadIdx.x; r < 2 * g.K; r += G::NTH) ct[r] = g.ct[r];
     __syncthreads();
-    const int64_t nm = (g.F * (CPLX ? 2 : 1) + G::BMR - 1) / G::BMR, nn = (g.N + G::BJ - 1) / G::BJ;
+    const int64_t nm = (g.F * kRows<MODE> + G::BMR - 1) / G::BMR, nn = (g.N + G::BJ - 1) / G::BJ;
     int64_t m0, n0;
     fold_place(xcd_logical_block(blockIdx.x, gridDim.x), nm, nn, G::BMR, G::BJ, m0, n0);
-    fold_tile<FORM_FP32, CPLX, 2, 2, true>(g, m0, n0, dyn, ct);
+    fold_tile<FORM_FP32, MODE, 2, 2, true>(g, m0, n0, dyn, ct);
 }
 
 // Batched: block b serves tile b / 8 of XCD b % 8's range of the table's
@@ -439,23 +512,25 @@ void fold_gemm_batch_kernel(const BatchTable* __restrict__ t) {
     const int it = batch_find(t->items, t->n_items, u, /*stage=*/5);
     const GemmArgs g = t->items[it].gemm;
     int64_t bm, bj, m0, n0;
-    const int64_t rows = g.F * (g.real_pack ? 1 : 2);
+    const int64_t rows = g.F * (g.real_pack ? 1 : g.split ? 4 : 2);
     fold_batch_tile(FORM, g.N, bm, bj);
     fold_place(u - t->items[it].gfold_unit0, (rows + bm - 1) / bm, (g.N + bj - 1) / bj, bm, bj, m0, n0);
     if (!F32 && g.N == 64) {
-        if (g.real_pack) fold_tile<FORM, false, F32 ? 2 : 4, 2, false>(g, m0, n0, lds, nullptr);
-        else fold_tile<FORM, true, F32 ? 2 : 4, 2, false>(g, m0, n0, lds, nullptr);
+        if (g.real_pack) fold_tile<FORM, REAL, F32 ? 2 : 4, 2, false>(g, m0, n0, lds, nullptr);
+        else if (g.split) fold_tile<FORM, SPLIT, F32 ? 2 : 4, 2, false>(g, m0, n0, lds, nullptr);
+        else fold_tile<FORM, CPLX, F32 ? 2 : 4, 2, false>(g, m0, n0, lds, nullptr);
     } else {
-        if (g.real_pack) fold_tile<FORM, false, 2, F32 ? 2 : 4, false>(g, m0, n0, lds, nullptr);
-        else fold_tile<FORM, true, 2, F32 ? 2 : 4, false>(g, m0, n0, lds, nullptr);
+        if (g.real_pack) fold_tile<FORM, REAL, 2, F32 ? 2 : 4, false>(g, m0, n0, lds, nullptr);
+        else if (g.split) fold_tile<FORM, SPLIT, 2, F32 ? 2 : 4, false>(g, m0, n0, lds, nullptr);
+        else fold_tile<FORM, CPLX, 2, F32 ? 2 : 4, false>(g, m0, n0, lds, nullptr);
     }
 }
 
-template <int FORM, bool CPLX, int WGM, int WGN>
+template <int FORM, int MODE, int WGM, int WGN>
 hipError_t launch_fold_wide(const GemmArgs& g, hipStream_t s) {
     using G = FoldTile<FORM, WGM, WGN>;
-    const int64_t nm = (g.F * (CPLX ? 2 : 1) + G::BMR - 1) / G::BMR, nn = (g.N + G::BJ - 1) / G::BJ;
-    hipLaunchKernelGGL((fold_gemm_kernel<FORM, CPLX, WGM, WGN>), dim3((unsigned)(nm * nn)), dim3(G::NTH), 0, s, g);
+    const int64_t nm = (g.F * kRows<MODE> + G::BMR - 1) / G::BMR, nn = (g.N + G::BJ - 1) / G::BJ;
+    hipLaunchKernelGGL((fold_gemm_kernel<FORM, MODE, WGM, WGN>), dim3((unsigned)(nm * nn)), dim3(G::NTH), 0, s, g);
     return hipGetLastError();
 }
 
@@ -463,37 +538,37 @@ hipError_t launch_fold_wide(const GemmArgs& g, hipStream_t s) {
 // channels, FP32: 64 of them take 106 us either way, 128 take 166 us against
 // 201 us with the small ones; 1024 real channels, BF16x3: 64 take 35 us against
 // 31 us, 128 37 us against 58 us).
-template <int FORM, bool CPLX>
+template <int FORM, int MODE>
 hipError_t launch_fold_form(const GemmArgs& g, hipStream_t s) {
-    const int64_t R = g.F * (CPLX ? 2 : 1);
+    const int64_t R = g.F * kRows<MODE>;
     if (R * g.N < 96 * 128 * 128) {
         // Real frames: 32 rows a block until those are 512 blocks (1024 channels,
         // FP32: 1024 frames 17 us against 21 us with 64 rows, 4096 frames 49 us
         // against 35 us).
-        if constexpr (!CPLX) {
+        if constexpr (MODE == REAL) {
             const int64_t blocks = (R + 31) / 32 * (g.N / 32);
             if (blocks <= 512) {
-                hipLaunchKernelGGL((fold_gemm_small_kernel<FORM, CPLX, 1>), dim3((unsigned)blocks), dim3(256), 0, s, g);
+                hipLaunchKernelGGL((fold_gemm_small_kernel<FORM, MODE, 1>), dim3((unsigned)blocks), dim3(256), 0, s, g);
                 return hipGetLastError();
             }
         }
         const int64_t blocks = (R + 63) / 64 * (g.N / 32);
-        hipLaunchKernelGGL((fold_gemm_small_kernel<FORM, CPLX, 2>), dim3((unsigned)blocks), dim3(256), 0, s, g);
+        hipLaunchKernelGGL((fold_gemm_small_kernel<FORM, MODE, 2>), dim3((unsigned)blocks), dim3(256), 0, s, g);
         return hipGetLastError();
     }
-    if constexpr (FORM == FORM_FP32) return launch_fold_wide<FORM, CPLX, 2, 2>(g, s);
-    else return g.N == 64 ? launch_fold_wide<FORM, CPLX, 4, 2>(g, s) : launch_fold_wide<FORM, CPLX, 2, 4>(g, s);
+    if constexpr (FORM == FORM_FP32) return launch_fold_wide<FORM, MODE, 2, 2>(g, s);
+    else return g.N == 64 ? launch_fold_wide<FORM, MODE, 4, 2>(g, s) : launch_fold_wide<FORM, MODE, 2, 4>(g, s);
 }
 
-template <bool CPLX>
+template <int MODE>
 hipError_t launch_fold_table(const GemmArgs& g, hipStream_t s) {
     using G = FoldTile<FORM_FP32, 2, 2>;
-    const int64_t nm = (g.F * (CPLX ? 2 : 1) + G::BMR - 1) / G::BMR, nn = (g.N + G::BJ - 1) / G::BJ;
-    static const hipError_t attr = hipFuncSetAttribute((const void*)fold_gemm_table_kernel<CPLX>,
+    const int64_t nm = (g.F * kRows<MODE> + G::BMR - 1) / G::BMR, nn = (g.N + G::BJ - 1) / G::BJ;
+    static const hipError_t attr = hipFuncSetAttribute((const void*)fold_gemm_table_kernel<MODE>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize,
                                                        2 * G::STAGE + 8 * 8192);
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL((fold_gemm_table_kernel<CPLX>), dim3((unsigned)(nm * nn)), dim3(G::NTH), 2 * G::STAGE + 8 * g.K, s, g);
+    hipLaunchKernelGGL((fold_gemm_table_kernel<MODE>), dim3((unsigned)(nm * nn)), dim3(G::NTH), 2 * G::STAGE + 8 * g.K, s, g);
     return hipGetLastError();
 }
 
@@ -502,15 +577,20 @@ hipError_t launch_fold_table(const GemmArgs& g, hipStream_t s) {
 hipError_t launch_dft_fold(const GemmArgs& g, hipStream_t s) {
     if (g.F <= 0) return hipSuccess;
     if (g.N * 4 != g.K || g.N < 64 || !g.tw) return hipErrorInvalidValue;
-    const bool cplx = !g.real_pack;
+    auto go = [&](auto tag) {
+        constexpr int FORM = decltype(tag)::value;
+        return g.real_pack ? launch_fold_form<FORM, REAL>(g, s)
+               : g.split   ? launch_fold_form<FORM, SPLIT>(g, s)
+                           : launch_fold_form<FORM, CPLX>(g, s);
+    };
     if (g.ct) {
         if (g.form != FORM_FP32) return hipErrorInvalidValue;
-        return cplx ? launch_fold_table<true>(g, s) : launch_fold_table<false>(g, s);
+        return g.real_pack ? launch_fold_table<REAL>(g, s) : g.split ? launch_fold_table<SPLIT>(g, s) : launch_fold_table<CPLX>(g, s);
     }
     switch (g.form) {
-        case FORM_FP32: return cplx ? launch_fold_form<FORM_FP32, true>(g, s) : launch_fold_form<FORM_FP32, false>(g, s);
-        case FORM_BF16: return cplx ? launch_fold_form<FORM_BF16, true>(g, s) : launch_fold_form<FORM_BF16, false>(g, s);
-        case FORM_BF16X3: return cplx ? launch_fold_form<FORM_BF16X3, true>(g, s) : launch_fold_form<FORM_BF16X3, false>(g, s);
+        case FORM_FP32: return go(std::integral_constant<int, FORM_FP32>{});
+        case FORM_BF16: return go(std::integral_constant<int, FORM_BF16>{});
+        case FORM_BF16X3: return go(std::integral_constant<int, FORM_BF16X3>{});
         default: return hipErrorInvalidValue;
     }
 }

@@ -186,7 +186,7 @@ __global__ void fold_tables_kernel(float* tw, float* ct, float* ones, int P, flo
         tw[2 * i] = scale * __double2float_rn(c);
         tw[2 * i + 1] = scale * __double2float_rn(s);
     }
-    if (ones && i < P) ones[i] = 1.0f;
+    if (ones && i < 2 * P) ones[i] = 1.0f;
     if (ct && i < 2 * P) ct[i] = __double2float_rn(cospi((double)i / (double)P));
 }
 

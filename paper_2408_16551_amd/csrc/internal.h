@@ -73,6 +73,7 @@ struct FirArgs {
     // exponent e_f (fexp[f], the frame's values are scaled by 2^-e_f), then
     // writes the scaled codes.
     int32_t* fexp;
+    const float* split_tw;  // folded output in two halves: cos, sin of 2 pi r / P, r < P (else nullptr)
 };
 // Chooses the vector width and unroll; returns the number of partial maxima
 // per frame through a.nparts when a.amax is set.
@@ -107,6 +108,7 @@ struct GemmArgs {
     const float* tw;       // FP32 only, non-null: Bt assembled from this P x (cos, sin) twiddle table (B0 unused)
                            // (folded product: cos, sin of pi k / P, k < P/2, for every form)
     const float* ct;       // folded product, FP32 only, non-null: operand assembled from cos(pi r / P), r < 2P
+    int32_t split;         // folded product, complex: frames in two halves (K = P/2, N = P/8)
     float inv;             // folded product, complex: 1/P for the inverse DFT (tw times 1/P), else 0
 };
 hipError_t launch_dft_gemm(const GemmArgs& a, hipStream_t s);
@@ -128,16 +130,31 @@ inline bool fold_form(int form) {
 // coefficients in bf16, a rounding an eighth of E4M3's.
 inline int fold_operand_form(int form) { return form == FORM_FP8 ? FORM_BF16 : form; }
 inline bool fold_supported(int P, int form) { return P >= 256 && fold_form(form); }
+// Complex frames take one decimation in frequency before the fold: half the
+// product's work for a FIR that writes its rows with twiddles.  FP32 from 512
+// channels (the halves are bank sizes of the folded product), 2^25 samples, 16
+// taps: 512 channels 316 -> 270 us, 1024 472 -> 360, 32 taps 654 -> 566.  The
+// 16-bit products take less time than the FIR until 2048 channels (BF16x3: 1024
+// channels 294 us unsplit, 298 split; 2048 398 -> 334, 4096 585 -> 426; BF16: 2048
+// 247 and 249, 4096 329 -> 290; FP8 with 8 taps: 2048 251 -> 233), and the longer
+// rings cost their FIR more than that gives.
+inline bool fold_split(int P, int cf, int form, int M) {
+    return cf == 2 && (form == FORM_FP32 ? P >= 512 : P >= 2048 && M <= 16);
+}
 // The FIR with folded output (a.y, or a.q / a.q1 with a.qmode; ldy, ldq unused).
 hipError_t launch_fir_fold(const FirArgs& a, hipStream_t s);
 hipError_t launch_dft_fold(const GemmArgs& a, hipStream_t s);
 // Folded operand [Q][4 parts][Q] in the pieces of `form`, in FP64 rounded once.
 hipError_t launch_fold_operand(void* piece0, void* piece1, int P, int form, hipStream_t s);
 // tw: (cos, sin)(pi k / P) times scale (a power of two), k < P/2; ct (optional):
-// cos(pi r / P), r < 2P; ones (optional): P times 1.
+// cos(pi r / P), r < 2P; ones (optional): 2P times 1.
 hipError_t launch_fold_tables(float* tw, float* ct, float* ones, int P, float scale, hipStream_t s);
 // Floats per thread of the batched folded FIR (its column blocks are 256 times as wide).
 inline int fold_batch_vec(int form, int cf, int M) { return form != FORM_FP32 && cf == 2 && M <= 16 ? 2 : 1; }
+// ... and floats per column block of a split item: eight groups of 64 lanes, or
+// of 32 in a batch with more than 16 taps (max_m), whose rings want a wave's
+// whole register file (64 lanes, eight waves: 150 to 840 registers spilled).
+inline int fold_split_cols(int max_m) { return 8 * (max_m <= 16 ? 64 : 32); }
 // Tile rows and columns of the batched folded product for N columns.
 __host__ __device__ inline void fold_batch_tile(int form, int64_t N, int64_t& bm, int64_t& bj) {
     bm = form != FORM_FP32 && N == 64 ? 256 : 128;
@@ -189,7 +206,7 @@ struct BatchItem {
     int64_t gemm_unit0;     // first GEMM tile of this item
     int64_t st_unit0;       // first state-update unit
     int32_t fir_tf;         // frames per FIR thread (fir_single: frames per frame-stage unit)
-    int64_t ffold_unit0, gfold_unit0;  // first unit / tile of the folded FIR / product
+    int64_t ffold_unit0, fsplit_unit0, gfold_unit0;  // first unit / tile of the folded FIR (whole, split frames) / product
     int32_t fir_single;     // per-frame scaled form: one pass, whole frame rows per unit (frame stage)
     int64_t frame_unit0;    // first unit of the frame stage
     float* st_dst;          // state buffer to fill (nullptr: no state)
@@ -201,15 +218,15 @@ struct BatchItem {
 struct BatchTable {
     int32_t n_items;
     int32_t pad_;
-    int64_t fir_units, gemm_units, st_units, frame_units, ffold_units, gfold_units;
-    int64_t fir_bounds[9], gemm_bounds[9], st_bounds[9], frame_bounds[9], ffold_bounds[9], gfold_bounds[9];
+    int64_t fir_units, gemm_units, st_units, frame_units, ffold_units, fsplit_units, gfold_units;
+    int64_t fir_bounds[9], gemm_bounds[9], st_bounds[9], frame_bounds[9], ffold_bounds[9], fsplit_bounds[9], gfold_bounds[9];
     int32_t gemm_bn;        // GEMM tile columns of this launch (kGemmBN or 2 * kGemmBN, or the wide tile's)
     int32_t gemm_wide;      // the launch uses the wide raw-operand tiles
     BatchItem items[1];     // n_items entries follow
 };
 
 // Index of the item that owns unit u of a stage (0 FIR, 1 GEMM, 2 state,
-// 3 single-pass per-frame FIR, 4 folded FIR, 5 folded product):
+// 3 single-pass per-frame FIR, 4 folded FIR, 5 folded product, 6 folded FIR of split frames):
 // the last item whose first unit is <= u.
 __device__ inline int batch_find(const BatchItem* items, int n, int64_t u, int stage) {
     int lo = 0, hi = n - 1;
@@ -220,6 +237,7 @@ __device__ inline int batch_find(const BatchItem* items, int n, int64_t u, int s
                           : stage == 2 ? items[mid].st_unit0
                           : stage == 3 ? items[mid].frame_unit0
                           : stage == 4 ? items[mid].ffold_unit0
+                          : stage == 6 ? items[mid].fsplit_unit0
                                        : items[mid].gfold_unit0;
         if (s <= u) lo = mid;
         else hi = mid - 1;
@@ -280,7 +298,8 @@ bool gemm_batch_wide_tile(int form, int K, int& bm, int& bn);
 hipError_t launch_gather_batch(const BatchTable* t, int grid, hipStream_t s);
 // Items with the folded product: their FIR (max_m: largest tap count among
 // them, qmode as launch_fir_batch) and their tiles (one block each).
-hipError_t launch_fir_fold_batch(const BatchTable* t, int max_m, int qmode, int grid, hipStream_t s);
+// split: the split items, else the others.
+hipError_t launch_fir_fold_batch(const BatchTable* t, int max_m, int qmode, bool split, int grid, hipStream_t s);
 hipError_t launch_fold_gemm_batch(const BatchTable* t, int form, int grid, hipStream_t s);
 
 }  // namespace tina

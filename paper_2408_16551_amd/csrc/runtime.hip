@@ -106,6 +106,7 @@ tina_status tina_pfb_plan(const tina_pfb_desc* d, tina_pfb_plan_t* out) {
     p->N = p->W;
     p->fold = d->output != TINA_OUT_FIR_ONLY && fold_supported(p->P, p->precision) &&
               (dft_alg == TINA_DFT_DENSE || dft_alg == TINA_DFT_FUSED || dft_alg == TINA_DFT_TABLE);
+    p->split = p->fold && fold_split(p->P, p->cf, p->precision, p->M);
     p->kout = d->output != TINA_OUT_PFB ? p->P : (p->cf == 2 ? p->P : p->P / 2 + 1);
 
     auto bail = [&](tina_status st, const std::string& m) {
@@ -129,38 +130,42 @@ tina_status tina_pfb_plan(const tina_pfb_desc* d, tina_pfb_plan_t* out) {
         const int form = p->precision;
         if (p->output == TINA_OUT_INVERSE) {
             if (p->fold) {
-                p->K = p->P;
-                p->N = p->P / 4;
+                p->K = p->split ? p->P / 2 : p->P;
+                p->N = p->K / 4;
             }
             const int64_t nbytes = (int64_t)p->N * p->K * form_elem_bytes(form);
             for (int i = 0; i < form_pieces(form); ++i)
                 if (hipMalloc(&p->B[i], nbytes) != hipSuccess) return bail(TINA_ERR_OUT_OF_MEMORY, "plan: IDFT operand allocation");
             if (p->fold && (hipMalloc(&p->fold_tw, sizeof(float) * p->P) != hipSuccess ||
-                            hipMalloc(&p->fold_one, sizeof(float) * p->P) != hipSuccess))
+                            hipMalloc(&p->fold_one, sizeof(float) * 2 * p->P) != hipSuccess ||
+                            (p->split && hipMalloc(&p->fft_tw, sizeof(float) * 2 * p->P) != hipSuccess)))
                 return bail(TINA_ERR_OUT_OF_MEMORY, "plan: twiddle table");
             if (hipMalloc(&p->g32, L * sizeof(float)) != hipSuccess) return bail(TINA_ERR_OUT_OF_MEMORY, "plan: synthesis taps");
             for (int i = 0; i < 2; ++i)
                 if (hipMalloc(&p->hist[i], std::max<int64_t>(1, (int64_t)(p->M - 1) * p->W) * sizeof(float)) != hipSuccess)
                     return bail(TINA_ERR_OUT_OF_MEMORY, "plan: synthesis history");
             if (p->fold) {
-                e = launch_fold_tables(p->fold_tw, nullptr, p->fold_one, p->P, 1.0f / (float)p->P, nullptr);
-                if (e == hipSuccess) e = launch_fold_operand(p->B[0], p->B[1], p->P, form, nullptr);
+                e = launch_fold_tables(p->fold_tw, nullptr, p->fold_one, p->K, 1.0f / (float)p->P, nullptr);
+                if (e == hipSuccess && p->split) e = launch_twiddle_table(p->fft_tw, p->P, nullptr);
+                if (e == hipSuccess) e = launch_fold_operand(p->B[0], p->B[1], p->K, fold_operand_form(form), nullptr);
             } else {
                 e = launch_dft_operand(p->B[0], p->B[1], p->P, 1, form, nullptr, /*inverse=*/1);
             }
             if (e == hipSuccess) e = launch_synthesis_taps(p->h64, p->g32, p->P, p->M, nullptr);
         } else if (p->fold) {
-            p->K = p->P;
-            p->N = p->P / 4;
+            p->K = p->split ? p->P / 2 : p->P;
+            p->N = p->K / 4;
             const bool table = p->dft_algorithm == TINA_DFT_TABLE;
             const int64_t nbytes = (int64_t)p->N * p->K * form_elem_bytes(fold_operand_form(form));
             for (int i = 0; i < form_pieces(fold_operand_form(form)) && !table; ++i)
                 if (hipMalloc(&p->B[i], nbytes) != hipSuccess) return bail(TINA_ERR_OUT_OF_MEMORY, "plan: DFT operand allocation");
             if (hipMalloc(&p->fold_tw, sizeof(float) * p->P) != hipSuccess ||
-                (table && hipMalloc(&p->fold_ct, sizeof(float) * 2 * p->P) != hipSuccess))
+                (table && hipMalloc(&p->fold_ct, sizeof(float) * 2 * p->P) != hipSuccess) ||
+                (p->split && hipMalloc(&p->fft_tw, sizeof(float) * 2 * p->P) != hipSuccess))
                 return bail(TINA_ERR_OUT_OF_MEMORY, "plan: twiddle table");
-            e = launch_fold_tables(p->fold_tw, p->fold_ct, nullptr, p->P, 1.0f, nullptr);
-            if (e == hipSuccess && !table) e = launch_fold_operand(p->B[0], p->B[1], p->P, fold_operand_form(form), nullptr);
+            e = launch_fold_tables(p->fold_tw, p->fold_ct, nullptr, p->K, 1.0f, nullptr);
+            if (e == hipSuccess && p->split) e = launch_twiddle_table(p->fft_tw, p->P, nullptr);
+            if (e == hipSuccess && !table) e = launch_fold_operand(p->B[0], p->B[1], p->K, fold_operand_form(form), nullptr);
         } else if (p->dft_algorithm == TINA_DFT_FACTORED || p->dft_algorithm == TINA_DFT_TABLE) {  // P twiddles alone
             if (hipMalloc(&p->fft_tw, sizeof(float) * 2 * p->P) != hipSuccess)
                 return bail(TINA_ERR_OUT_OF_MEMORY, "plan: twiddle table");
@@ -328,6 +333,7 @@ tina_status execute_with(tina_pfb_plan_s* p, const void* d_in, int64_t n, void* 
             // after the other; per-frame scaled forms also keep the frames'
             // exponents beside their partial maxima.
             fa.qmode = p->fold ? fold_fir_qmode(form) : form_fir_qmode(form);
+            fa.split_tw = p->split ? p->fft_tw : nullptr;
             if (fa.qmode != 0) {
                 fa.y = nullptr;
                 fa.q = (uint8_t*)w.ws;
@@ -387,6 +393,7 @@ tina_status execute_with(tina_pfb_plan_s* p, const void* d_in, int64_t n, void* 
             ga.compensated = p->dft_algorithm == TINA_DFT_COMPENSATED;
             ga.tw = p->fold ? p->fold_tw : p->dft_algorithm == TINA_DFT_TABLE ? p->fft_tw : nullptr;
             ga.ct = p->fold_ct;
+            ga.split = p->split;
             HIP_TRY(timed(p->ev_dft, [&] { return p->fold ? launch_dft_fold(ga, s) : launch_dft_gemm(ga, s); }));
         }
     }
@@ -555,6 +562,7 @@ tina_status tina_pfb_synthesize(tina_pfb_plan_t p, const void* d_X, int64_t F, v
             xa.cf = p->cf;
             xa.F = Fc;
             xa.qmode = form_fir_qmode(p->precision);
+            xa.split_tw = p->split ? p->fft_tw : nullptr;
             float* rows = p->ws + p->ch_frames * p->W;
             if (xa.qmode == 0) xa.y = rows;
             xa.q = (uint8_t*)rows;
@@ -565,6 +573,7 @@ tina_status tina_pfb_synthesize(tina_pfb_plan_t p, const void* d_X, int64_t F, v
             ga.Aq1 = xa.q1;
             ga.tw = p->fold_tw;
             ga.inv = 1.0f / (float)p->P;
+            ga.split = p->split;
             HIP_TRY(launch_dft_fold(ga, s));
         } else {
             HIP_TRY(launch_dft_gemm(ga, s));

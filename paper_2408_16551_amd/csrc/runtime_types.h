@@ -90,9 +90,10 @@ struct tina_pfb_plan_s {
     int dft_algorithm = 0;
     float* fft_tw = nullptr;    // cos, sin of 2 pi r / P (factored DFT, table operand below 256 channels)
     bool fold = false;          // dense DFT by the folded product (B: its operand, K = P, N = P/4)
+    bool split = false;         // ... of complex frames in two halves (K = P/2, N = P/8; fft_tw: their twiddles)
     float* fold_tw = nullptr;   // folded product: channel rotations
     float* fold_ct = nullptr;   // folded product with the table operand: cos(pi r / P)
-    float* fold_one = nullptr;  // P unit taps (synthesis: the channel frames are folded by the FIR)
+    float* fold_one = nullptr;  // unit taps (synthesis: the channel frames are folded by the FIR)
     float* g32 = nullptr;       // synthesis FIR taps (inverse plans)
     float* hist[2] = {nullptr, nullptr};  // history scratch between workspace pieces (inverse plans)
     int cus = 256;

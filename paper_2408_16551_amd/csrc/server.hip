@@ -309,7 +309,7 @@ tina_status tina_server_create(const tina_server_config* c_in, tina_server_t* ou
     // frames of the widest stream (128 x 128 tiles, N = 2 * max_channels).
     batch_set_graph_bound(sv->batch, (int64_t)c->max_active * ((c->frames_per_step + kGemmBM - 1) / kGemmBM) *
                                          ((2 * (int64_t)c->max_channels + kGemmBN - 1) / kGemmBN),
-                          (int64_t)c->max_active * ((2 * c->frames_per_step + 127) / 128) *
+                          (int64_t)c->max_active * ((4 * c->frames_per_step + 127) / 128) *
                               (((int64_t)c->max_channels / 4 + 63) / 64));
     if (hipStreamCreateWithFlags(&sv->s_comp, hipStreamNonBlocking) != hipSuccess ||
         hipStreamCreateWithFlags(&sv->s_h2d, hipStreamNonBlocking) != hipSuccess ||

@@ -111,3 +111,30 @@ def test_folded_synthesis_matches_oracle(oracle, P, M, F, prec):
     st, cut = State(plan), sorted({0, F // 3, F // 2, F})
     parts = [plan.synthesize(Xd[a:b].clone(), state=st).cpu().numpy() for a, b in zip(cut[:-1], cut[1:])]
     assert np.array_equal(np.concatenate(parts), got)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec", list(BOUND))
+@pytest.mark.parametrize("P,M,F", [(512, 1, 1), (512, 8, 17), (1024, 16, 31), (1024, 20, 33), (2048, 16, 15),
+                                   (2048, 7, 66), (2048, 17, 40), (8192, 64, 3)])
+def test_split_frames_match_oracle_and_batch(oracle, P, M, F, prec):
+    """Complex frames about the sizes and tap counts where they go in two halves:
+    the oracle, every value by itself, and a batch that mixes them (tap counts
+    up to 16, then with a longer one) bit for bit."""
+    from paper_2408_16551_amd.pfb import Batch
+    x = _x(P, F, True, P + 7 * M + F)
+    plan = _plan(P, M, True, prec)
+    got = _run(plan, x)
+    ref = oracle.pfb(x, P, M, oracle.window(P, M, "hann"))
+    assert rel_l2(got, ref) < BOUND[prec]
+    # Every value: white noise in, so each channel's error is complex normal of the
+    # forms' relative size times the spectrum's level, and beyond eight times it
+    # with probability exp(-64); a value at the wrong place is off by the level.
+    assert np.abs(got - ref).max() < 8 * BOUND[prec] * np.sqrt(np.mean(np.abs(ref) ** 2))
+    xd = torch.from_numpy(x).cuda()
+    for other in (_plan(1024, 5, True, prec), _plan(256, 33, False, prec)):
+        z = torch.from_numpy(_x(other.P, 40, other.sample_type == "c64", 3)).cuda()
+        items = [(plan, xd, plan.alloc_out(F)), (other, z, other.alloc_out(40))]
+        Batch(prec, max_items=2, workspace_bytes=1 << 28).execute(items)
+        assert np.array_equal(items[0][2].cpu().numpy(), got)
+        assert np.array_equal(items[1][2].cpu().numpy(), other(z).cpu().numpy())
