@@ -41,16 +41,28 @@ def rel_l2(got, ref):
     return float(np.linalg.norm(got - ref) / np.linalg.norm(ref))
 
 
-def dft_flops_per_frame(P: int, cplx: bool) -> float:
-    """Algorithmic flops of the dense DFT of one frame as the GEMM computes it:
-    real frame P x P real products (the two identically-zero imaginary
-    channels excluded), complex frame 2P x 2P."""
+FOLDED_FORMS = ("fp32", "bf16", "bf16x3", "fp8")
+
+
+def dft_flops_per_frame(P: int, cplx: bool, form: str = "fp32", dft: str = "dense", taps: int = 16) -> float:
+    """Flops of one frame's DFT as the kernels compute it.  The folded product
+    (FP32, BF16, BF16x3, FP8 from 256 channels): four P/4 x P/4 products, twice
+    for a complex frame, and half of that where a complex frame goes in two
+    halves.  Else the plain products: real frame P x P (the two identically-zero
+    imaginary channels excluded), complex frame 2P x 2P.  Factored: a complex FFT
+    of P points (P/2 for a real frame)."""
+    if dft == "factored":
+        n = P if cplx else P // 2
+        return 5.0 * n * np.log2(n)
+    if P >= 256 and form in FOLDED_FORMS and dft in ("dense", "fused", "table"):
+        split = cplx and (P >= 512 if form == "fp32" else P >= 2048 and taps <= 16)
+        return P * P * (0.5 if split or not cplx else 1.0)
     return 2.0 * (2 * P) * (2 * P) if cplx else 2.0 * P * P
 
 
 def source_digest() -> str:
     h = hashlib.sha256()
-    for f in ("paper_2408_16551_amd/csrc/gemm.hip", "paper_2408_16551_amd/csrc/internal.h"):
+    for f in ("paper_2408_16551_amd/csrc/gemm_fold.hip", "paper_2408_16551_amd/csrc/internal.h"):
         h.update(open(os.path.join(ROOT, f), "rb").read())
     return h.hexdigest()[:16]
 
@@ -137,7 +149,7 @@ def forms_table(w, forms, steps, warmup, torch, oracle_obj, n_frames_err):
         out = plan.alloc_out(F)
         sec, fir_ms, dft_ms = timed_steps(plan, xd, out, steps, warmup, torch)
         got = out[torch.from_numpy(fr).cuda()].cpu().numpy()
-        flops = dft_flops_per_frame(w.P, w.complex_input) * F
+        flops = dft_flops_per_frame(w.P, w.complex_input, form, dft, w.M) * F
         res[entry] = {
             "gsps": round(N / sec / 1e9, 3),
             "ms_per_step": round(sec * 1e3, 4),
@@ -153,11 +165,8 @@ def forms_table(w, forms, steps, warmup, torch, oracle_obj, n_frames_err):
         fir_out_b = FIR_OUT_BYTES[form]
         fir_b = F * w.P * (2 if w.complex_input else 1) * (4.0 + fir_out_b)
         res[entry]["fir_hbm_gbs"] = round(fir_b / (fir_ms * 1e-3) / 1e9, 1)
-        if dft == "factored":   # the dense-DFT flop figures do not apply
-            P1 = 1 << ((int(np.log2(w.P)) + 1) // 2)
-            f_fact = 8.0 * w.P * (P1 + w.P // P1) * F
-            res[entry]["dft_useful_tflops"] = round(f_fact / (dft_ms * 1e-3) / 1e12, 2)
-            res[entry]["dft_mfma_frac"] = round(f_fact / (dft_ms * 1e-3) / 1e12 / PEAK_TFLOPS["fp32"], 4)
+        if dft == "factored":   # on the vector units, bound by the bytes it moves
+            res[entry].pop("dft_mfma_frac")
             res[entry]["dft_bytes_gbs"] = round((4.0 * F * w.P * (2 if w.complex_input else 1)
                                                  + 8.0 * F * (w.P if w.complex_input else w.P // 2 + 1))
                                                 / (dft_ms * 1e-3) / 1e9, 1)
@@ -399,7 +408,7 @@ def batched_bench(torch, precisions=("fp32", "bf16x3", "fp32/factored"), steps=2
     """The ragged batch: 64 complex64 streams, log-uniform lengths 2^18-2^22,
     channels from {256, 512, 1024}, 16 taps, one persistent launch per stage,
     autotuned launch shapes ("fp32/factored": FP32 with the factored DFT,
-    one launch per channel count in place of the GEMM stage).  With an
+    one launch in place of the GEMM stage).  With an
     oracle: 4 seeded items of the timed batch are checked on sampled frames."""
     from paper_2408_16551_amd import workloads
     from paper_2408_16551_amd.pfb import Batch, Plan
@@ -423,7 +432,7 @@ def batched_bench(torch, precisions=("fp32", "bf16x3", "fp32/factored"), steps=2
             b.execute(items)
         torch.cuda.synchronize()
         sec = (time.perf_counter() - t) / steps
-        flops = sum(dft_flops_per_frame(s.P, True) * (x.size // s.P) for s, x in zip(specs, xs))
+        flops = sum(dft_flops_per_frame(s.P, True, prec, dft) * (x.size // s.P) for s, x in zip(specs, xs))
         res[entry] = {"gsps": round(total / sec / 1e9, 3), "ms_per_batch": round(sec * 1e3, 3),
                       "dft_useful_tflops_incl_fir": round(flops / sec / 1e12, 2),
                       "tuned": {"fir_frames_per_thread_mult": tf, "gemm_tile_n": tile_n}}
@@ -800,11 +809,11 @@ def main():
         "data": "synthetic (seeded N(0,1) noise + 8 channel-centre tones)",
         "config": {"workload": w.name, "channels": w.P, "taps": w.M, "window": "sinc x hann",
                    "samples": N, "sample_type": "r32", "precision": "fp32"},
-        "roofline": {"kernel": "dft_gemm_kernel<FP32>", "bound": "mfma", "achieved": round(achieved, 2),
+        "roofline": {"kernel": "fold_gemm_kernel<FP32>", "bound": "mfma", "achieved": round(achieved, 2),
                      "peak": PEAK_TFLOPS["fp32"], "unit": "TFLOP/s",
                      "frac": round(achieved / PEAK_TFLOPS["fp32"], 4), "traffic": traffic,
                      "flops_per_launch": flops, "avg_launch_ms": round(dft_ms, 4)},
-        "stages": {"fir": {"kernel": "fir_kernel", "bound": "hbm", "avg_launch_ms": round(fir_ms, 4),
+        "stages": {"fir": {"kernel": "fir_fold_kernel", "bound": "hbm", "avg_launch_ms": round(fir_ms, 4),
                            "achieved": round(fir_bytes / (fir_ms * 1e-3) / 1e9, 1), "peak": PEAK_HBM_GBS,
                            "unit": "GB/s", "frac": round(fir_bytes / (fir_ms * 1e-3) / 1e9 / PEAK_HBM_GBS, 4),
                            "bytes_per_launch": fir_bytes}},

@@ -152,9 +152,8 @@ typedef struct tina_pfb_desc {
  *   TINA_DFT_FACTORED  a factored DFT (mixed-radix FFT, passes of radix 2 to 16
  *                      in FP32): about 5 P log2 P flops per frame instead of
  *                      8 P^2.  FP32 only; 256 <= P <= 4096.
- *                      Also in FP32 batches (one launch per channel count and
- *                      input type over those items' frames) and in an FP32
- *                      server created with this algorithm.
+ *                      Also in FP32 batches (one launch over those items'
+ *                      frames) and in an FP32 server created with this algorithm.
  *   TINA_DFT_FUSED     the dense FP32 product for taps <= 16 and single-stream
  *                      execute, bit for bit TINA_DFT_DENSE.  It runs the FIR and
  *                      the product as two kernels like TINA_DFT_DENSE: a product

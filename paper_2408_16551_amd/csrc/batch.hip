@@ -1,13 +1,16 @@
 // Batched execution of many stream chunks with different channel counts,
 // tap counts and lengths in one persistent launch per stage:
-//   FIR stage  -> fir_batch_kernel   (all items' FIR units)
-//   DFT stage  -> dft_gemm_batch_kernel (all items' GEMM tiles)
+//   FIR stage  -> fir_batch_kernel, and fir_fold_batch_kernel /
+//                 fir_fold_split_batch_kernel for items of the folded product
+//   DFT stage  -> dft_gemm_batch_kernel, fold_gemm_batch_kernel (folded items),
+//                 fft_batch_kernel (factored items)
 //   state      -> gather_batch_kernel (all items' history/residue updates)
+// A kernel none of whose items are in the batch is not launched.
 // The launches read a device-resident BatchTable (item arguments, first unit
 // of each item per stage, and a cost-balanced split of every stage's units
 // into one contiguous range per XCD).  The table is uploaded from pinned host
 // memory on the caller's stream before the launches, so the launch arguments
-// themselves never change; that also makes the three launches capturable in
+// themselves never change; that also makes the launches capturable in
 // a graph and replayable with a new table.
 //
 // Launch shapes (frames per FIR thread, GEMM blocks per CU) are chosen by a

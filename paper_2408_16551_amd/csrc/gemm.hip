@@ -1,4 +1,6 @@
-// DFT across branches as a dense matrix product on the MFMA units
+// DFT across branches as a plain dense matrix product on the MFMA units: the
+// forms, bank sizes and options that gemm_fold.hip's folded product does not take
+// (FP16, FP16x3, block-scaled FP8, fewer than 256 channels, compensated sums)
 // (Sec. 4.1, Eq. (12): Z = X F, cast as a pointwise convolution, Sec. 3.2):
 //   C[f][n] = sum_k A[f][k] * Bt[n][k]
 // A = polyphase FIR output (FP32, frames x K), Bt = the DFT operand from
