@@ -70,9 +70,12 @@ __global__ __launch_bounds__(256) void fir_toeplitz_kernel(const float* __restri
     auto check = [&](float v) { odd |= (__builtin_bit_cast(uint32_t, v) & 0x7f800000u) == 0x7f800000u; };
     const int have = NBP + H;  // samples of a plane that an output reaches
     if (al16 && i0 >= H && i0 + NBP <= n) {  // i0 - H is a multiple of 4
+        // The block's own samples all in flight before the first LDS store: short
+        // filters are bound by this (16 M complex samples, 14 taps: 51.5 -> 43.7 us;
+        // 2^24 real samples, 129 taps: 54.1 -> 47.4).
         const f32x4* src = reinterpret_cast<const f32x4*>(x + (i0 - H) * CF);
-        for (int i = threadIdx.x; i < CF * have / 4; i += 256) {
-            const f32x4 v = src[i];
+        constexpr int U = CF * NBP / 4 / 256;
+        auto put = [&](int i, f32x4 v) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) check(v[e]);
             if constexpr (CF == 1) {
@@ -81,7 +84,13 @@ __global__ __launch_bounds__(256) void fir_toeplitz_kernel(const float* __restri
                 *reinterpret_cast<f32x2*>(sm + 2 * i) = f32x2{v[0], v[2]};
                 *reinterpret_cast<f32x2*>(sm + plane + 2 * i) = f32x2{v[1], v[3]};
             }
-        }
+        };
+        f32x4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = src[256 * u + threadIdx.x];
+        for (int i = 256 * U + threadIdx.x; i < CF * have / 4; i += 256) put(i, src[i]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) put(256 * u + threadIdx.x, v[u]);
     } else {
         for (int i = threadIdx.x; i < CF * have; i += 256) {
             const int p = i / CF, c = i % CF;
