@@ -262,9 +262,12 @@ tina_status tina_fir_execute(tina_fir_t f, const void* d_x, int64_t n, void* d_y
     const float* x = (const float*)d_x;
     float* y = (float*)d_y;
     hipStream_t s = (hipStream_t)stream;
-    // Blocks of 4096 floats; of 1024 (2048 complex floats) while those would
-    // leave CUs idle.
-    const bool big = nf >= 512 * 4096;
+    // Blocks of 4096 floats from eight of them a CU on, below that of 1024 (2048
+    // where complex): few large blocks a CU end together late (14 taps, buffers in
+    // turn: 4 M real samples 9.2 us against 10.9 with the large ones, 2.8 M complex
+    // 11.8 against 14.3; 5.9 M complex 21.7 either way; 40 taps 11.0 against 12.4,
+    // 13.8 against 16.2, 25.1 either way).
+    const bool big = nf >= 2048 * 4096;
     hipError_t e;
     if (f->cf == 1) e = big ? launch_toeplitz<4, 1>(x, n, f->taps, f->K, y, s) : launch_toeplitz<1, 1>(x, n, f->taps, f->K, y, s);
     else e = big ? launch_toeplitz<4, 2>(x, n, f->taps, f->K, y, s) : launch_toeplitz<2, 2>(x, n, f->taps, f->K, y, s);

@@ -24,7 +24,8 @@ def _ref(x, a):
 
 @pytest.mark.parametrize("K", [1, 2, 15, 16, 17, 18, 33, 129])
 @pytest.mark.parametrize("n,cplx", [(1, False), (15, True), (1023, False), (1025, True), (4097, False),
-                                    ((1 << 21) + 3, False), ((1 << 20) + 5, True)])
+                                    ((1 << 21) + 3, False), ((1 << 20) + 5, True),
+                                    ((1 << 23) + 3, False), ((1 << 22) + 5, True)])
 def test_edges_and_alignment(K, n, cplx):
     a, f = _filter(K, cplx)
     g = np.random.Generator(np.random.PCG64(n))
