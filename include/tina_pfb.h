@@ -89,9 +89,10 @@ typedef enum tina_window {
  *              same per-frame power-of-two scale.
  *   FP8_FRAME  operands in FP8 E4M3 (OCP), each frame scaled by a power of two
  *              so that its largest branch output maps to at most 448.  From 256
- *              channels the branch outputs are rounded to E4M3's four
- *              significant bits, and their sums and the Fourier coefficients
- *              (see TINA_DFT_DENSE) to bfloat16, whose range needs no scale.
+ *              channels the product is BF16's: the branch outputs are rounded
+ *              to E4M3's four significant bits (over float32's exponents, so
+ *              without a scale), their sums and the Fourier coefficients (see
+ *              TINA_DFT_DENSE) to bfloat16.
  *   MXFP8      block-scaled FP8 (quantisation, Sec. 1): operands in E4M3 with
  *              one power-of-two scale per 32 consecutive entries along the
  *              summed axis (a frame's branch values, re/im interleaved for
@@ -146,9 +147,13 @@ typedef struct tina_pfb_desc {
  *                      and under p -> P/2 - 1 - p, so the FIR writes four sums of
  *                      every four samples (FP32, then rounded to the operand type)
  *                      and four products of size P/4 replace the one of size P,
- *                      with a rotation of each channel at the end.  A frame with an
- *                      infinite or NaN sample gives non-finite channels either way;
- *                      which of them are infinite and which NaN is not specified;
+ *                      with a rotation of each channel at the end.  There a frame
+ *                      whose taps reach an infinite or NaN sample has no finite
+ *                      channel; which of them are infinite and which NaN is not
+ *                      specified, and branch outputs whose sums of four (complex,
+ *                      two halves: eight) pass the largest float count as infinite.
+ *                      The other scaled forms (FP16, FP16X3, MXFP8, FP8 below 256
+ *                      channels) promise nothing for such a frame;
  *   TINA_DFT_FACTORED  a factored DFT (mixed-radix FFT, passes of radix 2 to 16
  *                      in FP32): about 5 P log2 P flops per frame instead of
  *                      8 P^2.  FP32 only; 256 <= P <= 4096.

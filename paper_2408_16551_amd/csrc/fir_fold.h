@@ -72,14 +72,19 @@ __device__ __forceinline__ void fold_put(const FirArgs& a, int64_t el, const flo
 }
 
 // A value as the fold takes it: for FP8 rounded (to nearest even) to the 4
-// significant bits of E4M3, on the bit pattern.
+// significant bits of E4M3, on the bit pattern.  The largest floats saturate, as
+// E4M3's do.  Infinities and NaNs become NaN by the product with zero (a carry out
+// of a NaN's payload alone would leave a zero); a finite value's adds a zero of its
+// own sign.
 template <int VEC, int QM>
 __device__ __forceinline__ typename VecT<VEC>::T fold_value(typename VecT<VEC>::T v) {
     if constexpr (QM == QM_F8BF16) {
 #pragma unroll
         for (int i = 0; i < VEC; ++i) {
-            const uint32_t u = __builtin_bit_cast(uint32_t, vget<VEC>(v, i));
-            vset<VEC>(v, i, __builtin_bit_cast(float, (u + 0x7ffffu + ((u >> 20) & 1u)) & 0xfff00000u));
+            const float x = vget<VEC>(v, i), top = 0x1.ep127f;
+            const uint32_t u = __builtin_bit_cast(uint32_t, x);
+            const float r = __builtin_bit_cast(float, (u + 0x7ffffu + ((u >> 20) & 1u)) & 0xfff00000u);
+            vset<VEC>(v, i, fmaf(x, 0.0f, __builtin_amdgcn_fmed3f(r, -top, top)));
         }
     }
     return v;
