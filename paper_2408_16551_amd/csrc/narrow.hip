@@ -1,5 +1,6 @@
 // FIR and dense DFT in one kernel for narrow frames (at most 128 floats: up to 128
-// real or 64 complex channels; FP32, BF16, BF16x3).
+// real or 64 complex channels; FP32, BF16, BF16x3).  The output must lie apart from
+// the input: a block writes its channels while others still read.
 //
 // A frame of at most 128 floats is a short row of a small product: the tiles
 // of the two-kernel path are mostly padding (128 x 256 against 16 columns) and

@@ -321,6 +321,10 @@ tina_status execute_with(tina_pfb_plan_s* p, const void* d_in, int64_t n, void* 
     } else {
         const int form = p->precision;
         const int64_t ldo = p->cf == 2 ? 2 * (int64_t)p->P : (int64_t)p->P + 2;
+        // An output over the input: two kernels, whose FIR has read all of a piece
+        // before its first channel is written.
+        const uintptr_t in0 = (uintptr_t)d_in, out0 = (uintptr_t)d_out;
+        const bool apart = out0 >= in0 + (uintptr_t)fa.nchunk * 4 || in0 >= out0 + (uintptr_t)(F * ldo) * 4;
         for (int64_t c0 = 0; c0 < F; c0 += w.ch_frames) {
             const int64_t Fc = F - c0 < w.ch_frames ? F - c0 : w.ch_frames;
             fa.y = w.ws;
@@ -343,7 +347,7 @@ tina_status execute_with(tina_pfb_plan_s* p, const void* d_in, int64_t n, void* 
                     fa.q1 = (uint8_t*)w.ws + (int64_t)w.ch_frames * p->W * 2;
                 if (form_scaled(form)) fa.fexp = w.fexp;
             }
-            if (!p->fold && (p->dft_algorithm == TINA_DFT_DENSE || p->dft_algorithm == TINA_DFT_FUSED)) {
+            if (apart && !p->fold && (p->dft_algorithm == TINA_DFT_DENSE || p->dft_algorithm == TINA_DFT_FUSED)) {
                 GemmArgs na{};
                 na.B0 = p->B[0];
                 na.B1 = p->B[1];

@@ -37,3 +37,21 @@ def test_one_kernel_equals_two_bitwise(oracle, P, M, cplx, F, prec):
     st, cut = State(plan), sorted({0, n // 5, n // 5 + 3, n // 2 // P * P, n})
     parts = [plan(xd[a:b].clone(), state=st).cpu().numpy() for a, b in zip(cut[:-1], cut[1:])]
     assert np.array_equal(np.concatenate(parts), got)
+
+
+@pytest.mark.parametrize("P,M,cplx,F", [(16, 4, True, 50000), (64, 9, True, 20000), (32, 16, False, 40000)])
+def test_output_over_the_input(P, M, cplx, F):
+    """A call whose output lies over its input, at once and (the rows' start a
+    frame later) in part: the two-kernel path, bit for bit the call with both apart."""
+    from paper_2408_16551_amd.pfb import Plan
+    g = torch.Generator(device="cuda").manual_seed(P)
+    plan = Plan(P, M, "c64" if cplx else "r32", "hann", "fp32")
+    for at in (0, 1):
+        buf = torch.empty((F + 1, plan.channels_out), dtype=torch.complex64, device="cuda")
+        flat = torch.view_as_real(buf).view(-1)
+        src = torch.randn(F * P * (2 if cplx else 1), generator=g, device="cuda")
+        x = flat[: src.numel()]
+        x.copy_(src)
+        x = torch.view_as_complex(x.view(-1, 2)) if cplx else x
+        want = plan(x.clone())
+        assert torch.equal(plan(x, out=buf[at: at + F]), want)
