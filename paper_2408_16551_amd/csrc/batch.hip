@@ -243,9 +243,9 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
     for (int i = 0; i < g.count; ++i) all_exact = all_exact && w[g.first + i].plan->M == MT;
     // Frames per FIR thread, a whole number of the unit's ring blocks: the
     // ring is MT frames long, or the item's own M when mixed tap counts up to
-    // 16 run per-M units.
-    // Half of the tuned number where its units would be fewer than two per block
-    // of the persistent grid: a short step lasts as long as its last unit.
+    // 16 run per-M units; the tuned number of them, down to one where the units
+    // would be fewer than two per block of the persistent grid: a short step lasts
+    // as long as its last unit.
     int64_t all_floats = 0;
     for (int i = 0; i < g.count; ++i) all_floats += frames[g.first + i] * w[g.first + i].plan->W;
     auto frames_per_thread = [&](int ring) {
@@ -334,8 +334,8 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
         bi.fsplit_unit0 = fs0;
         bi.gfold_unit0 = gf0;
         ffu[i] = fsu[i] = gfu[i] = 0;
-        if (p->fold) {  // whole ring blocks of the item's own M (32 or 64 beyond 16 taps)
-            const int ring = p->M <= 16 ? p->M : p->M <= 32 ? 32 : 64;
+        if (p->fold) {
+            const int ring = fold_batch_ring(p->M);
             const int TF = frames_per_thread(ring);
             bi.fir_tf = TF;
             bi.fir_single = 1;  // no exponents to find for it

@@ -319,9 +319,10 @@ __device__ __forceinline__ void fir_fold_unit_own_m(const FirArgs& a, int TF, in
 }
 
 // Persistent batched form, over the table's folded FIR units, with the ring
-// unrolled for the item's own tap count up to 16, else 32 or 64 with the taps
-// beyond M switched off.  One float per thread (any alignment); two, a complex
-// sample, in the 16-bit forms (whole 128-byte lines of a part row).
+// unrolled for the item's own tap count up to 16, else for 32 or 64 taps
+// (fold_batch_ring) with those beyond M switched off.  One float per thread (any
+// alignment); two, a complex sample, in the 16-bit forms (whole 128-byte lines of a
+// part row).
 template <int MAXM, int QM>
 __global__ __launch_bounds__(256) void fir_fold_batch_kernel(const BatchTable* __restrict__ t) {
     constexpr int CV = QM == QM_NONE ? 1 : 2;  // floats per thread of complex items
@@ -341,9 +342,9 @@ __global__ __launch_bounds__(256) void fir_fold_batch_kernel(const BatchTable* _
         if (MAXM <= 16 || fa.M <= 16) {
             if (CV == 2 && fa.cf == 2) fir_fold_unit_own_m<CV, 4, 64, 1, 16, QM>(fa, b.fir_tf, blk, sm.cplx, ph);
             else fir_fold_unit_own_m<1, 4, 64, 1, 16, QM>(fa, b.fir_tf, blk, sm.one, ph);
-        } else {
-            if constexpr (MAXM == 32) fir_fold_unit<1, 4, 64, 32, false, QM>(fa, b.fir_tf, blk, sm.one, ph);
-            if constexpr (MAXM == 64) fir_fold_unit<1, 4, 64, 64, false, QM>(fa, b.fir_tf, blk, sm.one, ph);
+        } else if constexpr (MAXM > 16) {
+            if (MAXM == 32 || fold_batch_ring(fa.M) == 32) fir_fold_unit<1, 4, 64, 32, false, QM>(fa, b.fir_tf, blk, sm.one, ph);
+            else if constexpr (MAXM == 64) fir_fold_unit<1, 4, 64, 64, false, QM>(fa, b.fir_tf, blk, sm.one, ph);
         }
     }
 }
@@ -361,9 +362,9 @@ __global__ __launch_bounds__(MAXM <= 16 ? 512 : 256) void fir_fold_split_batch_k
         const int64_t blk = u - b.fsplit_unit0;
         if (MAXM <= 16 || fa.M <= 16) {
             fir_fold_unit_own_m<1, 8, GL, 1, 16, QM>(fa, b.fir_tf, blk, sm, ph);
-        } else {
-            if constexpr (MAXM == 32) fir_fold_unit<1, 8, GL, 32, false, QM>(fa, b.fir_tf, blk, sm, ph);
-            if constexpr (MAXM == 64) fir_fold_unit<1, 8, GL, 64, false, QM>(fa, b.fir_tf, blk, sm, ph);
+        } else if constexpr (MAXM > 16) {
+            if (MAXM == 32 || fold_batch_ring(fa.M) == 32) fir_fold_unit<1, 8, GL, 32, false, QM>(fa, b.fir_tf, blk, sm, ph);
+            else if constexpr (MAXM == 64) fir_fold_unit<1, 8, GL, 64, false, QM>(fa, b.fir_tf, blk, sm, ph);
         }
     }
 }

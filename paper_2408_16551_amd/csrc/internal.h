@@ -155,6 +155,12 @@ inline int fold_batch_vec(int form, int cf, int M) { return form != FORM_FP32 &&
 // of 32 in a batch with more than 16 taps (max_m), whose rings want a wave's
 // whole register file (64 lanes, eight waves: 150 to 840 registers spilled).
 inline int fold_split_cols(int max_m) { return 8 * (max_m <= 16 ? 64 : 32); }
+// Frames in the ring the batched folded FIR walks for an item of M taps, whatever
+// the launch's largest tap count.  A unit shorter than its ring takes every frame by
+// the path meant for the ends: 12 streams of 640 frames of 1024 complex channels, 20
+// taps, beside one of 40 taps took 1898 us while they walked that one's ring of 64
+// (647 with units that long, 162 without the other stream); 166 with their own.
+constexpr int fold_batch_ring(int M) { return M <= 16 ? M : M <= 32 ? 32 : 64; }
 // Tile rows and columns of the batched folded product for N columns.
 __host__ __device__ inline void fold_batch_tile(int form, int64_t N, int64_t& bm, int64_t& bj) {
     bm = form != FORM_FP32 && N == 64 ? 256 : 128;

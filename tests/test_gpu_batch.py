@@ -275,3 +275,37 @@ def test_batch_tune_then_execute_bitwise():
     torch.cuda.synchronize()
     for p, x, o, f in zip(plans, xd, outs, fw):
         assert torch.equal(o[:f], p(x))
+
+
+@pytest.mark.parametrize("prec,P,sample", [("fp32", 1024, "c64"), ("bf16x3", 1024, "r32")])
+def test_items_of_20_taps_do_not_pay_for_one_of_40(prec, P, sample):
+    """Twelve streams of 640 frames and 20 taps, beside one of 4 frames and 40 taps:
+    the same bits, and at most 3 times the time of the twelve alone (measured 1.03
+    and 1.2; 11.6 and 9.3 while their units were shorter than the ring that the
+    longer one made them walk)."""
+    from paper_2408_16551_amd.pfb import Batch, Plan
+    F = 640
+    dt = torch.complex64 if sample == "c64" else torch.float32
+    p20, p40 = (Plan(P, m, sample, "hann", prec, workspace_bytes=-1) for m in (20, 40))
+    xs = [torch.randn(P * F, dtype=dt, device="cuda") for _ in range(12)]
+    outs = [[p20.alloc_out(F) for _ in xs] for _ in range(2)]
+    alone = [(p20, x, o) for x, o in zip(xs, outs[0])]
+    beside = [(p20, x, o) for x, o in zip(xs, outs[1])]
+    beside.append((p40, torch.randn(P * 4, dtype=dt, device="cuda"), p40.alloc_out(4)))
+    b = Batch(prec, max_items=13, workspace_bytes=1 << 30)
+
+    def best(items):
+        ms = []
+        for _ in range(6):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            for _ in range(10):
+                b.execute(items)
+            e[1].record()
+            torch.cuda.synchronize()
+            ms.append(e[0].elapsed_time(e[1]))
+        return min(ms)
+
+    assert best(beside) < 3 * best(alone)
+    for a, c in zip(*outs):
+        assert torch.equal(a, c)
