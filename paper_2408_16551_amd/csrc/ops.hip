@@ -46,11 +46,12 @@ __global__ __launch_bounds__(256) void unfold_kernel(const float* __restrict__ x
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));  // four floats at any float's address
 
 // Four waves of NT column tiles (256 outputs each; complex: NT / 2 for the real
 // and NT / 2 for the imaginary parts).  LDS: the block's input, one plane per
 // part (from H samples before the block's first output, H = K - 1 rounded up to
-// a multiple of 4 so that 16-byte loads stay aligned), then the taps reversed,
+// a multiple of 4 so that a float4 of the input is one of a plane), then the taps reversed,
 // rt[15 + q] = a[H-q] with zeros around.  A 16-byte read of a lane
 // serves four MFMAs (lane group kk holds q = k0 + 4 kk + step on both sides), a
 // wave's 64 reads are 1 KB in a row, and a lane's four accumulators are four
@@ -60,7 +61,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 template <int NT, int CF>
 __global__ __launch_bounds__(256) void fir_toeplitz_kernel(const float* __restrict__ x, int64_t n,
                                                            const float* __restrict__ taps, int K, int S,
-                                                           float* __restrict__ y, bool al16) {
+                                                           float* __restrict__ y) {
     constexpr int NC = NT / CF, NBP = 4 * NC * 256;  // column tiles and block outputs per plane
     extern __shared__ __attribute__((aligned(16))) float sm[];
     const int plane = NBP + 16 * S, H = (K + 2) & ~3;
@@ -69,42 +70,66 @@ __global__ __launch_bounds__(256) void fir_toeplitz_kernel(const float* __restri
     bool odd = false;
     auto check = [&](float v) { odd |= (__builtin_bit_cast(uint32_t, v) & 0x7f800000u) == 0x7f800000u; };
     const int have = NBP + H;  // samples of a plane that an output reaches
-    if (al16 && i0 >= H && i0 + NBP <= n) {  // i0 - H is a multiple of 4
-        // The block's own samples all in flight before the first LDS store: short
-        // filters are bound by this (16 M complex samples, 14 taps: 51.5 -> 43.7 us;
-        // 2^24 real samples, 129 taps: 54.1 -> 47.4).
-        const f32x4* src = reinterpret_cast<const f32x4*>(x + (i0 - H) * CF);
-        constexpr int U = CF * NBP / 4 / 256;
-        auto put = [&](int i, f32x4 v) {
+    // A block's samples and taps are all in flight before the first LDS store, four
+    // floats a load whatever their alignment, in the first and the last block too:
+    // calls of a few blocks a CU are bound by these latencies, one after another.
+    // 8 taps, buffers in turn: 2 M complex samples 11.4 -> 9.7 us (as float4s on 16
+    // bytes alone, the edges float by float, the taps after the samples; 10.9 as one
+    // multiply-add a tap on the vector units), 65536 complex 4.8 -> 3.3 (4.3), 4 M real
+    // a float off 16 bytes 18.2 -> 10.2 (11.5).
+    const int64_t lo = (i0 - H) * CF, nf = n * CF;  // lo: a multiple of 4
+    constexpr int U = CF * NBP / 4 / 256;
+    auto tap = [&](int i) {
+        const int k = H - (i - 15);
+        return (k >= 0 && k < K) ? taps[k] : 0.0f;
+    };
+    // (Long filters in large blocks, which the products bound, load them after: 2^24
+    // real samples, 129 taps 48.7 us against 50.1, 300 taps 88.1 against 90.5; 64 taps
+    // 34.3 against 34.2.)
+    const bool early = NT < 4 || K <= 96;
+    float tap0 = early ? tap(threadIdx.x) : 0.0f;
+    auto put = [&](int i, f32x4 v) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) check(v[e]);
-            if constexpr (CF == 1) {
-                *reinterpret_cast<f32x4*>(sm + 4 * i) = v;
-            } else {
-                *reinterpret_cast<f32x2*>(sm + 2 * i) = f32x2{v[0], v[2]};
-                *reinterpret_cast<f32x2*>(sm + plane + 2 * i) = f32x2{v[1], v[3]};
-            }
-        };
+        for (int e = 0; e < 4; ++e) check(v[e]);
+        if constexpr (CF == 1) {
+            *reinterpret_cast<f32x4*>(sm + 4 * i) = v;
+        } else {
+            *reinterpret_cast<f32x2*>(sm + 2 * i) = f32x2{v[0], v[2]};
+            *reinterpret_cast<f32x2*>(sm + plane + 2 * i) = f32x2{v[1], v[3]};
+        }
+    };
+    auto stage = [&](auto fetch, auto tail) {
         f32x4 v[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = src[256 * u + threadIdx.x];
-        for (int i = 256 * U + threadIdx.x; i < CF * have / 4; i += 256) put(i, src[i]);
+        for (int u = 0; u < U; ++u) v[u] = fetch(256 * u + threadIdx.x);
+        for (int i = 256 * U + threadIdx.x; i < CF * have / 4; i += 256) put(i, tail(i, fetch(i)));
 #pragma unroll
-        for (int u = 0; u < U; ++u) put(256 * u + threadIdx.x, v[u]);
+        for (int u = 0; u < U; ++u) put(256 * u + threadIdx.x, tail(256 * u + threadIdx.x, v[u]));
+    };
+    if (lo >= 0 && lo + CF * have <= nf) {
+        stage([&](int i) -> f32x4 { return *reinterpret_cast<const f32x4_a4*>(x + lo + 4 * i); },
+              [](int, f32x4 v) { return v; });
     } else {
-        for (int i = threadIdx.x; i < CF * have; i += 256) {
-            const int p = i / CF, c = i % CF;
-            const int64_t src = i0 - H + p;
-            const float v = (src >= 0 && src < n) ? x[src * CF + c] : 0.0f;
-            check(v);
-            sm[c * plane + p] = v;
-        }
+        stage(
+            [&](int i) -> f32x4 {
+                const int64_t at = lo + 4 * i;
+                f32x4 v = {0.f, 0.f, 0.f, 0.f};
+                if (at >= 0 && at + 4 <= nf) v = *reinterpret_cast<const f32x4_a4*>(x + at);
+                return v;
+            },
+            [&](int i, f32x4 v) {
+                const int64_t at = lo + 4 * i;
+                if (at >= 0 && at < nf && at + 4 > nf)  // the input ends within
+#pragma unroll
+                    for (int e = 0; e < 3; ++e)
+                        if (at + e < nf) v[e] = x[at + e];
+                return v;
+            });
     }
     for (int i = threadIdx.x; i < CF * (plane - have); i += 256) sm[(i % CF) * plane + have + i / CF] = 0.0f;
-    for (int i = threadIdx.x; i < 16 * S + 16; i += 256) {
-        const int k = H - (i - 15);
-        rt[i] = (k >= 0 && k < K) ? taps[k] : 0.0f;
-    }
+    if (!early) tap0 = tap(threadIdx.x);
+    if ((int)threadIdx.x < 16 * S + 16) rt[threadIdx.x] = tap0;
+    for (int i = threadIdx.x + 256; i < 16 * S + 16; i += 256) rt[i] = tap(i);
     if (__syncthreads_or(odd)) {
         for (int i = threadIdx.x; i < CF * NBP; i += 256) {
             const int p = i / CF, c = i % CF;
@@ -144,10 +169,10 @@ __global__ __launch_bounds__(256) void fir_toeplitz_kernel(const float* __restri
 #pragma unroll
             for (int c = 0; c < CF; ++c) v[e * CF + c] = acc[c * NC + t][e];
         float* o = y + i * CF;
-        if (al16 && i + 4 <= n) {
+        if (i + 4 <= n) {
 #pragma unroll
             for (int e = 0; e < CF; ++e)
-                *reinterpret_cast<f32x4*>(o + 4 * e) = f32x4{v[4 * e], v[4 * e + 1], v[4 * e + 2], v[4 * e + 3]};
+                *reinterpret_cast<f32x4_a4*>(o + 4 * e) = f32x4{v[4 * e], v[4 * e + 1], v[4 * e + 2], v[4 * e + 3]};
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
@@ -168,9 +193,8 @@ size_t fir_lds(int K) {
 template <int NT, int CF>
 hipError_t launch_toeplitz(const float* x, int64_t n, const float* taps, int K, float* y, hipStream_t s) {
     constexpr int NBP = 4 * (NT / CF) * 256;
-    const bool al16 = (uintptr_t)y % 16 == 0 && (uintptr_t)x % 16 == 0;
     hipLaunchKernelGGL((fir_toeplitz_kernel<NT, CF>), dim3((unsigned)((n + NBP - 1) / NBP)), dim3(256), (fir_lds<NT, CF>(K)),
-                       s, x, n, taps, K, fir_slabs(K), y, al16);
+                       s, x, n, taps, K, fir_slabs(K), y);
     return hipGetLastError();
 }
 
@@ -230,7 +254,7 @@ tina_status tina_fir_create(int device, const double* taps, int32_t K, int32_t s
         delete f;
         return fail(TINA_ERR_OUT_OF_MEMORY, std::string("fir_create: ") + hipGetErrorString(e));
     }
-    const int top = 8192;  // the longest filter's LDS: 50 to 116 KB
+    const int top = 8192;  // the longest filter's LDS: 68 to 112 KB
     (void)hipFuncSetAttribute((const void*)fir_toeplitz_kernel<4, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fir_lds<4, 1>(top));
     (void)hipFuncSetAttribute((const void*)fir_toeplitz_kernel<1, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fir_lds<1, 1>(top));
     (void)hipFuncSetAttribute((const void*)fir_toeplitz_kernel<4, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fir_lds<4, 2>(top));
@@ -264,9 +288,9 @@ tina_status tina_fir_execute(tina_fir_t f, const void* d_x, int64_t n, void* d_y
     hipStream_t s = (hipStream_t)stream;
     // Blocks of 4096 floats from eight of them a CU on, below that of 1024 (2048
     // where complex): few large blocks a CU end together late (14 taps, buffers in
-    // turn: 4 M real samples 9.2 us against 10.9 with the large ones, 2.8 M complex
-    // 11.8 against 14.3; 5.9 M complex 21.7 either way; 40 taps 11.0 against 12.4,
-    // 13.8 against 16.2, 25.1 either way).
+    // turn, us with large and small blocks: 2.8 M complex samples 13.7 and 13.1, 4 M
+    // 16.9 and 16.2; 8 M real 15.4 and 15.6, 16.8 M 25.5 and 26.5; 40 taps: 4 M complex
+    // 18.3 and 17.7, 12 M 41.6 and 42.2, 16.8 M real 29.6 and 32.7).
     const bool big = nf >= 2048 * 4096;
     hipError_t e;
     if (f->cf == 1) e = big ? launch_toeplitz<4, 1>(x, n, f->taps, f->K, y, s) : launch_toeplitz<1, 1>(x, n, f->taps, f->K, y, s);

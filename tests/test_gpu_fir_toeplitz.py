@@ -55,3 +55,46 @@ def test_samples_that_are_not_finite_reach_their_taps_only(bad):
     assert np.array_equal(np.isnan(y[hit]), np.isnan(want))
     ok = ~np.isnan(want)
     assert np.array_equal(y[hit][ok], want[ok])
+
+
+@pytest.mark.parametrize("cplx", [False, True])
+@pytest.mark.parametrize("n", [1, 3, 5, 7, 1022, 1026, 4095, 8201, (1 << 23) + 1])
+def test_views_off_alignment_equal_aligned_bitwise(n, cplx):
+    """Inputs and outputs one to three floats off 16 bytes, lengths that end within
+    four floats: the aligned call's bits, and nothing written beside them."""
+    for K in (1, 9, 40):
+        a, f = _filter(K, cplx)
+        dt = torch.complex64 if cplx else torch.float32
+        x = torch.randn(n, dtype=dt, device="cuda")
+        want = f(x)
+        ref = _ref(x.cpu().numpy(), a)
+        assert np.linalg.norm(want.cpu().numpy() - ref) <= 1e-5 * np.linalg.norm(ref)
+        for at in (1,) if cplx else (1, 2, 3):
+            xo, yo = torch.empty(n + 4, dtype=dt, device="cuda"), torch.full((n + 5,), 7.0, dtype=dt, device="cuda")
+            xo.fill_(float("nan"))
+            xo[at:at + n] = x
+            f(xo[at:at + n], out=yo[at:at + n])
+            assert torch.equal(yo[at:at + n], want)
+            assert (yo[:at] == 7).all() and (yo[at + n:] == 7).all()
+
+
+def test_views_off_alignment_cost_little_more():
+    """4 M real samples, 16 taps, both buffers a float off 16 bytes: at most 1.4
+    times the aligned call (measured 1.07; 1.78 where such calls went float by float)."""
+    n = 1 << 22
+    _, f = _filter(16, False)
+    bufs = [[torch.randn(n + 4, device="cuda") for _ in range(2)] for _ in range(24)]
+
+    def best(at):
+        us = []
+        for _ in range(8):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            for x, y in bufs:
+                f(x[at:at + n], out=y[at:at + n])
+            e[1].record()
+            torch.cuda.synchronize()
+            us.append(e[0].elapsed_time(e[1]))
+        return min(us)
+
+    assert best(1) < 1.4 * best(0)
