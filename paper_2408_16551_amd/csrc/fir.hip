@@ -181,10 +181,11 @@ hipError_t launch_fir(FirArgs& a, hipStream_t s) {
 hipError_t launch_fir_batch(const BatchTable* t, int max_m, bool all_exact, int qmode, int grid, hipStream_t s,
                             bool frame_stage) {
     if (qmode_frame_scaled(qmode)) {
-        // Items with whole frame rows of 1024 threads: one pass (frame stage);
-        // the others as in launch_fir: maxima, exponents, codes.
+        // Items with whole frame rows of 1024 threads: one pass (frame stage; FP8
+        // frames that long are folded); the others as in launch_fir: maxima,
+        // exponents, codes.
         hipError_t e = hipSuccess;
-        if (frame_stage) e = launch_fir_frame_batch(t, qmode, grid / 4, s);  // one 1024-thread block per CU
+        if (frame_stage && qmode != QM_FP8F) e = launch_fir_frame_batch(t, qmode, grid / 4, s);  // one 1024-thread block per CU
         if (e != hipSuccess) return e;
         e = launch_fir_batch_mode_amaxonly(t, max_m, all_exact, grid, s);
         if (e != hipSuccess) return e;

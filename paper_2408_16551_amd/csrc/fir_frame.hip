@@ -205,23 +205,18 @@ int fir_frame_vec(const FirArgs& a) {
 }
 
 int fir_frame_batch_vec(const FirArgs& a) {
-    if (!qmode_frame_scaled(a.qmode)) return 0;
+    if (a.qmode != QM_FP16F && a.qmode != QM_FP16FX2) return 0;  // (FP8 frames this long are folded)
     const int vec = a.W == 1024 ? 1 : (a.W == 2048 ? 2 : (a.W == 4096 ? 4 : 0));
     if (vec == 0 || a.M < 1 || a.M > (vec == 4 ? 8 : 16)) return 0;
     auto aligned = [](const void* p, int bytes) { return ((uintptr_t)p % bytes) == 0; };
     if (a.plen % vec != 0 || !aligned(a.chunk, 4 * vec) || (a.prefix && !aligned(a.prefix, 4 * vec))) return 0;
-    if (a.qmode == QM_FP8F) {
-        if (!aligned(a.q, 4) || a.ldq % 4 != 0) return 0;
-    } else if (!aligned(a.q, 2 * vec) || (a.q1 && !aligned(a.q1, 2 * vec)) || a.ldq % vec != 0) {
-        return 0;
-    }
+    if (!aligned(a.q, 2 * vec) || (a.q1 && !aligned(a.q1, 2 * vec)) || a.ldq % vec != 0) return 0;
     return vec;
 }
 
 
 hipError_t launch_fir_frame_batch(const BatchTable* t, int qmode, int grid, hipStream_t s) {
     switch (qmode) {
-        case QM_FP8F: hipLaunchKernelGGL(fir_frame_batch_kernel<QM_FP8F>, dim3(grid), dim3(kFrameMaxThreads), 0, s, t); break;
         case QM_FP16F: hipLaunchKernelGGL(fir_frame_batch_kernel<QM_FP16F>, dim3(grid), dim3(kFrameMaxThreads), 0, s, t); break;
         case QM_FP16FX2: hipLaunchKernelGGL(fir_frame_batch_kernel<QM_FP16FX2>, dim3(grid), dim3(kFrameMaxThreads), 0, s, t); break;
         default: return hipErrorInvalidValue;

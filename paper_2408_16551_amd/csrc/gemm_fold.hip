@@ -516,8 +516,8 @@ void fold_gemm_batch_kernel(const BatchTable* __restrict__ t) {
     fold_batch_tile(FORM, g.N, bm, bj);
     fold_place(u - t->items[it].gfold_unit0, (rows + bm - 1) / bm, (g.N + bj - 1) / bj, bm, bj, m0, n0);
     if (!F32 && g.N == 64) {
+        // 256 channels: whole frames (16-bit forms split from 2048 on).
         if (g.real_pack) fold_tile<FORM, REAL, F32 ? 2 : 4, 2, false>(g, m0, n0, lds, nullptr);
-        else if (g.split) fold_tile<FORM, SPLIT, F32 ? 2 : 4, 2, false>(g, m0, n0, lds, nullptr);
         else fold_tile<FORM, CPLX, F32 ? 2 : 4, 2, false>(g, m0, n0, lds, nullptr);
     } else {
         if (g.real_pack) fold_tile<FORM, REAL, 2, F32 ? 2 : 4, false>(g, m0, n0, lds, nullptr);
@@ -557,6 +557,7 @@ hipError_t launch_fold_form(const GemmArgs& g, hipStream_t s) {
         return hipGetLastError();
     }
     if constexpr (FORM == FORM_FP32) return launch_fold_wide<FORM, MODE, 2, 2>(g, s);
+    else if constexpr (MODE == SPLIT) return launch_fold_wide<FORM, MODE, 2, 4>(g, s);  // from 2048 channels on
     else return g.N == 64 ? launch_fold_wide<FORM, MODE, 4, 2>(g, s) : launch_fold_wide<FORM, MODE, 2, 4>(g, s);
 }
 

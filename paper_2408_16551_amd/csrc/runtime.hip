@@ -190,7 +190,7 @@ tina_status tina_pfb_plan(const tina_pfb_desc* d, tina_pfb_plan_t* out) {
         if (ws_bytes > 0 && p->ch_frames < 1) p->ch_frames = 1;
         if (p->ch_frames > 0 && hipMalloc(&p->ws, ws_rows * p->ch_frames * p->W * sizeof(float)) != hipSuccess)
             return bail(TINA_ERR_OUT_OF_MEMORY, "plan: workspace allocation");
-        if (p->ch_frames > 0 && form_scaled(form)) {
+        if (p->ch_frames > 0 && form_scaled(form) && !p->fold) {
             p->amax_parts_cap = p->W / 32 > 1 ? p->W / 32 : 1;  // the most parts: one per 32 lanes at VEC = 1
             if (hipMalloc(&p->amax, p->ch_frames * p->amax_parts_cap * sizeof(float)) != hipSuccess ||
                 hipMalloc(&p->fexp, p->ch_frames * sizeof(int32_t)) != hipSuccess)
@@ -331,7 +331,7 @@ tina_status execute_with(tina_pfb_plan_s* p, const void* d_in, int64_t n, void* 
             fa.ldy = p->W;
             fa.g0 = c0;
             fa.F = Fc;
-            fa.amax = form_scaled(form) ? w.amax : nullptr;
+            fa.amax = form_scaled(form) && !p->fold ? w.amax : nullptr;
             // Operand-form FIR output in the FP32 workspace (4 bytes per float):
             // E4M3 codes (then the block scales), or the 16-bit piece(s) one
             // after the other; per-frame scaled forms also keep the frames'
@@ -345,7 +345,7 @@ tina_status execute_with(tina_pfb_plan_s* p, const void* d_in, int64_t n, void* 
                 if (form_mx(form)) fa.qs = (uint8_t*)w.ws + mx_codes_bytes(w.ch_frames, p->W);
                 if (form == TINA_PREC_BF16X3 || form == TINA_PREC_FP16X3)
                     fa.q1 = (uint8_t*)w.ws + (int64_t)w.ch_frames * p->W * 2;
-                if (form_scaled(form)) fa.fexp = w.fexp;
+                if (form_scaled(form) && !p->fold) fa.fexp = w.fexp;
             }
             if (apart && !p->fold && (p->dft_algorithm == TINA_DFT_DENSE || p->dft_algorithm == TINA_DFT_FUSED)) {
                 GemmArgs na{};

@@ -138,3 +138,19 @@ def test_split_frames_match_oracle_and_batch(oracle, P, M, F, prec):
         Batch(prec, max_items=2, workspace_bytes=1 << 28).execute(items)
         assert np.array_equal(items[0][2].cpu().numpy(), got)
         assert np.array_equal(items[1][2].cpu().numpy(), other(z).cpu().numpy())
+
+
+@pytest.mark.gpu
+def test_folded_fp8_plan_holds_no_scale_workspace():
+    """1 GiB of workspace: the plan's device memory is BF16's (within 4 MiB of
+    allocation granularity), without 36 MiB of frame maxima and exponents."""
+    from paper_2408_16551_amd.pfb import Plan
+    Plan(1024, 4, "r32", "hann", "bf16", workspace_bytes=1 << 20).close()
+    used = {}
+    for prec in ("bf16", "fp8"):
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        plan = Plan(1024, 4, "r32", "hann", prec, workspace_bytes=1 << 30)
+        used[prec] = before - torch.cuda.mem_get_info()[0]
+        plan.close()
+    assert used["bf16"] >= 1000 << 20 and abs(used["fp8"] - used["bf16"]) <= 4 << 20
