@@ -1,4 +1,7 @@
-// Folded polyphase FIR (values rounded to E4M3, parts in bf16): see fir_fold.h.
+// Folded polyphase FIR (values rounded to E4M3's four significant bits, parts in
+// bf16): see fir_fold.h.  Instantiated apart from BF16: with the rounding behind a
+// branch of the same kernels both forms lose where the ring is long (2048 complex
+// channels, 12 taps, 2^25 samples 260 -> 317 us; 512, 24 taps, 2^24 200 -> 281).
 #include "fir_fold.h"
 
 namespace tina {
