@@ -340,13 +340,13 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
             bi.fir_tf = TF;
             bi.fir_single = 1;  // no exponents to find for it
             const int64_t runs = (F + TF - 1) / TF;
-            if (p->split) fsu[i] = runs * (p->W / fold_split_cols(max_m));
+            if (p->split) fsu[i] = runs * (p->W / kFoldSplitCols);
             else ffu[i] = runs * (p->W / (256 * fold_batch_vec(b->form, p->cf, p->M)));
             int64_t bm, bj;
             fold_batch_tile(b->form, p->N, bm, bj);
             gfu[i] = (F * p->cf * (p->split ? 2 : 1) + bm - 1) / bm * ((p->N + bj - 1) / bj);
             fu[i] = ru[i] = 0;
-            fc[i] = (double)TF * ring;
+            fc[i] = (double)TF * p->M;
         } else if (bi.fir_single) {
             const int TF = p->M * ((b->frame_tf_target + p->M - 1) / p->M);
             bi.fir_tf = TF;

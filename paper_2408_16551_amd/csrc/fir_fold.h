@@ -203,57 +203,67 @@ __device__ __forceinline__ void fold_store_split(const FirArgs& a,
     }
 }
 
-// One unit: column block and run of logical block `blk`.  Every condition on
-// frames is the same for the whole block, so all its threads meet at each
-// barrier.  ph: the LDS buffer of the next phase (a buffer is written again
+// Place of a block's thread in the frame: its column group's first float j0, and
+// its floats' place in an LDS row.
+template <int VEC, int NG, int GL>
+struct FoldPlace {
+    int c0, j0, slot;
+    __device__ __forceinline__ FoldPlace(const FirArgs& a, int cb) {
+        using G = FoldGeom<VEC, NG, GL>;
+        // Floats that fold four-fold (a frame, or half of one) and a quarter of them.
+        const int span = NG == 8 ? a.W / 2 : a.W, quarter = span / 4;
+        const int g = threadIdx.x / GL, x = (threadIdx.x % GL) * VEC, gg = g & 3;
+        c0 = cb * G::GF;
+        j0 = (g >> 2) * span + (gg == 0 ? c0 : gg == 1 ? 2 * quarter - c0 - G::GF : gg == 2 ? 2 * quarter + c0 : span - c0 - G::GF) + x;
+        slot = g * G::GF + x;
+    }
+};
+
+// Column blocks of a frame (a power of two).
+template <int VEC, int NG, int GL>
+__host__ __device__ __forceinline__ int fold_col_blocks(const FirArgs& a) {
+    return a.W / NG / FoldGeom<VEC, NG, GL>::GF;
+}
+
+// One unit of up to 16 taps: column block and run of logical block `blk`.  Every
+// condition on frames is the same for the whole block, so all its threads meet at
+// each barrier.  ph: the LDS buffer of the next phase (a buffer is written again
 // two phases later, after every thread has passed the barrier in between, so
 // one barrier per phase is enough, across units too).
-template <int VEC, int NG, int GL, int MT, bool EXACT, int QM>
+template <int VEC, int NG, int GL, int MT, int QM>
 __device__ __forceinline__ void fir_fold_unit(const FirArgs& a, int TF, int64_t blk, FoldSmem<VEC, NG, GL>& sm, int& ph) {
     using V = typename VecT<VEC>::T;
     using G = FoldGeom<VEC, NG, GL>;
     constexpr int SB = G::SB < MT ? G::SB : MT;
-    // Floats that fold four-fold (a frame, or half of one), a quarter of them,
-    // and the column blocks of a quarter: powers of two.
-    const int span = NG == 8 ? a.W / 2 : a.W, quarter = span / 4, ncb = quarter / G::GF;
-    const int cb = (int)(blk & (ncb - 1));
+    const int ncb = fold_col_blocks<VEC, NG, GL>(a);
     const int64_t run = blk / ncb;
     const int64_t f_begin = run * TF;
     if (f_begin >= a.F) return;
     const int64_t f_end = min(a.F, f_begin + TF);
-    const int M = EXACT ? MT : a.M;
-    const int c0 = cb * G::GF;
-    const int g = threadIdx.x / GL, x = (threadIdx.x % GL) * VEC, gg = g & 3;
-    const int j0 = (g >> 2) * span + (gg == 0 ? c0 : gg == 1 ? 2 * quarter - c0 - G::GF : gg == 2 ? 2 * quarter + c0 : span - c0 - G::GF) + x;
-    const int slot = g * G::GF + x;  // this thread's floats in an LDS row
+    const FoldPlace<VEC, NG, GL> at(a, (int)(blk & (ncb - 1)));
+    const int j0 = at.j0, slot = at.slot;
 
     V tp[MT];
 #pragma unroll
-    for (int m = 0; m < MT; ++m) tp[m] = (EXACT || m < M) ? load_taps<VEC>(a, M, m, j0) : V(0.0f);
+    for (int m = 0; m < MT; ++m) tp[m] = load_taps<VEC>(a, MT, m, j0);
     V win[MT];  // ring of input frames, as in fir_unit
     auto direct = [&](int64_t f) {
         V acc = V(0.0f);
-        if constexpr (EXACT) {
-            // All its loads in flight before the first FMA (195 frames of 1024
-            // channels, 12 taps, half of them such: 10 us; 20 us where the
-            // compiler puts waits between the loads).
-            V in[MT];
+        // All its loads in flight before the first FMA (195 frames of 1024
+        // channels, 12 taps, half of them such: 10 us; 20 us where the
+        // compiler puts waits between the loads).
+        V in[MT];
 #pragma unroll
-            for (int m = 0; m < MT; ++m) in[m] = load_frame<VEC, true>(a, a.g0 + f - m, j0);
-            __builtin_amdgcn_sched_barrier(0);
+        for (int m = 0; m < MT; ++m) in[m] = load_frame<VEC, true>(a, a.g0 + f - m, j0);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int m = 0; m < MT; ++m) acc = __builtin_elementwise_fma(tp[m], in[m], acc);
-        } else {
-#pragma unroll
-            for (int m = 0; m < MT; ++m)
-                if (m < M) acc = __builtin_elementwise_fma(tp[m], load_frame<VEC, true>(a, a.g0 + f - m, j0), acc);
-        }
+        for (int m = 0; m < MT; ++m) acc = __builtin_elementwise_fma(tp[m], in[m], acc);
         return acc;
     };
     auto flush = [&](int64_t f0, int cnt) {
         __syncthreads();
-        if constexpr (NG == 8) fold_store_split<VEC, GL, QM>(a, sm.ys[ph], f0, cnt, c0);
-        else fold_store<VEC, GL, QM>(a, sm.ys[ph], f0, cnt, c0);
+        if constexpr (NG == 8) fold_store_split<VEC, GL, QM>(a, sm.ys[ph], f0, cnt, at.c0);
+        else fold_store<VEC, GL, QM>(a, sm.ys[ph], f0, cnt, at.c0);
         ph ^= 1;
     };
     // Frames [f0, f1) straight from their input frames: blocks that straddle
@@ -277,8 +287,7 @@ __device__ __forceinline__ void fir_fold_unit(const FirArgs& a, int TF, int64_t 
         }
         if (!ring_ok) {
 #pragma unroll
-            for (int d = 1; d < MT; ++d)
-                win[MT - d] = (EXACT || d < M) ? load_frame<VEC, false>(a, a.g0 + fb - d, j0) : V(0.0f);
+            for (int d = 1; d < MT; ++d) win[MT - d] = load_frame<VEC, false>(a, a.g0 + fb - d, j0);
         }
         ring_ok = true;
         const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.chunk + eu, (a.nchunk - eu) * 4);
@@ -295,7 +304,7 @@ __device__ __forceinline__ void fir_fold_unit(const FirArgs& a, int TF, int64_t 
                 const int u = sb + i;
                 if (u >= MT) continue;
                 win[u] = in[i];
-                *reinterpret_cast<V*>(&sm.ys[ph][i][slot]) = fold_value<VEC, QM>(fir_point<VEC, MT, EXACT>(tp, win, u, M));
+                *reinterpret_cast<V*>(&sm.ys[ph][i][slot]) = fold_value<VEC, QM>(fir_point<VEC, MT, true>(tp, win, u, MT));
             }
             flush(fb + sb, MT - sb < SB ? MT - sb : SB);
         }
@@ -303,27 +312,103 @@ __device__ __forceinline__ void fir_fold_unit(const FirArgs& a, int TF, int64_t 
     slow(fb, f_end);
 }
 
-template <int VEC, int NG, int GL, int MT, bool EXACT, int QM>
+// One unit of more than 16 taps, any number of them: kFoldLong frames at a time,
+// their sums in registers, tap after tap, while the input frames they meet move
+// through a ring of that length, one older frame a tap (1 + (M - 1) / 32 reads a
+// float, all but one of them from L2).  Taps and frames are loaded kFoldAhead taps
+// ahead.  In place of rings of 32 and 64 taps in registers, those beyond M behind a
+// condition each (512 registers, 584 scalar ones spilled), 1024 real channels, BF16,
+// 2^25 samples, the whole call: 24 taps 204 -> 111 us, 64 taps 3510 -> 144 (94 with 16
+// taps; 237 and 174 with the plain product).
+constexpr int kFoldLong = 32, kFoldAhead = 8;
+template <int NG, int GL, int QM>
+__device__ __forceinline__ void fir_fold_unit_long(const FirArgs& a, int TF, int64_t blk, FoldSmem<1, NG, GL>& sm, int& ph) {
+    using G = FoldGeom<1, NG, GL>;
+    constexpr int B = kFoldLong, C = kFoldAhead, SB = G::SB;
+    const int ncb = fold_col_blocks<1, NG, GL>(a);
+    const int64_t run = blk / ncb;
+    const int64_t f_begin = run * TF;
+    if (f_begin >= a.F) return;
+    const int64_t f_end = min(a.F, f_begin + TF);
+    const FoldPlace<1, NG, GL> at(a, (int)(blk & (ncb - 1)));
+    const int j0 = at.j0, M = a.M;
+    for (int64_t fb = f_begin; fb < f_end; fb += B) {
+        const int cnt = (int)min((int64_t)B, f_end - fb);
+        float ring[B], acc[B], t[C], x[C], tn[C], xn[C];
+        auto ahead = [&](int m) {
+#pragma unroll
+            for (int i = 0; i < C; ++i) {
+                const int k = min(m + i, M - 1);  // past the last: reads in range, not used
+                tn[i] = load_taps<1>(a, M, k, j0);
+                xn[i] = load_frame<1, false>(a, a.g0 + fb - k, j0);
+            }
+        };
+        ahead(0);
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            ring[u] = load_frame<1, false>(a, a.g0 + fb + min(u, cnt - 1), j0);
+            acc[u] = -0.0f;  // the first multiply-add gives the product itself
+        }
+        // Tap m meets frame fb + u - m for output u, in slot (u - m) mod B.
+        for (int m0 = 0; m0 < M; m0 += B) {
+#pragma unroll
+            for (int s = 0; s < B; ++s) {
+                if (s % C == 0) {
+                    if (m0 + s >= M) break;
+#pragma unroll
+                    for (int i = 0; i < C; ++i) {
+                        t[i] = tn[i];
+                        x[i] = xn[i];
+                    }
+                    ahead(m0 + s + C);
+                }
+                if (m0 + s < M) {
+                    ring[(B - s) % B] = x[s % C];
+#pragma unroll
+                    for (int u = 0; u < B; ++u) acc[u] = fmaf(t[s % C], ring[(u - s + B) % B], acc[u]);
+                }
+            }
+        }
+#pragma unroll
+        for (int sb = 0; sb < B; sb += SB) {
+            if (sb >= cnt) break;
+#pragma unroll
+            for (int i = 0; i < SB; ++i) sm.ys[ph][i][at.slot] = fold_value<1, QM>(acc[sb + i]);
+            __syncthreads();
+            const int n = min(SB, cnt - sb);
+            if constexpr (NG == 8) fold_store_split<1, GL, QM>(a, sm.ys[ph], fb + sb, n, at.c0);
+            else fold_store<1, GL, QM>(a, sm.ys[ph], fb + sb, n, at.c0);
+            ph ^= 1;
+        }
+    }
+}
+
+template <int VEC, int NG, int GL, int MT, int QM>
 __global__ __launch_bounds__((FoldGeom<VEC, NG, GL>::NTH)) void fir_fold_kernel(FirArgs a, int TF) {
     __shared__ __attribute__((aligned(16))) FoldSmem<VEC, NG, GL> sm;
     int ph = 0;
-    fir_fold_unit<VEC, NG, GL, MT, EXACT, QM>(a, TF, xcd_logical_block(blockIdx.x, gridDim.x), sm, ph);
+    fir_fold_unit<VEC, NG, GL, MT, QM>(a, TF, xcd_logical_block(blockIdx.x, gridDim.x), sm, ph);
+}
+template <int NG, int GL, int QM>
+__global__ __launch_bounds__((FoldGeom<1, NG, GL>::NTH)) void fir_fold_long_kernel(FirArgs a) {
+    __shared__ __attribute__((aligned(16))) FoldSmem<1, NG, GL> sm;
+    int ph = 0;
+    fir_fold_unit_long<NG, GL, QM>(a, kFoldLong, xcd_logical_block(blockIdx.x, gridDim.x), sm, ph);
 }
 
 template <int VEC, int NG, int GL, int M0, int MT, int QM>
 __device__ __forceinline__ void fir_fold_unit_own_m(const FirArgs& a, int TF, int64_t blk, FoldSmem<VEC, NG, GL>& sm, int& ph) {
     if constexpr (M0 <= MT) {
-        if (a.M == M0) fir_fold_unit<VEC, NG, GL, M0, true, QM>(a, TF, blk, sm, ph);
+        if (a.M == M0) fir_fold_unit<VEC, NG, GL, M0, QM>(a, TF, blk, sm, ph);
         else fir_fold_unit_own_m<VEC, NG, GL, M0 + 1, MT, QM>(a, TF, blk, sm, ph);
     }
 }
 
-// Persistent batched form, over the table's folded FIR units, with the ring
-// unrolled for the item's own tap count up to 16, else for 32 or 64 taps
-// (fold_batch_ring) with those beyond M switched off.  One float per thread (any
-// alignment); two, a complex sample, in the 16-bit forms (whole 128-byte lines of a
-// part row).
-template <int MAXM, int QM>
+// Persistent batched form, over the table's folded FIR units, each with its item's
+// tap count.  LONG: items of more than 16 taps among them (apart, for the registers).
+// One float per thread (any alignment); two, a complex sample, in the 16-bit forms
+// (whole 128-byte lines of a part row).
+template <bool LONG, int QM>
 __global__ __launch_bounds__(256) void fir_fold_batch_kernel(const BatchTable* __restrict__ t) {
     constexpr int CV = QM == QM_NONE ? 1 : 2;  // floats per thread of complex items
     __shared__ __attribute__((aligned(16))) union {
@@ -339,19 +424,14 @@ __global__ __launch_bounds__(256) void fir_fold_batch_kernel(const BatchTable* _
         const BatchItem& b = t->items[it];
         const FirArgs fa = b.fir;
         const int64_t blk = u - b.ffold_unit0;
-        if (MAXM <= 16 || fa.M <= 16) {
-            if (CV == 2 && fa.cf == 2) fir_fold_unit_own_m<CV, 4, 64, 1, 16, QM>(fa, b.fir_tf, blk, sm.cplx, ph);
-            else fir_fold_unit_own_m<1, 4, 64, 1, 16, QM>(fa, b.fir_tf, blk, sm.one, ph);
-        } else if constexpr (MAXM > 16) {
-            if (MAXM == 32 || fold_batch_ring(fa.M) == 32) fir_fold_unit<1, 4, 64, 32, false, QM>(fa, b.fir_tf, blk, sm.one, ph);
-            else if constexpr (MAXM == 64) fir_fold_unit<1, 4, 64, 64, false, QM>(fa, b.fir_tf, blk, sm.one, ph);
-        }
+        if (LONG && fa.M > 16) fir_fold_unit_long<4, 64, QM>(fa, b.fir_tf, blk, sm.one, ph);
+        else if (CV == 2 && fa.cf == 2) fir_fold_unit_own_m<CV, 4, 64, 1, 16, QM>(fa, b.fir_tf, blk, sm.cplx, ph);
+        else fir_fold_unit_own_m<1, 4, 64, 1, 16, QM>(fa, b.fir_tf, blk, sm.one, ph);
     }
 }
-template <int MAXM, int QM>
-__global__ __launch_bounds__(MAXM <= 16 ? 512 : 256) void fir_fold_split_batch_kernel(const BatchTable* __restrict__ t) {
-    constexpr int GL = MAXM <= 16 ? 64 : 32;
-    __shared__ __attribute__((aligned(16))) FoldSmem<1, 8, GL> sm;
+template <bool LONG, int QM>
+__global__ __launch_bounds__(512) void fir_fold_split_batch_kernel(const BatchTable* __restrict__ t) {
+    __shared__ __attribute__((aligned(16))) FoldSmem<1, 8, 64> sm;
     int ph = 0;
     const int x = blockIdx.x & 7, i = blockIdx.x >> 3, nbx = gridDim.x >> 3;
     const int64_t end = t->fsplit_bounds[x + 1];
@@ -360,32 +440,35 @@ __global__ __launch_bounds__(MAXM <= 16 ? 512 : 256) void fir_fold_split_batch_k
         const BatchItem& b = t->items[it];
         const FirArgs fa = b.fir;
         const int64_t blk = u - b.fsplit_unit0;
-        if (MAXM <= 16 || fa.M <= 16) {
-            fir_fold_unit_own_m<1, 8, GL, 1, 16, QM>(fa, b.fir_tf, blk, sm, ph);
-        } else if constexpr (MAXM > 16) {
-            if (MAXM == 32 || fold_batch_ring(fa.M) == 32) fir_fold_unit<1, 8, GL, 32, false, QM>(fa, b.fir_tf, blk, sm, ph);
-            else if constexpr (MAXM == 64) fir_fold_unit<1, 8, GL, 64, false, QM>(fa, b.fir_tf, blk, sm, ph);
-        }
+        if (LONG && fa.M > 16) fir_fold_unit_long<8, 64, QM>(fa, b.fir_tf, blk, sm, ph);
+        else fir_fold_unit_own_m<1, 8, 64, 1, 16, QM>(fa, b.fir_tf, blk, sm, ph);
     }
 }
 
-template <int VEC, int NG, int GL, int MT, bool EXACT, int QM>
+template <int VEC, int NG, int GL, int MT, int QM>
 hipError_t launch_fold_one(const FirArgs& a, hipStream_t s) {
     using G = FoldGeom<VEC, NG, GL>;
-    const int ncb = a.W / NG / G::GF;
+    const int ncb = fold_col_blocks<VEC, NG, GL>(a);
     // Frames per block: whole ring blocks, two of them (at least 16 frames) so
     // that the halo stays small; one while that leaves CUs without a block.
     int TF = 2 * MT < 16 ? ((16 + MT - 1) / MT) * MT : 2 * MT;
     while (TF > MT && TF > 4 && (a.F + TF - 1) / TF * ncb < 512) TF -= MT;
     const int64_t runs = (a.F + TF - 1) / TF;
-    hipLaunchKernelGGL((fir_fold_kernel<VEC, NG, GL, MT, EXACT, QM>), dim3((unsigned)(runs * ncb)), dim3(G::NTH), 0, s, a, TF);
+    hipLaunchKernelGGL((fir_fold_kernel<VEC, NG, GL, MT, QM>), dim3((unsigned)(runs * ncb)), dim3(G::NTH), 0, s, a, TF);
+    return hipGetLastError();
+}
+
+template <int NG, int GL, int QM>
+hipError_t launch_fold_long(const FirArgs& a, hipStream_t s) {
+    const int64_t blocks = (a.F + kFoldLong - 1) / kFoldLong * fold_col_blocks<1, NG, GL>(a);
+    hipLaunchKernelGGL((fir_fold_long_kernel<NG, GL, QM>), dim3((unsigned)blocks), dim3(FoldGeom<1, NG, GL>::NTH), 0, s, a);
     return hipGetLastError();
 }
 
 template <int VEC, int NG, int GL, int M0, int MTOP, int QM>
 hipError_t launch_fold_m(const FirArgs& a, hipStream_t s) {
     if constexpr (M0 <= MTOP) {
-        if (a.M == M0) return launch_fold_one<VEC, NG, GL, M0, true, QM>(a, s);
+        if (a.M == M0) return launch_fold_one<VEC, NG, GL, M0, QM>(a, s);
         return launch_fold_m<VEC, NG, GL, M0 + 1, MTOP, QM>(a, s);
     }
     return hipErrorInvalidValue;
@@ -403,9 +486,7 @@ hipError_t launch_fold_qm(const FirArgs& a, hipStream_t s) {
         // taps, FP32: 131 us; 156 with four, 184 with two in 512 threads).
         if (a.M <= 8 && al16) return launch_fold_m<4, 8, 32, 1, 8, QM>(a, s);
         if (a.M <= 16) return launch_fold_m<1, 8, 64, 1, 16, QM>(a, s);
-        if (a.M <= 32) return launch_fold_one<1, 8, 32, 32, false, QM>(a, s);
-        if (a.M <= 64) return launch_fold_one<1, 8, 32, 64, false, QM>(a, s);
-        return hipErrorInvalidValue;
+        return launch_fold_long<8, 64, QM>(a, s);
     }
     if (a.M <= 8 && al16 && a.W >= 1024) return launch_fold_m<4, 4, 64, 1, 8, QM>(a, s);
     // 16-bit complex rows: 128 lanes a group, for whole lines as above (1024
@@ -413,22 +494,18 @@ hipError_t launch_fold_qm(const FirArgs& a, hipStream_t s) {
     // half lines, 129 us; FP32 rows the same either way).
     if (QM != QM_NONE && a.cf == 2 && a.M <= 16) return launch_fold_m<1, 4, 128, 1, 16, QM>(a, s);
     if (a.M <= 16) return launch_fold_m<1, 4, 64, 1, 16, QM>(a, s);
-    if (a.M <= 32) return launch_fold_one<1, 4, 64, 32, false, QM>(a, s);
-    if (a.M <= 64) return launch_fold_one<1, 4, 64, 64, false, QM>(a, s);
-    return hipErrorInvalidValue;
+    return launch_fold_long<4, 64, QM>(a, s);
 }
 
 template <int QM>
 hipError_t launch_fold_batch_qm(const BatchTable* t, int max_m, bool split, int grid, hipStream_t s) {
     auto go = [&](auto tag) {
-        constexpr int MAXM = decltype(tag)::value;
-        if (split) hipLaunchKernelGGL((fir_fold_split_batch_kernel<MAXM, QM>), dim3(grid), dim3(MAXM <= 16 ? 512 : 256), 0, s, t);
-        else hipLaunchKernelGGL((fir_fold_batch_kernel<MAXM, QM>), dim3(grid), dim3(256), 0, s, t);
+        constexpr bool LONG = decltype(tag)::value;
+        if (split) hipLaunchKernelGGL((fir_fold_split_batch_kernel<LONG, QM>), dim3(grid), dim3(512), 0, s, t);
+        else hipLaunchKernelGGL((fir_fold_batch_kernel<LONG, QM>), dim3(grid), dim3(256), 0, s, t);
         return hipGetLastError();
     };
-    if (max_m <= 16) return go(std::integral_constant<int, 16>{});
-    if (max_m <= 32) return go(std::integral_constant<int, 32>{});
-    return go(std::integral_constant<int, 64>{});
+    return max_m <= 16 ? go(std::false_type{}) : go(std::true_type{});
 }
 
 }  // namespace

@@ -151,16 +151,11 @@ hipError_t launch_fold_operand(void* piece0, void* piece1, int P, int form, hipS
 hipError_t launch_fold_tables(float* tw, float* ct, float* ones, int P, float scale, hipStream_t s);
 // Floats per thread of the batched folded FIR (its column blocks are 256 times as wide).
 inline int fold_batch_vec(int form, int cf, int M) { return form != FORM_FP32 && cf == 2 && M <= 16 ? 2 : 1; }
-// ... and floats per column block of a split item: eight groups of 64 lanes, or
-// of 32 in a batch with more than 16 taps (max_m), whose rings want a wave's
-// whole register file (64 lanes, eight waves: 150 to 840 registers spilled).
-inline int fold_split_cols(int max_m) { return 8 * (max_m <= 16 ? 64 : 32); }
-// Frames in the ring the batched folded FIR walks for an item of M taps, whatever
-// the launch's largest tap count.  A unit shorter than its ring takes every frame by
-// the path meant for the ends: 12 streams of 640 frames of 1024 complex channels, 20
-// taps, beside one of 40 taps took 1898 us while they walked that one's ring of 64
-// (647 with units that long, 162 without the other stream); 166 with their own.
-constexpr int fold_batch_ring(int M) { return M <= 16 ? M : M <= 32 ? 32 : 64; }
+// ... and floats per column block of a split item: eight groups of 64 lanes.
+constexpr int kFoldSplitCols = 8 * 64;
+// Frames that the batched folded FIR takes at a time for an item of M taps; its
+// units are whole numbers of them, whatever the launch's other items.
+constexpr int fold_batch_ring(int M) { return M <= 16 ? M : 32; }
 // Tile rows and columns of the batched folded product for N columns.
 __host__ __device__ inline void fold_batch_tile(int form, int64_t N, int64_t& bm, int64_t& bj) {
     bm = form != FORM_FP32 && N == 64 ? 256 : 128;

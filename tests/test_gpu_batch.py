@@ -280,9 +280,9 @@ def test_batch_tune_then_execute_bitwise():
 @pytest.mark.parametrize("prec,P,sample", [("fp32", 1024, "c64"), ("bf16x3", 1024, "r32")])
 def test_items_of_20_taps_do_not_pay_for_one_of_40(prec, P, sample):
     """Twelve streams of 640 frames and 20 taps, beside one of 4 frames and 40 taps:
-    the same bits, and at most 3 times the time of the twelve alone (measured 1.03
-    and 1.2; 11.6 and 9.3 while their units were shorter than the ring that the
-    longer one made them walk)."""
+    the same bits, and at most 3 times the time of the twelve alone (measured 1.0; 11.6
+    and 9.3 while their units were shorter than the ring that the longer one made
+    them walk)."""
     from paper_2408_16551_amd.pfb import Batch, Plan
     F = 640
     dt = torch.complex64 if sample == "c64" else torch.float32
