@@ -335,7 +335,7 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
         bi.gfold_unit0 = gf0;
         ffu[i] = fsu[i] = gfu[i] = 0;
         if (p->fold) {
-            const int ring = fold_batch_ring(p->M);
+            const int ring = fold_batch_ring(b->form, p->cf, p->split, p->M);
             const int TF = frames_per_thread(ring);
             bi.fir_tf = TF;
             bi.fir_single = 1;  // no exponents to find for it

@@ -234,7 +234,11 @@ template <int VEC, int NG, int GL, int MT, int QM>
 __device__ __forceinline__ void fir_fold_unit(const FirArgs& a, int TF, int64_t blk, FoldSmem<VEC, NG, GL>& sm, int& ph) {
     using V = typename VecT<VEC>::T;
     using G = FoldGeom<VEC, NG, GL>;
-    constexpr int SB = G::SB < MT ? G::SB : MT;
+    // Frames walked at a time: whole rings, as many as fill an LDS phase (with one
+    // ring a phase, and so a barrier for every M frames, 256 complex channels, BF16,
+    // 2^24 samples took 182 us with 1 tap and 133 with 6; now 78 and 80; 104 and 96
+    // with the plain product).
+    constexpr int BL = fold_block_frames(MT, G::SB);
     const int ncb = fold_col_blocks<VEC, NG, GL>(a);
     const int64_t run = blk / ncb;
     const int64_t f_begin = run * TF;
@@ -247,19 +251,6 @@ __device__ __forceinline__ void fir_fold_unit(const FirArgs& a, int TF, int64_t 
 #pragma unroll
     for (int m = 0; m < MT; ++m) tp[m] = load_taps<VEC>(a, MT, m, j0);
     V win[MT];  // ring of input frames, as in fir_unit
-    auto direct = [&](int64_t f) {
-        V acc = V(0.0f);
-        // All its loads in flight before the first FMA (195 frames of 1024
-        // channels, 12 taps, half of them such: 10 us; 20 us where the
-        // compiler puts waits between the loads).
-        V in[MT];
-#pragma unroll
-        for (int m = 0; m < MT; ++m) in[m] = load_frame<VEC, true>(a, a.g0 + f - m, j0);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int m = 0; m < MT; ++m) acc = __builtin_elementwise_fma(tp[m], in[m], acc);
-        return acc;
-    };
     auto flush = [&](int64_t f0, int cnt) {
         __syncthreads();
         if constexpr (NG == 8) fold_store_split<VEC, GL, QM>(a, sm.ys[ph], f0, cnt, at.c0);
@@ -267,23 +258,45 @@ __device__ __forceinline__ void fir_fold_unit(const FirArgs& a, int TF, int64_t 
         ph ^= 1;
     };
     // Frames [f0, f1) straight from their input frames: blocks that straddle
-    // the prefix/chunk boundary, and the tail.
+    // the prefix/chunk boundary, and the tail.  All loads of D frames in flight
+    // before the first FMA (195 frames of 1024 channels, 12 taps, half of them such:
+    // 10 us; 20 us where the compiler puts waits between the loads).
+    constexpr int D = 8 / (MT * VEC) > 1 ? 8 / (MT * VEC) : 1;
+    auto direct = [&](int64_t f, int u0, int cnt) {
+        V in[D][MT];
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+                in[d][m] = load_frame<VEC, true>(a, a.g0 + f + (D > 1 ? min(u0 + d, cnt - 1) : u0) - m, j0);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            V acc = V(0.0f);
+#pragma unroll
+            for (int m = 0; m < MT; ++m) acc = __builtin_elementwise_fma(tp[m], in[d][m], acc);
+            if (D == 1 || u0 + d < cnt) *reinterpret_cast<V*>(&sm.ys[ph][u0 + d][slot]) = fold_value<VEC, QM>(acc);
+        }
+    };
     auto slow = [&](int64_t f0, int64_t f1) {
+        constexpr int SB = G::SB < BL ? G::SB : BL;
         for (int64_t f = f0; f < f1; f += SB) {
             const int cnt = (int)min((int64_t)SB, f1 - f);
-            for (int u = 0; u < cnt; ++u) *reinterpret_cast<V*>(&sm.ys[ph][u][slot]) = fold_value<VEC, QM>(direct(f + u));
+#pragma unroll 1
+            for (int u = 0; u < cnt; u += D) direct(f, u, cnt);  // unrolled: up to 250 registers
             flush(f, cnt);
         }
     };
     bool ring_ok = false;
-    int64_t fb = f_begin;
-    for (; fb + MT <= f_end; fb += MT) {
+    // LEN frames from fb on (whole rings), through the ring where they lie in the chunk.
+    auto walk = [&](auto len, int64_t fb) {
+        constexpr int LEN = decltype(len)::value, SB = G::SB < LEN ? G::SB : LEN;
         const int64_t fu = (int64_t)uniform64((uint64_t)fb);
         const int64_t eu = (a.g0 + fu + a.M - 1) * (int64_t)a.W - a.plen;  // block's first float in the chunk
         if (eu < 0) {
             ring_ok = false;
-            slow(fb, fb + MT);
-            continue;
+            slow(fb, fb + LEN);
+            return;
         }
         if (!ring_ok) {
 #pragma unroll
@@ -294,21 +307,25 @@ __device__ __forceinline__ void fir_fold_unit(const FirArgs& a, int TF, int64_t 
         const uint32_t vin = (uint32_t)j0 * 4u;
         const int32_t w4 = a.W * 4;
 #pragma unroll
-        for (int sb = 0; sb < MT; sb += SB) {
+        for (int sb = 0; sb < LEN; sb += SB) {
             V in[SB];
 #pragma unroll
             for (int i = 0; i < SB; ++i)
-                if (sb + i < MT) in[i] = buf_load<VEC, true>(rin, vin, (sb + i) * w4);
+                if (sb + i < LEN) in[i] = buf_load<VEC, true>(rin, vin, (sb + i) * w4);
 #pragma unroll
             for (int i = 0; i < SB; ++i) {
-                const int u = sb + i;
-                if (u >= MT) continue;
+                if (sb + i >= LEN) continue;
+                const int u = (sb + i) % MT;
                 win[u] = in[i];
                 *reinterpret_cast<V*>(&sm.ys[ph][i][slot]) = fold_value<VEC, QM>(fir_point<VEC, MT, true>(tp, win, u, MT));
             }
-            flush(fb + sb, MT - sb < SB ? MT - sb : SB);
+            flush(fb + sb, LEN - sb < SB ? LEN - sb : SB);
         }
-    }
+    };
+    int64_t fb = f_begin;
+    for (; fb + BL <= f_end; fb += BL) walk(std::integral_constant<int, BL>{}, fb);
+    if constexpr (BL > MT)
+        for (; fb + MT <= f_end; fb += MT) walk(std::integral_constant<int, MT>{}, fb);
     slow(fb, f_end);
 }
 
@@ -449,10 +466,11 @@ template <int VEC, int NG, int GL, int MT, int QM>
 hipError_t launch_fold_one(const FirArgs& a, hipStream_t s) {
     using G = FoldGeom<VEC, NG, GL>;
     const int ncb = fold_col_blocks<VEC, NG, GL>(a);
-    // Frames per block: whole ring blocks, two of them (at least 16 frames) so
-    // that the halo stays small; one while that leaves CUs without a block.
-    int TF = 2 * MT < 16 ? ((16 + MT - 1) / MT) * MT : 2 * MT;
-    while (TF > MT && TF > 4 && (a.F + TF - 1) / TF * ncb < 512) TF -= MT;
+    // Frames per block: two of the unit's blocks (at least 16 frames) so that the
+    // halo stays small; fewer, down to one ring, while that leaves CUs without a block.
+    constexpr int BL = fold_block_frames(MT, G::SB);
+    int TF = 2 * BL < 16 ? ((16 + BL - 1) / BL) * BL : 2 * BL;
+    while (TF > MT && TF > 4 && (a.F + TF - 1) / TF * ncb < 512) TF -= TF > BL ? BL : MT;
     const int64_t runs = (a.F + TF - 1) / TF;
     hipLaunchKernelGGL((fir_fold_kernel<VEC, NG, GL, MT, QM>), dim3((unsigned)(runs * ncb)), dim3(G::NTH), 0, s, a, TF);
     return hipGetLastError();
