@@ -24,6 +24,7 @@ namespace {
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));  // four floats at any float's address
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
@@ -63,10 +64,10 @@ __global__ __launch_bounds__(256) void narrow_kernel(NarrowArgs na) {
     const int64_t e0 = (a.g0 + f0) * (int64_t)W;
     const int valid = (nrow + M - 1) * W, total = (R + M - 1) * W;
     const float* src = a.chunk + (e0 - a.plen);
-    if (e0 >= a.plen && ((uintptr_t)src & 15) == 0) {
+    if (e0 >= a.plen) {
         for (int i = tid; i < total / 4; i += 256)
             reinterpret_cast<f32x4*>(xs)[i] =
-                4 * i < valid ? __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src) + i) : f32x4{0.f, 0.f, 0.f, 0.f};
+                4 * i < valid ? __builtin_nontemporal_load(reinterpret_cast<const f32x4_a4*>(src + 4 * i)) : f32x4{0.f, 0.f, 0.f, 0.f};
     } else {
         for (int i = tid; i < total; i += 256) {
             const int64_t e = e0 + i;
@@ -183,6 +184,18 @@ bool narrow_supported(const FirArgs& x, const GemmArgs& g) {
     // 128 complex channels: the operand fragments of 256 x 256 entries a block of
     // 32 rows reads from L2 take longer than the round trip saved (2^24 samples,
     // 8 taps: FP32 278 against 225 us, BF16x3 219 against 132 us).
+    // Frames of 128 floats in the 16-bit forms with 9 to 16 or 32 taps (exact rings in
+    // the two kernels' FIR): its LDS reads, M a float, bound a long call here.  2^25
+    // floats, one and two kernels: BF16 12 taps 102 and 96 us, 16 taps 122 and 109, 32
+    // taps 172 and 111; BF16x3 141 and 133, 159 and 148, 205 and 142; at 2^23 9 to 16
+    // taps 26-47 and 31-44, 32 taps from 2^22 on 22-36 and 23-30.  Also 32 taps over
+    // 128 floats in FP32 (123 and 119 at 2^24) and over 64 in BF16 (71 and 64).
+    const int64_t fl = x.F * x.W;
+    const bool wide = x.W == 128, f32 = g.form == FORM_FP32;
+    if (fl >= 1 << 24 && ((wide && !f32 && x.M >= 9 && x.M <= 16) ||
+                          (x.M == 32 && (wide || (x.W == 64 && g.form == FORM_BF16)))))
+        return false;
+    if (fl >= 1 << 22 && wide && !f32 && x.M == 32) return false;
     return x.W <= 128 && x.M <= 32 && !g.compensated && g.K == x.W && g.N == x.W &&
            (g.form == FORM_FP32 || g.form == FORM_BF16 || g.form == FORM_BF16X3);
 }

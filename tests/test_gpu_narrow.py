@@ -55,3 +55,16 @@ def test_output_over_the_input(P, M, cplx, F):
         x = torch.view_as_complex(x.view(-1, 2)) if cplx else x
         want = plan(x.clone())
         assert torch.equal(plan(x, out=buf[at: at + F]), want)
+
+
+@pytest.mark.parametrize("P,M,cplx,prec,F", [(128, 9, False, "bf16", 131075), (64, 16, True, "bf16x3", 131073),
+                                             (128, 32, False, "bf16x3", 32770), (64, 32, True, "fp32", 131072),
+                                             (64, 32, False, "bf16", 262147)])
+def test_long_calls_of_many_taps_take_two_kernels_with_the_same_bits(P, M, cplx, prec, F):
+    """About the sizes from which these tap counts leave the one kernel: a shorter call
+    (one kernel) gives the same frames."""
+    from paper_2408_16551_amd.pfb import Plan
+    plan = Plan(P, M, "c64" if cplx else "r32", "hann", prec)
+    x = torch.randn(F * P * (2 if cplx else 1), device="cuda")
+    x = torch.view_as_complex(x.view(-1, 2)) if cplx else x
+    assert torch.equal(plan(x)[:1000], plan(x[:1000 * P]))
