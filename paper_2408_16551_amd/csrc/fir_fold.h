@@ -288,14 +288,15 @@ __device__ __forceinline__ void fir_fold_unit(const FirArgs& a, int TF, int64_t 
         }
     };
     bool ring_ok = false;
-    // LEN frames from fb on (whole rings), through the ring where they lie in the chunk.
-    auto walk = [&](auto len, int64_t fb) {
+    // n frames from fb on (LEN, whole rings, or at the end fewer: rows past the last
+    // read the last one again), through the ring where they lie in the chunk.
+    auto walk = [&](auto len, int64_t fb, int n) {
         constexpr int LEN = decltype(len)::value, SB = G::SB < LEN ? G::SB : LEN;
         const int64_t fu = (int64_t)uniform64((uint64_t)fb);
         const int64_t eu = (a.g0 + fu + a.M - 1) * (int64_t)a.W - a.plen;  // block's first float in the chunk
         if (eu < 0) {
             ring_ok = false;
-            slow(fb, fb + LEN);
+            slow(fb, fb + n);
             return;
         }
         if (!ring_ok) {
@@ -308,10 +309,11 @@ __device__ __forceinline__ void fir_fold_unit(const FirArgs& a, int TF, int64_t 
         const int32_t w4 = a.W * 4;
 #pragma unroll
         for (int sb = 0; sb < LEN; sb += SB) {
+            if (sb >= n) break;
             V in[SB];
 #pragma unroll
             for (int i = 0; i < SB; ++i)
-                if (sb + i < LEN) in[i] = buf_load<VEC, true>(rin, vin, (sb + i) * w4);
+                if (sb + i < LEN) in[i] = buf_load<VEC, true>(rin, vin, min(sb + i, n - 1) * w4);
 #pragma unroll
             for (int i = 0; i < SB; ++i) {
                 if (sb + i >= LEN) continue;
@@ -319,14 +321,12 @@ __device__ __forceinline__ void fir_fold_unit(const FirArgs& a, int TF, int64_t 
                 win[u] = in[i];
                 *reinterpret_cast<V*>(&sm.ys[ph][i][slot]) = fold_value<VEC, QM>(fir_point<VEC, MT, true>(tp, win, u, MT));
             }
-            flush(fb + sb, LEN - sb < SB ? LEN - sb : SB);
+            flush(fb + sb, min(n - sb, LEN - sb < SB ? LEN - sb : SB));
         }
     };
     int64_t fb = f_begin;
-    for (; fb + BL <= f_end; fb += BL) walk(std::integral_constant<int, BL>{}, fb);
-    if constexpr (BL > MT)
-        for (; fb + MT <= f_end; fb += MT) walk(std::integral_constant<int, MT>{}, fb);
-    slow(fb, f_end);
+    for (; fb + BL <= f_end; fb += BL) walk(std::integral_constant<int, BL>{}, fb, BL);
+    if (fb < f_end) walk(std::integral_constant<int, BL>{}, fb, (int)(f_end - fb));
 }
 
 // One unit of more than 16 taps, any number of them: kFoldLong frames at a time,
