@@ -408,6 +408,70 @@ __device__ __forceinline__ void fir_store(const FirArgs& a, const typename VecT<
     }
 }
 
+// Frames [f_begin, f_end) of column j0 for more than 16 taps, one float a thread:
+// kFirLong frames at a time, their sums in registers, tap after tap, while the input
+// frames they meet move through a ring of that length, one older frame a tap (1 + (M -
+// 1) / 32 reads a float, all but one of them from L2).  Taps and frames are loaded
+// kFirAhead taps ahead.  In place of rings of 32 and 64 taps whose taps beyond M were
+// behind a condition each: 1024 real channels, 2^26 samples, the FIR alone, 24 taps 284
+// -> 111 us, 48 taps 5355 -> 153 (16 taps: 90).
+constexpr int kFirLong = 32, kFirAhead = 8;
+template <bool NT, int QM>
+__device__ __forceinline__ void fir_long_frames(const FirArgs& a, int j0, int gw, int64_t f_begin, int64_t f_end) {
+    constexpr int B = kFirLong, C = kFirAhead, QB = qm_bytes(QM);
+    const int M = a.M;
+    const int64_t nsc = a.W / 32;
+    for (int64_t fb = f_begin; fb < f_end; fb += B) {
+        const int cnt = (int)min((int64_t)B, f_end - fb);
+        float ring[B], acc[B], t[C], x[C], tn[C], xn[C];
+        auto ahead = [&](int m) {
+#pragma unroll
+            for (int i = 0; i < C; ++i) {
+                const int k = min(m + i, M - 1);  // past the last: reads in range, not used
+                tn[i] = load_taps<1>(a, M, k, j0);
+                xn[i] = load_frame<1, false>(a, a.g0 + fb - k, j0);
+            }
+        };
+        ahead(0);
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            ring[u] = load_frame<1, false>(a, a.g0 + fb + min(u, cnt - 1), j0);
+            acc[u] = -0.0f;  // the first multiply-add gives the product itself
+        }
+        // Tap m meets frame fb + u - m for output u, in slot (u - m) mod B.
+        for (int m0 = 0; m0 < M; m0 += B) {
+#pragma unroll
+            for (int s = 0; s < B; ++s) {
+                if (s % C == 0) {
+                    if (m0 + s >= M) break;
+#pragma unroll
+                    for (int i = 0; i < C; ++i) {
+                        t[i] = tn[i];
+                        x[i] = xn[i];
+                    }
+                    ahead(m0 + s + C);
+                }
+                if (m0 + s < M) {
+                    ring[(B - s) % B] = x[s % C];
+#pragma unroll
+                    for (int u = 0; u < B; ++u) acc[u] = fmaf(t[s % C], ring[(u - s + B) % B], acc[u]);
+                }
+            }
+        }
+        PtrSink<1, NT> o;
+        o.yb = QM ? nullptr : a.y + fb * a.ldy + j0;
+        o.qb[0] = qm_stores(QM) ? a.q + (fb * a.ldq + j0) * QB : nullptr;
+        o.qb[1] = qm_two_pieces(QM) ? a.q1 + (fb * a.ldq + j0) * QB : nullptr;
+        o.sb = QM == QM_MX ? a.qs + fb * nsc + j0 / 32 : nullptr;
+        o.ldy = a.ldy;
+        o.ldq = a.ldq * QB;
+        o.nsc = nsc;
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+            if (u < cnt) fir_store<1, QM>(a, acc[u], fb + u, j0, gw, o, u);
+    }
+}
+
 // MT: ring length (unroll); EXACT: M == MT (no per-tap predicate);
 // NT: non-temporal input loads and output stores (streaming cache policy);
 // QM: operand-form output (a.q, a.q1, a.qs; QMode) instead of FP32 (a.y).
@@ -444,6 +508,18 @@ __device__ __forceinline__ void fir_unit(const FirArgs& a, int TF, int64_t blk) 
     // these rare cases need no statically unrolled copy of the block.
     auto direct = [&](int64_t f) {
         V acc = V(0.0f);
+        if constexpr (EXACT && MT >= 32 && VEC == 1) {  // 16 loads in flight
+#pragma unroll
+            for (int m0 = 0; m0 < MT; m0 += 16) {
+                V in[16];
+#pragma unroll
+                for (int m = 0; m < 16; ++m) in[m] = load_frame<VEC, NT>(a, a.g0 + f - m0 - m, j0);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int m = 0; m < 16; ++m) acc = __builtin_elementwise_fma(tp[m0 + m], in[m], acc);
+            }
+            return acc;
+        }
 #pragma unroll
         for (int m = 0; m < MT; ++m)
             if (EXACT || m < M) acc = __builtin_elementwise_fma(tp[m], load_frame<VEC, NT>(a, a.g0 + f - m, j0), acc);
@@ -520,12 +596,21 @@ __device__ __forceinline__ void fir_unit(const FirArgs& a, int TF, int64_t blk) 
         } else {
             ring_ok = false;
             const PtrSink<VEC, NT> o = sink_ptr(fb);
+#pragma unroll 1
             for (int u = 0; u < MT; ++u) fir_store<VEC, QM>(a, direct(fb + u), fb + u, col, gw, o, u);
         }
     }
     // Tail block.
     const PtrSink<VEC, NT> o = sink_ptr(fb);
+#pragma unroll 1
     for (int u = 0; u < MT && fb + u < f_end; ++u) fir_store<VEC, QM>(a, direct(fb + u), fb + u, col, gw, o, u);
+}
+
+template <bool NT, int QM>
+__global__ __launch_bounds__(256) void fir_long_kernel(FirArgs a) {
+    const int64_t gid = xcd_logical_block(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
+    const int64_t f0 = gid / a.W * kFirLong;
+    if (f0 < a.F) fir_long_frames<NT, QM>(a, (int)(gid & (a.W - 1)), a.W < 32 ? a.W : 32, f0, min(a.F, f0 + kFirLong));
 }
 
 template <int VEC, int MT, bool EXACT, bool NT, int QM>
@@ -625,6 +710,51 @@ hipError_t launch_mt(FirArgs& a, hipStream_t s) {
     return launch_one<VEC, MT, false, MODE>(a, s);
 }
 
+// a for its frames [f0, f1).
+template <int MODE>
+FirArgs fir_part(const FirArgs& a, int64_t f0, int64_t f1) {
+    constexpr int QM = mode_qm(MODE);
+    FirArgs p = a;
+    p.g0 += f0;
+    p.F = f1 - f0;
+    if (a.y) p.y += f0 * a.ldy;
+    if (a.q) p.q += f0 * a.ldq * qm_bytes(QM);
+    if (a.q1) p.q1 += f0 * a.ldq * qm_bytes(QM);
+    if (a.qs) p.qs += f0 * (a.W / 32);
+    if (a.amax) p.amax += f0 * a.nparts;
+    if (a.fexp) p.fexp += f0;
+    return p;
+}
+
+template <int MODE>
+hipError_t launch_long(const FirArgs& a, hipStream_t s) {
+    if (a.F <= 0) return hipSuccess;
+    const int64_t threads = (a.F + kFirLong - 1) / kFirLong * a.W;
+    hipLaunchKernelGGL((fir_long_kernel<true, mode_qm(MODE)>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+// 32 or 64 taps: the exact ring for calls that are whole rings (or all but two frames)
+// from 2^22 floats on, and for the whole rings of those from 2^25 on (2^26 real samples
+// of 1024 channels, the FIR alone, us: 32 taps 103, tap after tap 118; 64 taps 141 and
+// 180).  Frames left over, and a first one that begins in the history, go tap after tap:
+// in the ring kernel, frame by frame, their loads wait for one another.  That is two
+// launches more, and below 2^25 floats tap after tap takes no longer than all of them
+// (20 M complex floats through a state: 32 taps 44, 58 with three launches, 151 by the
+// ring alone; 64 taps 59, 83, 177).
+template <int MT, int MODE>
+hipError_t launch_ring_long(FirArgs& a, hipStream_t s) {
+    const int64_t head = (a.g0 + a.M - 1) * (int64_t)a.W < a.plen ? 1 : 0;
+    const int64_t rings = (a.F - head) / MT * MT, tail = a.F - head - rings, floats = a.F * a.W;
+    if (!head && tail <= 2 && floats >= 1 << 22) return launch_one<1, MT, true, MODE>(a, s);
+    if (floats < 1 << 25) return launch_long<MODE>(a, s);
+    FirArgs ring = fir_part<MODE>(a, head, head + rings);
+    hipError_t e = launch_one<1, MT, true, MODE>(ring, s);
+    if (e == hipSuccess && head) e = launch_long<MODE>(fir_part<MODE>(a, 0, head), s);
+    if (e == hipSuccess && tail) e = launch_long<MODE>(fir_part<MODE>(a, a.F - tail, a.F), s);
+    return e;
+}
+
 template <int VEC, int MODE>
 hipError_t launch_vec(FirArgs& a, hipStream_t s) {
     if (a.M <= 1) return launch_mt<VEC, 1, MODE>(a, s);
@@ -632,11 +762,13 @@ hipError_t launch_vec(FirArgs& a, hipStream_t s) {
     if (a.M <= 4) return launch_mt<VEC, 4, MODE>(a, s);
     if (a.M <= 8) return launch_mt<VEC, 8, MODE>(a, s);
     if (a.M <= 16) return launch_mt<VEC, 16, MODE>(a, s);
-    if constexpr (VEC <= 2) {
-        if (a.M <= 32) return launch_mt<VEC, 32, MODE>(a, s);
+    if constexpr (VEC == 2) {  // (a tuning choice)
+        if (a.M <= 32) return launch_mt<2, 32, MODE>(a, s);
     }
     if constexpr (VEC == 1) {
-        if (a.M <= 64) return launch_mt<VEC, 64, MODE>(a, s);
+        if (a.M == 32) return launch_ring_long<32, MODE>(a, s);
+        if (a.M == 64) return launch_ring_long<64, MODE>(a, s);
+        return launch_long<MODE>(a, s);
     }
     return hipErrorInvalidValue;
 }
