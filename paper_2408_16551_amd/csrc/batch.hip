@@ -241,11 +241,9 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
     const int MT = pow2_at_least(max_m);
     all_exact = true;
     for (int i = 0; i < g.count; ++i) all_exact = all_exact && w[g.first + i].plan->M == MT;
-    // Frames per FIR thread, a whole number of the unit's ring blocks: the
-    // ring is MT frames long, or the item's own M when mixed tap counts up to
-    // 16 run per-M units; the tuned number of them, down to one where the units
-    // would be fewer than two per block of the persistent grid: a short step lasts
-    // as long as its last unit.
+    // Frames per FIR thread, a whole number of the blocks a unit walks: the tuned
+    // number, down to one where the units would be fewer than two per block of the
+    // persistent grid (a short step lasts as long as its last unit).
     int64_t all_floats = 0;
     for (int i = 0; i < g.count; ++i) all_floats += frames[g.first + i] * w[g.first + i].plan->W;
     auto frames_per_thread = [&](int ring) {
@@ -355,12 +353,11 @@ void fill_table(tina_pfb_batch_s* b, tina_pfb_work* w, const std::vector<int64_t
             ru[i] = F > 0 ? (F + TF - 1) / TF : 0;
             rc[i] = (double)TF * p->W * p->M;
         } else {
-            const int ring = (!all_exact && MT <= 16) ? p->M : MT;
-            const int TF = frames_per_thread(ring);
+            const int TF = frames_per_thread(fir_batch_block(all_exact && MT <= 16 ? MT : p->M));
             bi.fir_tf = TF;
             const int64_t runs = (F + TF - 1) / TF;
             fu[i] = F > 0 ? (runs * p->W + 255) / 256 : 0;
-            fc[i] = (double)TF * ring;
+            fc[i] = (double)TF * p->M;
             ru[i] = 0;
         }
         r0 += ru[i];

@@ -537,7 +537,7 @@ __device__ __forceinline__ void fir_unit(const FirArgs& a, int TF, int64_t blk) 
     // pointers, choosing between prefix and chunk per load.  The choice is
     // uniform over the wave's active lanes, so the lanes that share a block
     // maximum of the block-scaled output take the same path.
-    constexpr int SB = (VEC == 4 ? 8 : 16) < MT ? (VEC == 4 ? 8 : 16) : MT;
+    constexpr int SB = VEC == 4 ? 8 : 16;
     const int64_t nsc = a.W / 32;
     constexpr int QB = qm_bytes(QM);  // bytes per operand element
     auto sink_ptr = [&](int64_t fb) {
@@ -552,14 +552,15 @@ __device__ __forceinline__ void fir_unit(const FirArgs& a, int TF, int64_t blk) 
         return o;
     };
     bool ring_ok = false;
-    int64_t fb = f_begin;
-    for (; fb + MT <= f_end; fb += MT) {
+    // LEN frames from fb on, whole rings.
+    auto walk = [&](auto len, int64_t fb) {
+        constexpr int LEN = decltype(len)::value, SBL = SB < LEN ? SB : LEN;
         const int64_t e_row = (a.g0 + fb + a.M - 1) * (int64_t)a.W - a.plen;  // block's first float in the chunk
         if (ct >= 64 ? e_row >= 0 : (bool)__all(e_row >= 0)) {
             if (!ring_ok) load_ring(fb);
             ring_ok = true;
             const int64_t fu = (int64_t)uniform64((uint64_t)fb);
-            const uint32_t ahead = ct >= 64 ? 0u : (uint32_t)(fb - fu);  // frames from the first lane's block to this one's
+            const uint32_t ahead = ct >= 64 ? 0u : (uint32_t)(fb - fu);  // frames from the first active lane's block to this one's
             const int64_t eu = (a.g0 + fu + a.M - 1) * (int64_t)a.W - a.plen;
             const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.chunk + eu, (a.nchunk - eu) * 4);
             const uint32_t vin = (uint32_t)(j0 + ahead * a.W) * 4u;
@@ -581,29 +582,38 @@ __device__ __forceinline__ void fir_unit(const FirArgs& a, int TF, int64_t blk) 
                 o.ldy4 = (int32_t)(a.ldy * 4);
             }
 #pragma unroll
-            for (int sb = 0; sb < MT; sb += SB) {
-                V in[SB];
+            for (int sb = 0; sb < LEN; sb += SBL) {
+                V in[SBL];
 #pragma unroll
-                for (int i = 0; i < SB; ++i) in[i] = buf_load<VEC, NT>(rin, vin, (sb + i) * w4);
+                for (int i = 0; i < SBL; ++i) in[i] = buf_load<VEC, NT>(rin, vin, (sb + i) * w4);
 #pragma unroll
-                for (int i = 0; i < SB; ++i) {
+                for (int i = 0; i < SBL; ++i) {
                     const int u = sb + i;
-                    win[u] = in[i];
-                    const V acc = fir_point<VEC, MT, EXACT>(tp, win, u, M);
+                    win[u % MT] = in[i];
+                    const V acc = fir_point<VEC, MT, EXACT>(tp, win, u % MT, M);
                     fir_store<VEC, QM>(a, acc, fb + u, col, gw, o, u);
                 }
             }
         } else {
             ring_ok = false;
-            const PtrSink<VEC, NT> o = sink_ptr(fb);
+            const PtrSink<VEC, NT> po = sink_ptr(fb);
 #pragma unroll 1
-            for (int u = 0; u < MT; ++u) fir_store<VEC, QM>(a, direct(fb + u), fb + u, col, gw, o, u);
+            for (int u = 0; u < LEN; ++u) fir_store<VEC, QM>(a, direct(fb + u), fb + u, col, gw, po, u);
         }
-    }
+    };
+    // Several short rings at a time: a block sets up its buffer resources and has only
+    // its own loads in flight (1 tap: 1024 real channels, 2^26 samples 114 -> 97 us, 32
+    // complex channels, 2^24 77 -> 51; a batch of 256 channels, 1 to 4 taps, FP16 368 ->
+    // 200).
+    constexpr int BL = EXACT ? fold_block_frames(MT, 8) : MT;
+    int64_t fb = f_begin;
+    for (; fb + BL <= f_end; fb += BL) walk(std::integral_constant<int, BL>{}, fb);
+    if constexpr (BL > MT)
+        for (; fb + MT <= f_end; fb += MT) walk(std::integral_constant<int, MT>{}, fb);
     // Tail block.
-    const PtrSink<VEC, NT> o = sink_ptr(fb);
+    const PtrSink<VEC, NT> po = sink_ptr(fb);
 #pragma unroll 1
-    for (int u = 0; u < MT && fb + u < f_end; ++u) fir_store<VEC, QM>(a, direct(fb + u), fb + u, col, gw, o, u);
+    for (int u = 0; u < MT && fb + u < f_end; ++u) fir_store<VEC, QM>(a, direct(fb + u), fb + u, col, gw, po, u);
 }
 
 template <bool NT, int QM>
@@ -631,8 +641,8 @@ __device__ __forceinline__ void fir_unit_own_m(const FirArgs& a, int TF, int64_t
 
 // Persistent batched FIR: each block walks its XCD's contiguous, cost-balanced
 // range of units (see BatchTable); a unit is one 256-thread block of one item.
-// Batches whose largest tap count is at most 16 with mixed tap counts run
-// every item's units with the ring unrolled for its own M.
+// Batches with mixed tap counts run every item's units with the ring unrolled for its
+// own M, or tap after tap beyond 16 taps (MT = 17: such items among them).
 template <int MT, bool EXACT, int QM>
 __global__ __launch_bounds__(256) void fir_batch_kernel(const BatchTable* __restrict__ t) {
     const int x = blockIdx.x & 7, i = blockIdx.x >> 3, nbx = gridDim.x >> 3;
@@ -643,7 +653,15 @@ __global__ __launch_bounds__(256) void fir_batch_kernel(const BatchTable* __rest
         // A private copy of the item's arguments: read through the table, every
         // field would be reloaded after each output store (they might alias).
         const FirArgs fa = b.fir;
-        if constexpr (!EXACT && MT <= 16) fir_unit_own_m<1, MT, QM>(fa, b.fir_tf, u - b.fir_unit0);
+        if constexpr (MT > 16) {
+            if (fa.M > 16) {
+                const int64_t gid = (u - b.fir_unit0) * 256 + threadIdx.x, f0 = gid / fa.W * b.fir_tf;
+                if (f0 < fa.F)
+                    fir_long_frames<true, QM>(fa, (int)(gid & (fa.W - 1)), fa.W < 32 ? fa.W : 32, f0, min(fa.F, f0 + b.fir_tf));
+            } else {
+                fir_unit_own_m<1, 16, QM>(fa, b.fir_tf, u - b.fir_unit0);
+            }
+        } else if constexpr (!EXACT) fir_unit_own_m<1, MT, QM>(fa, b.fir_tf, u - b.fir_unit0);
         else fir_unit<1, MT, EXACT, true, QM>(fa, b.fir_tf, u - b.fir_unit0);
     }
 }
@@ -796,9 +814,9 @@ hipError_t launch_batch_mode(const BatchTable* t, int max_m, bool all_exact, int
     if (max_m <= 4) return go(std::integral_constant<int, 4>{});
     if (max_m <= 8) return go(std::integral_constant<int, 8>{});
     if (max_m <= 16) return go(std::integral_constant<int, 16>{});
-    if (max_m <= 32) return go(std::integral_constant<int, 32>{});
-    if (max_m <= 64) return go(std::integral_constant<int, 64>{});
-    return hipErrorInvalidValue;
+    if (max_m > 64) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((fir_batch_kernel<17, false, QM>), dim3(grid), dim3(256), 0, s, t);
+    return hipGetLastError();
 }
 
 }  // namespace

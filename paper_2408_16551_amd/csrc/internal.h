@@ -153,11 +153,12 @@ hipError_t launch_fold_tables(float* tw, float* ct, float* ones, int P, float sc
 inline int fold_batch_vec(int form, int cf, int M) { return form != FORM_FP32 && cf == 2 && M <= 16 ? 2 : 1; }
 // ... and floats per column block of a split item: eight groups of 64 lanes.
 constexpr int kFoldSplitCols = 8 * 64;
-// Frames that the folded FIR of M <= 16 taps walks at a time: whole rings of M, in
-// one LDS phase of `sb` frames where that holds several.
+// Frames that a FIR unit of M <= 16 taps walks at a time: whole rings of M, as many
+// as sb frames hold (sb: its loads in flight, or the frames of an LDS phase).
 constexpr int fold_block_frames(int M, int sb) { return M < sb ? sb / M * M : M; }
-// ... and that the batched one walks for an item; its units are whole numbers of
-// them, whatever the launch's other items.
+// ... and that the batched FIR and folded FIR walk for an item; their units are whole
+// numbers of them, whatever the launch's other items.
+constexpr int fir_batch_block(int M) { return M > 16 ? 32 : fold_block_frames(M, 8); }
 inline int fold_batch_ring(int form, int cf, bool split, int M) {
     return M > 16 ? 32 : fold_block_frames(M, split ? 8 : 16 / fold_batch_vec(form, cf, M));
 }
