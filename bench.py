@@ -6,10 +6,12 @@ One step = one tina_pfb_execute over the whole real stream (1024 channels,
 GEMM): the polyphase FIR kernel then the DFT-GEMM kernel, input resident in
 HBM.  Prints ONE JSON line with the throughput (input GSamples/s), the
 roofline of the dominant kernel (HIP events on the launch stream, inside the
-timed region), the other precision forms with their error against the FP64
-oracle, and the oracle itself timed on the host cores on a bounded sample.
+timed region), and in short the other precision forms with their error against
+the FP64 oracle, the batched, serving and standalone legs, and the oracle itself
+timed on the host cores on a bounded sample.  Every leg's full figures go to
+stderr, and with --details to a file.
 
-    python bench.py [--steps K] [--warmup W] [--gpus 1]
+    python bench.py [--steps K] [--warmup W] [--gpus 1] [--details FILE]
 """
 from __future__ import annotations
 
@@ -737,6 +739,27 @@ def check_oracle():
     return Oracle()
 
 
+LINE_BYTES = 4096  # the line stays whole in the tail of a log
+
+
+def summary(result: dict) -> dict:
+    """The printed line: the headline's fields as they are, and of each leg the
+    throughput, the error and the latencies alone."""
+    r = {k: v for k, v in result.items() if k not in ("forms", "ops", "batched", "serving", "cpu_context")}
+    if "cpu_baseline" in r:
+        r["cpu_baseline"] = {k: v for k, v in r["cpu_baseline"].items() if k != "sample"}
+    if "forms" in result:
+        r["forms"] = {w: {f: {"gsps": x["gsps"], "rel_l2": x["rel_l2_vs_fp64_oracle"]} for f, x in t.items()}
+                      for w, t in result["forms"].items()}
+    if "batched" in result:
+        r["batched_gsps"] = {k: v["gsps"] for k, v in result["batched"].items() if isinstance(v, dict) and "gsps" in v}
+    if "serving" in result:
+        r["serving"] = [f"{x['precision']} {'device' if x['buffers'].startswith('device') else 'host'} "
+                        f"{x['hbm_budget_bytes'] >> 20} MiB rho {x['rho']}: p50 {x['p50_ms']} p99 {x['p99_ms']} ms, "
+                        f"{x['gsps_served']} GS/s" for x in result["serving"]]
+    return r
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -757,6 +780,7 @@ def main():
                     help="timed steps per form (0: 20, after 5 warm-up steps, on both workloads)")
     ap.add_argument("--no-fir-only", action="store_true", help="skip the FIR-only run")
     ap.add_argument("--no-ops", action="store_true", help="skip the standalone building blocks")
+    ap.add_argument("--details", default="", help="file for the full figures of every leg (JSON)")
     ap.add_argument("--copy-probe", action="store_true",
                     help="run only a plain 1 GiB device copy (for scaling rocprofv3 byte counters)")
     args = ap.parse_args()
@@ -872,7 +896,16 @@ def main():
         wd = workloads.wide_dynamic_range()
         result["cpu_context"]["precision_workload"] = cpu_context_precision(wd)
         del wd
-    print(json.dumps(result), flush=True)
+    for leg in ("serving", "cpu_context"):
+        if leg in result:
+            log(f"[bench] {leg}: {json.dumps(result[leg])}")
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(result, f, indent=1)
+    line = json.dumps(summary(result))
+    if len(line) > LINE_BYTES:
+        log(f"[bench] the line has {len(line)} bytes")
+    print(line, flush=True)
 
 
 if __name__ == "__main__":

@@ -53,3 +53,37 @@ def test_channel_errors_names_worst_channel_and_weakest_tone():
     assert abs(e["worst_channel_rel_l2"] - 0.5) < 1e-12
     assert e["weakest_tone"]["channel"] == 5
     assert abs(e["weakest_tone"]["rel_l2"] - 1e-3) < 1e-12
+
+
+def test_line_of_a_full_run_stays_short_and_keeps_the_headline():
+    """A result of every leg at its full size (ten forms on two workloads, three
+    batches, ten serving runs with their latency parts): the printed line holds the
+    headline's fields and stays under LINE_BYTES."""
+    import json
+    form = {k: 123456.789 for k in ("gsps", "ms_per_step", "dft_ms", "fir_ms", "dft_useful_tflops", "dft_mfma_frac",
+                                    "worst_channel_rel_l2", "fir_hbm_gbs")}
+    form.update(rel_l2_vs_fp64_oracle=1.234e-07, weakest_tone={"channel": 2812, "rel_l2": 1e-3})
+    names = ["fp32", "bf16", "bf16x3", "fp16", "fp16x3", "fp8", "mxfp8", "fp32/factored", "fp32/compensated", "fp32/table"]
+    head = {"metric": "PFB input GSamples/s (FP32 DFT GEMM; reduced-precision forms at their rel. error in 'forms')",
+            "value": 144.123, "unit": "GSamples/s", "n_gpus": 1, "steps": 50, "warmup": 20, "ms_per_step": 0.4661,
+            "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f32",
+            "data": "synthetic (seeded N(0,1) noise + 8 channel-centre tones)",
+            "config": {"workload": "real_stream_r32_p1024_m16", "channels": 1024, "taps": 16, "window": "sinc x hann",
+                       "samples": 1 << 26, "sample_type": "r32", "precision": "fp32"}}
+    stage = {"kernel": "fold_gemm_kernel<FP32>", "bound": "mfma", "achieved": 101.23, "peak": 157.3, "unit": "TFLOP/s",
+             "frac": 0.6436, "avg_launch_ms": 0.3181}
+    served = {"precision": "fp32/factored", "hbm_budget_bytes": 8 << 30, "rho": 0.5, "buffers": "device (in place)",
+              "p50_ms": 0.344, "p99_ms": 12.345, "gsps_served": 91.234, "latency_parts": {str(i): 1.0 / 3 for i in range(80)}}
+    full = dict(head, roofline=dict(stage, traffic=590123456.0),
+                stages={"fir": stage}, forms={w: {n: form for n in names} for w in ("real_stream_r32_p1024_m16",
+                                                                                    "wide_dynamic_range_c64_p4096_m8")},
+                fir_only={"gsps": 700.12, "kernel_ms": 0.0921, "hbm_gbs": 5812.3, "hbm_frac": 0.7265},
+                ops={str(i): form for i in range(9)}, batched={"streams": 64, "fp32": form, "bf16x3": form, "fp32/factored": form},
+                serving=[served] * 10, cpu_context={str(i): 1.5 for i in range(90)},
+                cpu_baseline={"value": 0.035123, "unit": "GSamples/s", "cores": 16, "kind": "oracle", "sample": "y" * 400})
+    line = json.dumps(bench.summary(full))
+    assert len(json.dumps(full)) > 16000 and len(line) < bench.LINE_BYTES
+    got = json.loads(line)
+    assert {k: got[k] for k in head} == head
+    assert got["roofline"]["achieved"] == 101.23 and got["forms"]["real_stream_r32_p1024_m16"]["fp8"]["gsps"] == 123456.789
+    assert got["roofline"]["traffic"] == 590123456.0
