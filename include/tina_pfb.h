@@ -160,10 +160,9 @@ typedef struct tina_pfb_desc {
  *                      Also in FP32 batches (one launch over those items'
  *                      frames) and in an FP32 server created with this algorithm.
  *   TINA_DFT_FUSED     the dense FP32 product for taps <= 16 and single-stream
- *                      execute, bit for bit TINA_DFT_DENSE.  It runs the FIR and
- *                      the product as two kernels like TINA_DFT_DENSE: a product
- *                      with the FIR inside its tiles forms each FIR row once per
- *                      column tile and measured slower at every size.
+ *                      execute, bit for bit TINA_DFT_DENSE and by its kernels: a
+ *                      product with the FIR inside its tiles forms each FIR row once
+ *                      per column tile and measured slower at every size.
  *   TINA_DFT_COMPENSATED the dense FP32 product with compensated accumulation
  *                      over K: each K tile of 32 products is summed on its
  *                      own, and the tile sums are added to the running sum
