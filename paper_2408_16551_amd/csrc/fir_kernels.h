@@ -604,7 +604,7 @@ __device__ __forceinline__ void fir_unit(const FirArgs& a, int TF, int64_t blk) 
     // Several short rings at a time: a block sets up its buffer resources and has only
     // its own loads in flight (1 tap: 1024 real channels, 2^26 samples 114 -> 97 us, 32
     // complex channels, 2^24 77 -> 51; a batch of 256 channels, 1 to 4 taps, FP16 368 ->
-    // 200).
+    // 213).
     constexpr int BL = EXACT ? fold_block_frames(MT, 8) : MT;
     int64_t fb = f_begin;
     for (; fb + BL <= f_end; fb += BL) walk(std::integral_constant<int, BL>{}, fb);
