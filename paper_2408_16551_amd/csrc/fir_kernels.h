@@ -752,19 +752,22 @@ hipError_t launch_long(const FirArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// 32 or 64 taps: the exact ring for calls that are whole rings (or all but two frames)
-// from 2^22 floats on, and for the whole rings of those from 2^25 on (2^26 real samples
-// of 1024 channels, the FIR alone, us: 32 taps 103, tap after tap 118; 64 taps 141 and
-// 180).  Frames left over, and a first one that begins in the history, go tap after tap:
-// in the ring kernel, frame by frame, their loads wait for one another.  That is two
-// launches more, and below 2^25 floats tap after tap takes no longer than all of them
-// (20 M complex floats through a state: 32 taps 44, 58 with three launches, 151 by the
-// ring alone; 64 taps 59, 83, 177).
+// 32 or 64 taps: the exact ring for calls that are whole rings (or all but a few frames,
+// which the ring kernel takes one by one) from 2^22 floats on, and for the whole rings of
+// those from 2^25 on (2^26 real samples of 1024 channels, the FIR alone, us: 32 taps 103,
+// tap after tap 118; 64 taps 141 and 180).  The few: at 2^22 floats 4 frames over take
+// 15.7 by the ring and 17.6 tap after tap (64 taps: 21.0, 23.2), 8 take 20.6 and 17.3
+// (28.4, 22.6); at 1.5 * 2^24 8 take 46 and 56 (65, 77), 16 take 56 and 56 (80, 79).
+// More, and a first one that begins in the history, go tap after tap: in the ring
+// kernel, frame by frame, their loads wait for one another.  That is two launches more,
+// and below 2^25 floats tap after tap takes no longer than all of them (20 M complex
+// floats through a state: 32 taps 44, 58 with three launches, 151 by the ring alone; 64
+// taps 59, 83, 177).
 template <int MT, int MODE>
 hipError_t launch_ring_long(FirArgs& a, hipStream_t s) {
     const int64_t head = (a.g0 + a.M - 1) * (int64_t)a.W < a.plen ? 1 : 0;
     const int64_t rings = (a.F - head) / MT * MT, tail = a.F - head - rings, floats = a.F * a.W;
-    if (!head && tail <= 2 && floats >= 1 << 22) return launch_one<1, MT, true, MODE>(a, s);
+    if (!head && floats >= 1 << 22 && tail <= (floats < 3 << 23 ? 4 : 8)) return launch_one<1, MT, true, MODE>(a, s);
     if (floats < 1 << 25) return launch_long<MODE>(a, s);
     FirArgs ring = fir_part<MODE>(a, head, head + rings);
     hipError_t e = launch_one<1, MT, true, MODE>(ring, s);

@@ -43,9 +43,9 @@ def test_tap_and_frame_counts(oracle, P, cplx, prec, dft, out):
 @pytest.mark.parametrize("M", [32, 64])
 @pytest.mark.parametrize("P,cplx,prec", [(128, False, "fp16"), (64, True, "bf16"), (128, True, "mxfp8"), (128, False, "fp8")])
 def test_long_calls_in_whole_rings_first_and_last_frames(P, cplx, prec, M):
-    """2^25 floats and more (the rings apart from the rest) and 2^22 (whole rings and two
-    frames), frames left over, the first one begun in the history: the same stream in
-    one call, in two through a state and in a batch, bit for bit."""
+    """2^25 floats and more (the rings apart from the rest), 2^22 and 3 * 2^23 (whole
+    rings and a few frames more), frames left over, the first one begun in the history:
+    the same stream in one call, in two through a state and in a batch, bit for bit."""
     from paper_2408_16551_amd.pfb import Batch, Plan, State
     W = P * (2 if cplx else 1)
     F = (1 << 25) // W + 77
@@ -58,5 +58,5 @@ def test_long_calls_in_whole_rings_first_and_last_frames(P, cplx, prec, M):
     o = plan.alloc_out(F + 3)
     Batch(prec, max_items=1, workspace_bytes=1 << 28).execute([(plan, x, o)])
     assert torch.equal(o, got)
-    n = (1 << 22) // W + 2
-    assert torch.equal(plan(x[:n * P]), got[:n])
+    for n in ((1 << 22) // W + 4, (1 << 22) // W + 5, (3 << 23) // W + 8, (3 << 23) // W + 9):
+        assert torch.equal(plan(x[:n * P]), got[:n])
