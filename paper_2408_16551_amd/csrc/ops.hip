@@ -5,9 +5,10 @@
 // width/stride times the input; each thread writes 4 consecutive outputs
 // (one 16-byte store when a row holds whole groups of 4).
 //
-// FIR: y[i] = sum_k a[k] x[i-k], as a product with the Toeplitz matrix of the
-// taps on the FP32 matrix units: 16 consecutive outputs are the rows of a
-// 16 x 16 MFMA tile, 16 such runs its columns,
+// FIR: y[i] = sum_k a[k] x[i-k].  Up to 16 taps (complex samples: 9) as it stands, on
+// the vector units; beyond as a product with the Toeplitz matrix of the taps on the
+// FP32 matrix units: 16 consecutive outputs are the rows of a 16 x 16 MFMA tile, 16
+// such runs its columns,
 //   Y[m][n] = sum_q T[m][q] x[16 n - H + q],  T[m][q] = a[H + m - q], H >= K - 1,
 // q < H + 16 in slabs of 16.  The vector units (no packed FP32) reach half the
 // matrix units' rate, of which the product wastes 15 / (K + 15); with 129 taps
@@ -48,6 +49,58 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));  // four floats at any float's address
 
+// Few taps: four floats a thread straight from its loads, no LDS and no barrier; of a
+// thread's loads all but one hit L1, whose rate bounds it as the taps grow.  Bound by HBM
+// in long calls, by one load's latency in short ones.  us here, by the product below and
+// as the LDS form with a multiply-add a tap that preceded both:
+//                                        8 taps              9 taps           16 taps
+//   4 M real, one buffer            5.1   8.3   7.4    5.1   8.3   7.7    5.9   8.3   9.2
+//   4 M real, buffers in turn       7.8   9.7  10.9    7.8   9.8  11.1    8.1   9.7  12.7
+//   2 M complex, one buffer         5.9   7.8   7.4    5.9   7.8   7.6    7.6   7.8   9.2
+//   2 M complex, buffers in turn    8.2   9.7  10.9    8.2   9.9  11.2   10.5   9.7  12.7
+//   2^26 real                      88.6  93.0   133   85.7  93.0   134   90.8  93.1   141
+//   2^26 complex                    182   182   260    181   182   264    266   182   276
+// 18 real taps take 98 over 2^26 (92), 10 complex ones 197 (183): the lines below.
+constexpr int direct_taps(int cf) { return cf == 1 ? 16 : 9; }
+template <int K, int CF>
+__global__ __launch_bounds__(256) void fir_direct_kernel(const float* __restrict__ x, int64_t nf,
+                                                         const float* __restrict__ taps, float* __restrict__ y) {
+    constexpr int H = (CF * (K - 1) + 3) & ~3, L = H / 4 + 1;
+    const int64_t b0 = (int64_t)blockIdx.x * 1024, at0 = b0 + 4 * threadIdx.x;
+    float t[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) t[k] = taps[k];
+    auto run = [&](auto edge) {
+        f32x4 w[L], acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int l = 0; l < L; ++l) {
+            const int64_t at = at0 - H + 4 * l;  // a multiple of 4
+            if (!edge || (at >= 0 && at + 4 <= nf)) {
+                w[l] = *reinterpret_cast<const f32x4_a4*>(x + at);
+            } else {
+                w[l] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (at >= 0)
+#pragma unroll
+                    for (int e = 0; e < 3; ++e)
+                        if (at + e < nf) w[l][e] = x[at + e];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] = fmaf(t[k], w[(H + e - CF * k) / 4][(H + e - CF * k) % 4], acc[e]);
+        if (!edge || at0 + 4 <= nf) {
+            *reinterpret_cast<f32x4_a4*>(y + at0) = acc;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+                if (at0 + e < nf) y[at0 + e] = acc[e];
+        }
+    };
+    if (b0 >= H && b0 + 1024 <= nf) run(std::false_type{});
+    else run(std::true_type{});
+}
+
 // Four waves of NT column tiles (256 outputs each; complex: NT / 2 for the real
 // and NT / 2 for the imaginary parts).  LDS: the block's input, one plane per
 // part (from H samples before the block's first output, H = K - 1 rounded up to
@@ -73,10 +126,9 @@ __global__ __launch_bounds__(256) void fir_toeplitz_kernel(const float* __restri
     // A block's samples and taps are all in flight before the first LDS store, four
     // floats a load whatever their alignment, in the first and the last block too:
     // calls of a few blocks a CU are bound by these latencies, one after another.
-    // 8 taps, buffers in turn: 2 M complex samples 11.4 -> 9.7 us (as float4s on 16
-    // bytes alone, the edges float by float, the taps after the samples; 10.9 as one
-    // multiply-add a tap on the vector units), 65536 complex 4.8 -> 3.3 (4.3), 4 M real
-    // a float off 16 bytes 18.2 -> 10.2 (11.5).
+    // Buffers in turn: 2 M complex samples, 12 taps 11.5 -> 9.7 us (as float4s on 16 bytes
+    // alone, the edges float by float, the taps after the samples), 65536 complex 4.8 ->
+    // 3.3, 4 M real a float off 16 bytes 18.2 -> 10.2.
     const int64_t lo = (i0 - H) * CF, nf = n * CF;  // lo: a multiple of 4
     constexpr int U = CF * NBP / 4 / 256;
     auto tap = [&](int i) {
@@ -198,6 +250,17 @@ hipError_t launch_toeplitz(const float* x, int64_t n, const float* taps, int K, 
     return hipGetLastError();
 }
 
+template <int CF, int K = 1>
+hipError_t launch_direct(const float* x, int64_t n, const float* taps, int k, float* y, hipStream_t s) {
+    if constexpr (K <= direct_taps(CF)) {
+        if (k != K) return launch_direct<CF, K + 1>(x, n, taps, k, y, s);
+        const int64_t nf = n * CF;
+        hipLaunchKernelGGL((fir_direct_kernel<K, CF>), dim3((unsigned)((nf + 1023) / 1024)), dim3(256), 0, s, x, nf, taps, y);
+        return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
+}
+
 }  // namespace
 
 struct tina_fir_s {
@@ -293,7 +356,9 @@ tina_status tina_fir_execute(tina_fir_t f, const void* d_x, int64_t n, void* d_y
     // 18.3 and 17.7, 12 M 41.6 and 42.2, 16.8 M real 29.6 and 32.7).
     const bool big = nf >= 2048 * 4096;
     hipError_t e;
-    if (f->cf == 1) e = big ? launch_toeplitz<4, 1>(x, n, f->taps, f->K, y, s) : launch_toeplitz<1, 1>(x, n, f->taps, f->K, y, s);
+    if (f->K <= direct_taps(f->cf))
+        e = f->cf == 1 ? launch_direct<1>(x, n, f->taps, f->K, y, s) : launch_direct<2>(x, n, f->taps, f->K, y, s);
+    else if (f->cf == 1) e = big ? launch_toeplitz<4, 1>(x, n, f->taps, f->K, y, s) : launch_toeplitz<1, 1>(x, n, f->taps, f->K, y, s);
     else e = big ? launch_toeplitz<4, 2>(x, n, f->taps, f->K, y, s) : launch_toeplitz<2, 2>(x, n, f->taps, f->K, y, s);
     HIP_TRY(e);
     return TINA_OK;
